@@ -212,6 +212,19 @@ static PassAConfig pass_a_config(const sk_plan_desc& d, int64_t B, const PassATu
   t->cs = nullptr;
   t->timeline = nullptr;
   t->simd_balance = 1;
+  if (u.lpr == 0 && u.variant < 0 && u.grid == 0 && u.blocks == 0) {
+    if (const int lanes = pass_a_phased_lanes(d_packed, t->row_bytes, d.n_inputs, B, d.block_len)) {
+      t->col_groups = (int32_t)((t->row_bytes + 15) / 16);
+      t->chunks = 1;
+      t->n_tasks = (B * t->col_groups + lanes - 1) / lanes;
+      PassAConfig c;
+      c.vec = 16;
+      c.lpr = lanes;
+      c.variant = 5;
+      c.grid = (int)t->n_tasks;
+      return c;
+    }
+  }
   PassAConfig c = default_pass_a_config(vec, t->row_bytes, B, d.block_len, u.lpr == 0 && u.variant < 0, u.n_cu);
   if (u.lpr) c.lpr = u.lpr;
   if (u.variant >= 0) c.variant = u.variant;

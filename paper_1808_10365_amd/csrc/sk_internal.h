@@ -58,7 +58,7 @@ struct PassATask {
 struct PassAConfig {
   int vec;     // 16, 4 or 1 bytes per lane per row
   int lpr;     // lanes per row: power of two, 1..256
-  int variant; // 0 shared table; 16-byte path: 1, 2 packed, 3 side by side, 4 deferred stores
+  int variant; // 0 shared table; 16-byte path: 1, 2 packed, 3 side by side, 4 deferred stores; 5 phased
   int grid;    // workgroups launched (<= tasks; grid-stride beyond)
 };
 
@@ -81,6 +81,8 @@ inline void launch_kernel(void (*k)(P...), dim3 grid, dim3 wg, uint32_t lds, hip
 
 int launch_pass_a(const PassATask& t, const PassAConfig& c, hipStream_t s, PassEvents ev = PassEvents());
 int pick_vec(const uint8_t* x, int32_t n_inputs);
+// Variant 5: units of 16 columns per workgroup, or 0 where it does not suit.
+int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len);
 // Lanes per row the variant supports; the planner clamps into [lo, hi].
 void pass_a_lane_range(int vec, int variant, int* lo, int* hi);
 // Whether the variant uses the packed lane table (tasks may span several blocks).

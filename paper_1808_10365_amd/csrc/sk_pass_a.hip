@@ -20,10 +20,13 @@
 //     rows put 256 / L blocks side by side.
 //   4 packed table, 512-lane workgroups walking up to 4 consecutive blocks
 //     with every block's sums held in registers and stored at the task's end.
+//   5 packed table, 512-lane workgroups of row phases over runs of 16-byte units,
+//     any N and alignment (library choice only).
 #include <hip/hip_runtime.h>
 
 #include "sk_internal.h"
 #include "sk_pass_a_dev.h"
+#include "sk_wave_dev.h"
 
 namespace sk {
 
@@ -296,6 +299,215 @@ __global__ __launch_bounds__(512) void pass_a_deferred_kernel(PassATask t) {
   }
 }
 
+// Stores four columns from column c on (S1 a, S2 b) of block `blk`; they may
+// straddle channels, and the sums' rows need only 4-byte alignment.
+__device__ __forceinline__ void store_quad(const PassATask& t, int blk, int c, u32x4 a, u32x4 b) {
+  typedef u32x4 u32x4_word __attribute__((aligned(4)));
+  const int N = t.n_inputs, B = t.n_blocks;
+  int f = c / N, i = c - f * N;
+  const int64_t d = ((int64_t)f * B + blk) * N + i;
+  if (i + 4 <= N) {
+    *reinterpret_cast<u32x4_word*>(t.s1 + d) = a;
+    *reinterpret_cast<u32x4_word*>(t.s2 + d) = b;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t e = ((int64_t)f * B + blk) * N + i;
+      t.s1[e] = (int32_t)a[j];
+      t.s2[e] = (int32_t)b[j];
+      if (++i == N) {
+        i = 0;
+        ++f;
+      }
+    }
+  }
+}
+
+// Variant 5 (library choice only): packed lane table with row phases, any N and
+// any alignment. A unit is 16 consecutive bytes of a row over one block (they
+// may straddle two channels); when 16 does not divide the row, its last unit is
+// moved back to end with the row, and the columns it shares with its neighbour
+// are summed by both. A workgroup takes LPR consecutive units (over block ends)
+// times 512 / LPR row phases, so no lane idles at a row's end and a call of few
+// blocks still has many loads in flight. The first rows are in flight while the
+// table is filled, and each batch of rows is loaded before the batch ahead of it
+// is summed.
+//
+// The phases meet in LDS: the row groups of a wavefront first (two swaps leave
+// each lane 8 of the 32 sums at LPR <= 16, as in the combine), then one LDS add
+// per value left.
+//
+// Bound by HBM for calls of about 50 MB to 0.5 GB, at 80 to 93 % of the read
+// ceiling: 1000 inputs, 3 channels, 98 MB 31.7 -> 20.2 us (4.9 TB/s; 4-byte lanes
+// before), 2048 inputs, 403 MB 68 -> 61 us (6.6 TB/s), 1024 inputs, 268 MB 51 ->
+// 43 us (6.2 TB/s; one wavefront per SIMD before), 256 inputs, 50 MB 13.8 -> 11.5
+// us (the shared table's bank conflicts before).
+template <int LPR>
+__global__ __launch_bounds__(512, 4) void pass_a_phased_kernel(PassATask t) {
+  constexpr int VEC = 16, RP = 512 / LPR;
+  constexpr int S = LPR + 1;            // accumulator row stride
+  constexpr int NV = LPR >= 64 ? 32 : LPR == 32 ? 16 : 8;   // sums a lane adds
+  // Accumulators: S1 of column k of unit g at k S + g, S2 at (16 + k) S + g;
+  // in the table's place where they would cost a second workgroup per CU.
+  constexpr bool OVER = LPR > 64;
+  __shared__ __attribute__((aligned(16))) uint32_t lut32[LANE_LUT_DWORDS];
+  __shared__ uint32_t red_own[OVER || RP == 1 ? 1 : 2 * VEC * S];
+  uint32_t* red = OVER ? lut32 : red_own;
+  const int tid = threadIdx.x;
+  const int lc = tid % LPR;
+  const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
+  const int M = t.block_len, ph = tid / LPR;
+  const int G = (int)t.row_bytes, cg = t.col_groups;
+  constexpr int STEP = PHASE_ROWS * RP;   // rows of the block per batch
+  const int64_t step_bytes = (int64_t)STEP * G;
+  const int u0 = (int)blockIdx.x * LPR, units = t.n_blocks * cg;
+  const int b_first = u0 / cg;            // uniform: the lanes' offsets start at this block
+  uint32_t col0;
+  {
+    const int u = u0 + lc < units ? u0 + lc : units - 1;
+    const int bl = u / cg, c = (u - bl * cg) * VEC;
+    col0 = (uint32_t)(bl - b_first) * (uint32_t)M * (uint32_t)G + (uint32_t)(c < G - VEC ? c : G - VEC);
+  }
+  const uint8_t* p = t.x + (int64_t)b_first * M * G;
+  u32x4 qa[PHASE_ROWS], qb[PHASE_ROWS];
+  phased_load_end<RP>(qa, p, M, G, ph, col0);
+  fill_lane_packed_lut<512>(lut32, tid);
+  if constexpr (!OVER && RP > 1)
+    for (int o = tid; o < 2 * VEC * S; o += 512) red[o] = 0u;
+  lds_barrier();
+  uint32_t v[2 * VEC], acc[VEC];
+#pragma unroll
+  for (int k = 0; k < 2 * VEC; ++k) v[k] = 0;
+#pragma unroll
+  for (int k = 0; k < VEC; ++k) acc[k] = 0;
+  const auto unpack = [&] {
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) {
+      v[k] += acc[k] & ((1u << PACK_SHIFT) - 1);
+      v[VEC + k] += acc[k] >> PACK_SHIFT;
+      acc[k] = 0;
+    }
+  };
+  const uint32_t off = __umul24(ph, G) + col0;
+  int left = M;
+  // Whole batches four at a time (16 rows, one packed run), the next one in
+  // flight, while another whole batch follows them; then the at most five
+  // batches that remain (20 rows still fit the packed sums: 20 * 128 < 2^12).
+  for (; left >= 5 * STEP; left -= 4 * STEP) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      p += step_bytes;
+      phased_load<RP>(qb, p, G, off);
+      phased_add(qa, lut, acc);
+      p += step_bytes;
+      phased_load<RP>(qa, p, G, off);
+      phased_add(qb, lut, acc);
+    }
+    unpack();
+  }
+  // (A fetch past the end reads the last row: under a branch instead, the wait
+  // for the batch before it would cover the fetch too.)
+  const auto fetch = [&](u32x4(&q)[PHASE_ROWS], int k) {
+    const int at = k * STEP < left ? k * STEP : left - 1;
+    phased_load_end<RP>(q, p + (int64_t)at * G, left - at, G, ph, col0);
+  };
+  const auto take = [&](u32x4(&q)[PHASE_ROWS], int k) {
+    phased_mask<RP>(q, left - k * STEP, ph);
+    phased_add(q, lut, acc);
+  };
+  fetch(qb, 1);
+  take(qa, 0);
+  if (left > STEP) {
+    fetch(qa, 2);
+    take(qb, 1);
+    if (left > 2 * STEP) {
+      fetch(qb, 3);
+      take(qa, 2);
+      if (left > 3 * STEP) {
+        fetch(qa, 4);
+        take(qb, 3);
+        if (left > 4 * STEP) take(qa, 4);
+      }
+    }
+  }
+  unpack();
+  if constexpr (RP == 1) {
+    const int u = u0 + lc;
+    if (u < units) {
+      const int blk = u / cg, c = (u - blk * cg) * VEC, c0 = c < G - VEC ? c : G - VEC;
+#pragma unroll
+      for (int k = 0; k < VEC; k += 4)
+        store_quad(t, blk, c0 + k, u32x4{v[k], v[k + 1], v[k + 2], v[k + 3]},
+                   u32x4{v[VEC + k], v[VEC + k + 1], v[VEC + k + 2], v[VEC + k + 3]});
+    }
+    return;
+  }
+  if constexpr (OVER) {
+    lds_barrier();
+    for (int o = tid; o < 2 * VEC * S; o += 512) red[o] = 0u;
+    lds_barrier();
+  }
+  // Sum over the wavefront's row groups, then over the wavefronts.
+  const int lane = tid & 63;
+  if constexpr (LPR >= 64) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) atomicAdd(&red[k * S + lc], v[k]);
+  } else {
+    uint32_t c[VEC];
+#pragma unroll
+    for (int m = 0; m < VEC; ++m) {
+      swap_halves(v[2 * m], v[2 * m + 1]);
+      c[m] = v[2 * m] + v[2 * m + 1];
+    }
+    if constexpr (LPR == 32) {
+#pragma unroll
+      for (int m = 0; m < VEC; ++m) atomicAdd(&red[(2 * m + (lane >> 5)) * S + lc], c[m]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        swap_rows(c[2 * q], c[2 * q + 1]);
+        uint32_t x = c[2 * q] + c[2 * q + 1];
+        if constexpr (LPR <= 8) x += row_rot<8>(x);
+        if constexpr (LPR <= 4) x += row_rot<4>(x);
+        if constexpr (LPR <= 2) x += row_rot<2>(x);
+        if constexpr (LPR <= 1) x += row_rot<1>(x);
+        if ((lane & 15) < LPR) atomicAdd(&red[wave_value_of_row(q, lane >> 4) * S + lc], x);
+      }
+    }
+  }
+  lds_barrier();
+  for (int o = tid; o < 4 * LPR; o += 512) {
+    const int lg = o >> 2, k = (o & 3) * 4, u = u0 + lg;
+    if (u < units) {
+      const int blk = u / cg, c = (u - blk * cg) * VEC, c0 = c < G - VEC ? c : G - VEC;
+      const uint32_t* r1 = red + k * S + lg;
+      const uint32_t* r2 = r1 + VEC * S;
+      store_quad(t, blk, c0 + k, u32x4{r1[0], r1[S], r1[2 * S], r1[3 * S]}, u32x4{r2[0], r2[S], r2[2 * S], r2[3 * S]});
+    }
+  }
+}
+
+static int launch_phased(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {
+  const dim3 g(grid), w(512);
+  switch (lpr) {
+    case 1: launch_kernel(pass_a_phased_kernel<1>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 2: launch_kernel(pass_a_phased_kernel<2>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 4: launch_kernel(pass_a_phased_kernel<4>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 8: launch_kernel(pass_a_phased_kernel<8>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 16: launch_kernel(pass_a_phased_kernel<16>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 32: launch_kernel(pass_a_phased_kernel<32>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 64: launch_kernel(pass_a_phased_kernel<64>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 128: launch_kernel(pass_a_phased_kernel<128>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 256: launch_kernel(pass_a_phased_kernel<256>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 512: launch_kernel(pass_a_phased_kernel<512>, g, w, 0, s, ev.start, ev.stop, t); break;
+    default:
+      set_error("pass A: phased variant needs 1..512 lanes per row, got %d", lpr);
+      return SK_ERR_INVALID_ARG;
+  }
+  SK_HIP_TRY(hipGetLastError());
+  return SK_OK;
+}
+
 // Blocks per task for variant 4: about one task per CU, at most 4 (the
 // sums of 4 blocks take 128 registers per lane).
 int pass_a_deferred_blocks(int64_t n_blocks, int64_t col_groups, int n_cu) {
@@ -325,6 +537,7 @@ static int launch_vec(const PassATask& t, int lpr, int variant, int grid, hipStr
     const dim3 g(grid), w512(512);
     switch (variant) {
       case 1: return launch_packed<8>(t, lpr, grid, s, ev);
+      case 5: return launch_phased(t, lpr, grid, s, ev);
       case 2: return launch_packed<16>(t, lpr, grid, s, ev);
       case 3:
         launch_kernel(pass_a_side_by_side_kernel<16>, g, dim3(256), 0, s, ev.start, ev.stop, t, lpr);
@@ -349,6 +562,43 @@ static int launch_vec(const PassATask& t, int lpr, int variant, int grid, hipStr
     }
   }
   return launch_shared<VEC>(t, lpr, grid, s, ev);
+}
+
+// Units a workgroup of variant 5 takes for a call it suits, else 0. Measured,
+// pass A alone (us, variant 5 against the best other):
+//   rows not of 16-byte groups, on 4-byte boundaries: 20.2 / 31.7 (3000 bytes,
+//     M = 256, 98 MB), 92 / 128 (4004 bytes, 525 MB), 39 / 38.5 at M = 16, 57 / 40
+//     at M = 2: from 16 rows a block;
+//   off 4-byte boundaries, where the hardware splits the loads: 24 / 29 (3003
+//     bytes, M = 256), 51 / 70 (2047 bytes, M = 256), 21.6 / 18.8 (2545 bytes,
+//     M = 100), 12.7 / 9.5 (17 bytes): from 192 rows and 256 bytes;
+//   16-byte groups: 61 / 68 (2048 inputs, 403 MB), 43 / 51 (1024 inputs, 268 MB),
+//     11.5 / 13.8 (256 inputs, 50 MB), 21 / 65 (16 inputs, 67 MB), but 175 / 174 at
+//     1 GiB, 360 / 334 at 2 GiB and 105 / 102 for wide rows of M = 64: the variants
+//     whose lanes hold whole rows there; 5.5 / 5.3 below 1024 units (launch-bound).
+int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len) {
+  const int64_t cg = (row_bytes + 15) / 16, units = cg * n_blocks;
+  // 24-bit row bytes and 32-bit offsets over the blocks a workgroup spans.
+  if (row_bytes < 16 || row_bytes >= (1 << 24) || units < 1024 || units >= ((int64_t)1 << 30) ||
+      (512 / cg + 2) * block_len * row_bytes >= ((int64_t)1 << 31))
+    return 0;
+  if (pick_vec(x, n_inputs) == 16) {
+    if (block_len < 32 || units * block_len * 16 > ((int64_t)1 << 29) || (cg >= 512 && block_len < 128)) return 0;
+  } else if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0) {
+    if (block_len < 16) return 0;
+  } else if (block_len < 192 || cg < 16) {
+    return 0;
+  }
+  // About one workgroup per CU with the fewest phases to join (in1000: 20.2 us
+  // with 188 workgroups of 128 units, 21.4 with 752 of 32, 29 with 94 of 256), at
+  // least 4 rows a lane; rows of under 16 groups keep a wavefront's lanes on
+  // neighbouring rows, and short calls take 16 units (within a microsecond of the
+  // best there).
+  int lanes = 16;
+  if (cg >= 16 && units >= (1 << 14))
+    while (lanes < (block_len < 128 ? 256 : 512) && 160 * 2 * lanes <= units) lanes *= 2;
+  while (lanes < 256 && lanes * block_len < 2048) lanes *= 2;
+  return lanes;
 }
 
 int pick_vec(const uint8_t* x, int32_t n_inputs) {

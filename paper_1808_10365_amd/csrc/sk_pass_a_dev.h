@@ -99,6 +99,65 @@ __device__ __forceinline__ void fill_lane_packed_lut(uint32_t* t, int tid) {
   }
 }
 
+// Batches of PHASE_ROWS rows of one lane's 16 columns, rows ph, ph + RP, ...
+// of a batch that starts at the uniform pointer `p`. Four rows: two buffers of
+// eight and the sums do not fit 128 registers. The 16 bytes may start anywhere
+// (one global_load_dwordx4 either way).
+constexpr int PHASE_ROWS = 4;
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+
+__device__ __forceinline__ u32x4 load16_any(const uint8_t* row, uint32_t off) {
+  return __builtin_nontemporal_load((const SK_GLOBAL u32x4_any*)((const SK_GLOBAL uint8_t*)row + off));
+}
+
+// A whole batch: `off` = ph G + column, the row a scalar step.
+template <int RP>
+__device__ __forceinline__ void phased_load(u32x4 (&q)[PHASE_ROWS], const uint8_t* p, int64_t G, uint32_t off) {
+#pragma unroll
+  for (int u = 0; u < PHASE_ROWS; ++u) {
+    // The row pointer in scalar registers and the lane's 32-bit offset in one
+    // vector register: left to itself the compiler carries a 64-bit vector
+    // address per row through the loop.
+    const uint8_t* row = p + (int64_t)(u * RP) * G;
+    asm("" : "+s"(row), "+v"(off));
+    q[u] = load16_any(row, off);
+  }
+}
+
+// A batch `left` rows before the block ends: a row past the end reads the last
+// one in its place (phased_mask clears it). Row offsets are 24-bit products:
+// the row index is below PHASE_ROWS RP and G below 2^24.
+template <int RP>
+__device__ __forceinline__ void phased_load_end(u32x4 (&q)[PHASE_ROWS], const uint8_t* p, int left, uint32_t G, int ph,
+                                                uint32_t col) {
+  asm("" : "+v"(ph));   // offsets formed here, not kept from the first batch
+#pragma unroll
+  for (int u = 0; u < PHASE_ROWS; ++u) {
+    const int r = ph + u * RP;
+    q[u] = load16_any(p, __umul24((uint32_t)(r < left ? r : left - 1), G) + col);
+  }
+}
+
+// Rows past the end get the code of zero power (0x88: Re = Im = 0).
+template <int RP>
+__device__ __forceinline__ void phased_mask(u32x4 (&q)[PHASE_ROWS], int left, int ph) {
+#pragma unroll
+  for (int u = 0; u < PHASE_ROWS; ++u)
+    if (ph + u * RP >= left) q[u] = u32x4{0x88888888u, 0x88888888u, 0x88888888u, 0x88888888u};
+}
+
+__device__ __forceinline__ void phased_add(const u32x4 (&q)[PHASE_ROWS], const LanePackedLut& lut, uint32_t (&acc)[16]) {
+#pragma unroll
+  for (int u = 0; u < PHASE_ROWS; u += 2)
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        acc[4 * w + k] = acc[4 * w + k] + lut.at(q[u][w], k) + lut.at(q[u + 1][w], k);
+      if (w & 1) __builtin_amdgcn_sched_barrier(0);   // 16 table reads in flight at most: more spill
+    }
+}
+
 // Nothing between packed runs.
 struct NoBalance {
   __device__ __forceinline__ void operator()() {}
