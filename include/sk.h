@@ -126,8 +126,9 @@ int sk_compute(sk_plan_t plan, const uint8_t* d_packed, const uint8_t* d_mask,
  * that forbid hipMalloc. It allocates nothing. desc as for sk_plan_create;
  * outs->s1 and outs->s2 are required (the per-input sums live in the
  * caller's buffers); the other outputs as for sk_compute. Pass B's prefix
- * sums use a static device array of sk_noalloc_scratch_bytes() bytes per
- * GPU (32 MiB, held until the process ends): a call whose window (L >= 2)
+ * sums (or the sums of its input slices, where a call needs no prefix sums) use
+ * a static device array of sk_noalloc_scratch_bytes() bytes per GPU (32 MiB,
+ * held until the process ends, with 64 KiB of counters): a call whose window (L >= 2)
  * needs more, F (ceil(B / R) + 1) N 4 bytes with R the library's chunk
  * length, returns SK_ERR_SHAPE. False-alarm thresholds are not available
  * (k sigma flags). Calls that overlap on one GPU share the array and race:

@@ -70,10 +70,11 @@ int sk_plan_set_pass_a_variant(sk_plan_t plan, int32_t variant, int32_t grid);
  * contiguous runs of rows per workgroup. */
 int sk_plan_set_pass_a_blocks(sk_plan_t plan, int32_t blocks);
 
-/* Pass B's chunk length R (blocks per combine workgroup and per prefix step:
- * 1, 2 or 4; 0 = library choice) and inputs per lane (1 or 4; 0 = library
- * choice, 4 when N % 4 == 0 and the sums are 16-byte aligned). Results do not
- * depend on R. */
+/* Pass B's chunk length R (1, 2 or 4; 0 = library choice): blocks per combine
+ * workgroup and per prefix step, or, where a call's windows are summed directly
+ * (window of at least 2 blocks, 4 inputs per lane, few rows to sum again),
+ * blocks per wavefront. And inputs per lane (1 or 4; 0 = library choice, 4 from
+ * 4 inputs on). Results do not depend on R. */
 int sk_plan_set_pass_b_tile(sk_plan_t plan, int32_t chunk, int32_t inputs_per_lane);
 
 /* Pass A's lanes per row and workgroup count for the next call (after
@@ -92,11 +93,11 @@ int sk_read_probe(const uint8_t* d_x, int64_t bytes, int32_t workgroups, uint32_
 
 /* Result of sk_plan_autotune: the settings kept and their times. */
 typedef struct {
-  int32_t pass_a_variant;      /* 0..4, as SK_PASS_A_* */
+  int32_t pass_a_variant;      /* 0..4, as SK_PASS_A_*; 5: row phases over 16-byte units (library choice) */
   int32_t pass_a_lanes;        /* lanes per row */
   int32_t pass_a_blocks;       /* consecutive blocks per task */
   int32_t pass_a_chunk_sums;   /* 1: pass A writes the chunk sums the scan reads */
-  int32_t pass_b_chunk;        /* blocks per combine workgroup (1, 2, 4) */
+  int32_t pass_b_chunk;        /* R of sk_plan_set_pass_b_tile (1, 2, 4) */
   int32_t pass_b_vec;          /* inputs per combine lane (1 or 4) */
   int32_t candidates;          /* combinations timed */
   float ms_pass_a, ms_pass_b;  /* pooled kernel-time estimates of the kept combination */

@@ -327,8 +327,9 @@ class Plan:
         _check(self._lib.sk_plan_set_pass_a_tile(self.handle, int(lanes_per_row)))
 
     def set_pass_b_tile(self, chunk: int = 0, inputs_per_lane: int = 0):
-        """Pass B blocks per combine workgroup (1, 2, 4; 0: library choice) and
-        inputs per lane (1, 4; 0: library choice)."""
+        """Pass B blocks per combine workgroup, or per wavefront where windows are
+        summed directly (1, 2, 4; 0: library choice), and inputs per lane (1, 4;
+        0: library choice)."""
         _check(self._lib.sk_plan_set_pass_b_tile(self.handle, int(chunk), int(inputs_per_lane)))
 
     def autotune(self, x: torch.Tensor, reps: int = 2, stream: Optional[torch.cuda.Stream] = None) -> dict:

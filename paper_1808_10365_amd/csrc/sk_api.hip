@@ -9,6 +9,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 
 #include "sk_internal.h"
 #include "sk_profile.h"
@@ -45,6 +46,8 @@ struct sk_plan_s {
   int32_t* s2;
   uint32_t* pc;            // [F][ceil(B / R) + 1][N] prefix sums of pass B
   size_t pc_bytes;
+  double* part;            // sums of the window kernel's input slices (N > 256), then its counters
+  uint32_t* done;
   int32_t* cs;             // [F][ceil(B / R)][N] chunk sums written by pass A (variant 4 with Q == R)
   size_t cs_bytes;
   int32_t* hs[2];          // [F][hist_cap][N] history suffix sums, ping-pong
@@ -103,6 +106,7 @@ static void free_plan_memory(sk_plan_s* p) {
     if (p->s2) (void)hipFree(p->s2);
   }
   if (p->pc) (void)hipFree(p->pc);
+  if (p->part) (void)hipFree(p->part);
   if (p->cs) (void)hipFree(p->cs);
   if (p->hs[0]) (void)hipFree(p->hs[0]);
   if (p->hs[1]) (void)hipFree(p->hs[1]);
@@ -147,7 +151,7 @@ int sk_plan_create(const sk_plan_desc* desc, sk_plan_t* out) {
   const int L = desc->norm_window_blocks;
   p->hist_cap = L >= 2 ? L - 1 : 0;
   p->hist_len = 0;
-  p->chunk = pass_b_chunk((int32_t)N, (int32_t)F, p->n_blocks, L);
+  p->chunk = pass_b_plan_chunk((int32_t)N, (int32_t)F, p->n_blocks, L);
   p->s1_s2_owned = 1;
   const size_t fbn = (size_t)F * p->n_blocks * N;
   SK_ALLOC(p->s1, fbn * sizeof(int32_t));
@@ -163,6 +167,18 @@ int sk_plan_create(const sk_plan_desc* desc, sk_plan_t* out) {
     }
     SK_ALLOC(p->hs[0], (size_t)F * p->hist_cap * N * sizeof(int32_t));
     SK_ALLOC(p->hs[1], (size_t)F * p->hist_cap * N * sizeof(int32_t));
+    const size_t part = pass_b_direct_part_bytes((int32_t)N, (int32_t)F, p->n_blocks);
+    const size_t done = pass_b_direct_done_bytes((int32_t)N, (int32_t)F, p->n_blocks);
+    SK_ALLOC(p->part, part + done);
+    if (done > 0) {
+      p->done = (uint32_t*)((char*)p->part + part);
+      if (hipMemset(p->done, 0, done) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+        set_error("clearing the window kernel's counters failed");
+        free_plan_memory(p);
+        delete p;
+        return SK_ERR_DEVICE;
+      }
+    }
   }
   p->cur = 0;
   *out = p;
@@ -284,7 +300,7 @@ int sk_plan_set_pass_b_tile(sk_plan_t p, int32_t chunk, int32_t vec) {
     return SK_ERR_INVALID_ARG;
   }
   const int32_t R = chunk ? chunk
-                          : pass_b_chunk(p->d.n_inputs, p->d.n_channels, p->n_blocks, p->d.norm_window_blocks);
+                          : pass_b_plan_chunk(p->d.n_inputs, p->d.n_channels, p->n_blocks, p->d.norm_window_blocks);
   if (p->d.norm_window_blocks >= 2) {
     const size_t need = pass_b_prefix_bytes(p->d.n_inputs, p->d.n_channels, p->n_blocks, R);
     if (need > p->pc_bytes) {
@@ -360,6 +376,8 @@ struct CallBuffers {
   const int32_t* hs;     // history suffix sums of this call (L >= 2; hist_len slots valid)
   int32_t* hs_next;      // the next call's
   int32_t hist_len;
+  double* part;          // the window kernel's scratch (null: scan and combine)
+  uint32_t* done;
 };
 
 // Pass B arguments of one call.
@@ -395,10 +413,11 @@ static PassBArgs make_pass_b_args(const sk_plan_desc& d, int64_t B, int32_t hist
   a.hist_next_len = (int32_t)(total < hist_cap ? total : hist_cap);
   a.chunk = chunk;
   a.n_chunks = (int32_t)((B + chunk - 1) / chunk);
-  // Four inputs per lane need 16-byte aligned rows of the sums.
-  a.vec = pass_b_vec((int32_t)N);
-  if (((uintptr_t)cb.s1 | (uintptr_t)cb.s2 | (uintptr_t)outs->sk_i) % 16 != 0) a.vec = 1;
-  if (vec_pref == 1) a.vec = 1;
+  a.vec = vec_pref == 1 ? 1 : pass_b_vec((int32_t)N);
+  a.direct = pass_b_direct((int32_t)N, d.n_channels, B, a.window, chunk, a.vec) &&
+             (cb.part || pass_b_direct_part_bytes((int32_t)N, d.n_channels, B) == 0);
+  a.part = cb.part;
+  a.done = cb.done;
   a.estimator = d.estimator;
   a.k_sigma = d.k_sigma;
   a.expect_offset = d.expect_offset;
@@ -425,6 +444,8 @@ static int plan_call(sk_plan_s* p, const uint8_t* d_packed, const uint8_t* d_mas
   cb.hs = p->hs[p->cur];
   cb.hs_next = p->hs[1 - p->cur];
   cb.hist_len = p->hist_len;
+  cb.part = p->part;
+  cb.done = p->done;
 
   PassATask t;
   PassAConfig c = plan_pass_a_config(p, d_packed, &t);
@@ -434,7 +455,7 @@ static int plan_call(sk_plan_s* p, const uint8_t* d_packed, const uint8_t* d_mas
   t.cs = nullptr;
   PassBArgs a = make_pass_b_args(p->d, B, p->hist_cap, p->chunk, p->pass_b_vec, d_mask, outs, cb, p->thresholds);
   // Pass A tasks of Q = R consecutive blocks hand the scan its chunk sums.
-  if (a.window >= 2 && p->cs && p->chunk_sums && pass_a_deferred(c.vec, c.variant) && t.blocks_per_task == a.chunk &&
+  if (a.window >= 2 && !a.direct && p->cs && p->chunk_sums && pass_a_deferred(c.vec, c.variant) && t.blocks_per_task == a.chunk &&
       (size_t)a.n_channels * a.n_chunks * a.n_inputs * sizeof(int32_t) <= p->cs_bytes) {
     t.cs = p->cs;
     a.cs = p->cs;
@@ -678,14 +699,14 @@ int sk_plan_autotune(sk_plan_t p, const uint8_t* d_x, int32_t reps, void* stream
       // Whether the kept combination hands the scan chunk sums (the same
       // test as a call's).
       PassBArgs pb = make_pass_b_args(p->d, p->n_blocks, p->hist_cap, p->chunk, p->pass_b_vec, nullptr, &none,
-                                      CallBuffers{p->s1, p->s2, p->pc, nullptr, nullptr, 0}, nullptr);
-      cs = pb.window >= 2 && p->cs && p->chunk_sums && pass_a_deferred(pc.vec, pc.variant) &&
+                                      CallBuffers{p->s1, p->s2, p->pc, nullptr, nullptr, 0, p->part, p->done}, nullptr);
+      cs = pb.window >= 2 && !pb.direct && p->cs && p->chunk_sums && pass_a_deferred(pc.vec, pc.variant) &&
            t.blocks_per_task == pb.chunk &&
            (size_t)pb.n_channels * pb.n_chunks * pb.n_inputs * sizeof(int32_t) <= p->cs_bytes;
     }
     out->pass_a_chunk_sums = cs ? 1 : 0;
     out->pass_b_vec = make_pass_b_args(p->d, p->n_blocks, p->hist_cap, p->chunk, p->pass_b_vec, nullptr, &none,
-                                       CallBuffers{p->s1, p->s2, p->pc, nullptr, nullptr, 0}, nullptr).vec;
+                                       CallBuffers{p->s1, p->s2, p->pc, nullptr, nullptr, 0, p->part, p->done}, nullptr).vec;
     out->candidates = (int32_t)cands.size();
     out->ms_pass_a = best_a;
     out->ms_pass_b = best_b;
@@ -747,29 +768,36 @@ int sk_plan_pass_a_timeline(sk_plan_t p, const uint8_t* d_x, int32_t simd_balanc
 // taken once per device with hipGetSymbolAddress and kept below.
 static constexpr size_t kNoallocScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) uint8_t scratch[kNoallocScratchBytes];
+// The window kernel's counters (zero between calls; its slices' sums take the
+// scratch in the prefix sums' place).
+static constexpr size_t kNoallocDone = 1 << 14;
+static __device__ uint32_t scratch_done[kNoallocDone];
 
 namespace {
 std::mutex g_scratch_mu;
-std::map<int, void*> g_scratch_ptr;   // device -> address of that device's scratch
+std::map<int, std::pair<void*, void*>> g_scratch_ptr;   // device -> addresses of that device's scratch and counters
 }  // namespace
 
 // Address of the current device's scratch (looked up on the first call on
 // each device, with that device current).
-static int noalloc_scratch(int dev, void** ptr) {
+static int noalloc_scratch(int dev, void** ptr, void** done) {
   std::lock_guard<std::mutex> lk(g_scratch_mu);
   auto it = g_scratch_ptr.find(dev);
   if (it != g_scratch_ptr.end()) {
-    *ptr = it->second;
+    *ptr = it->second.first;
+    *done = it->second.second;
     return SK_OK;
   }
-  void* p = nullptr;
-  const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-  if (e != hipSuccess || !p) {
+  void *p = nullptr, *c = nullptr;
+  hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+  if (e == hipSuccess) e = hipGetSymbolAddress(&c, HIP_SYMBOL(scratch_done));
+  if (e != hipSuccess || !p || !c) {
     set_error("hipGetSymbolAddress(scratch) failed on device %d: %s", dev, hipGetErrorString(e));
     return SK_ERR_DEVICE;
   }
-  g_scratch_ptr[dev] = p;
+  g_scratch_ptr[dev] = {p, c};
   *ptr = p;
+  *done = c;
   return SK_OK;
 }
 
@@ -800,8 +828,8 @@ int sk_compute_noalloc(const sk_plan_desc* desc, const uint8_t* d_packed, const 
   }
   int dev = -1;
   SK_HIP_TRY(hipGetDevice(&dev));
-  void* sp = nullptr;
-  rc = noalloc_scratch(dev, &sp);
+  void *sp = nullptr, *sd = nullptr;
+  rc = noalloc_scratch(dev, &sp, &sd);
   if (rc) return rc;
   PassATuning u;
   int ncu = 0;
@@ -814,12 +842,20 @@ int sk_compute_noalloc(const sk_plan_desc* desc, const uint8_t* d_packed, const 
   cb.hs = nullptr;
   cb.hs_next = nullptr;   // no state: nothing is carried to a next call
   cb.hist_len = 0;
+  const bool fits = pass_b_direct_part_bytes(d.n_inputs, d.n_channels, B) <= kNoallocScratchBytes &&
+                    pass_b_direct_done_bytes(d.n_inputs, d.n_channels, B) <= sizeof(uint32_t) * kNoallocDone;
+  cb.part = fits ? (double*)sp : nullptr;
+  cb.done = fits ? (uint32_t*)sd : nullptr;
   PassATask t;
   PassAConfig c = pass_a_config(d, B, u, d_packed, &t);
   t.x = d_packed;
   t.s1 = cb.s1;
   t.s2 = cb.s2;
-  PassBArgs a = make_pass_b_args(d, B, L >= 2 ? L - 1 : 0, R, 0, d_mask, outs, cb, nullptr);
+  // The window kernel's own R where the call takes it (its slices' sums fit);
+  // the limit above is the scan's either way.
+  const int32_t Rw = pass_b_plan_chunk(d.n_inputs, d.n_channels, B, L);
+  PassBArgs a = make_pass_b_args(d, B, L >= 2 ? L - 1 : 0, Rw, 0, d_mask, outs, cb, nullptr);
+  if (!a.direct) a = make_pass_b_args(d, B, L >= 2 ? L - 1 : 0, R, 0, d_mask, outs, cb, nullptr);
   rc = launch_pass_a(t, c, s);
   if (rc) return rc;
   return launch_pass_b(a, s);

@@ -121,7 +121,10 @@ struct PassBArgs {
   int32_t n_inputs, n_channels, n_blocks, block_len, window, hist_len, hist_cap, hist_next_len;
   int32_t chunk;          // R: blocks per combine workgroup and per prefix step (1, 2 or 4)
   int32_t n_chunks;       // ceil(B / R)
-  int32_t vec;            // inputs per combine lane: 4 (16-byte aligned sums, N % 4 == 0) or 1
+  int32_t vec;            // inputs per combine lane: 4 (N >= 4) or 1
+  int32_t direct;         // 1: the window kernel (R blocks per wavefront), 0: scan and combine
+  double* part;           // window kernel, N > 256: [5][F][B][W] sums of the input slices (W = combine_waves)
+  uint32_t* done;         // and [F][segments] finished slices, zero between calls
   int32_t estimator;
   double k_sigma, expect_offset, sigma_override;
 };
@@ -129,6 +132,14 @@ struct PassBArgs {
 // Library choice of R for a call of B blocks (F channels, N inputs).
 int pass_b_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window);
 int pass_b_vec(int32_t n_inputs);
+// Whether a call takes the window kernel at `chunk` blocks per wavefront, and the
+// scratch its input slices meet in (bytes of part and of done; 0 for N <= 256).
+bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec);
+size_t pass_b_direct_part_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
+size_t pass_b_direct_done_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
+// Library choice of R: blocks per wavefront of the window kernel where a call
+// takes it, else as pass_b_chunk.
+int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window);
 // Device bytes of the prefix buffer: F (ceil(B / R) + 1) N uint32.
 size_t pass_b_prefix_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t chunk);
 int launch_pass_b(const PassBArgs& a, hipStream_t s, PassEvents ev = PassEvents());

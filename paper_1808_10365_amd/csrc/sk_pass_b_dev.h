@@ -52,12 +52,14 @@ struct IVec<1> {
 template <>
 struct IVec<4> {
   int32_t v[4];
+  // Rows of any N are 4-byte aligned, which is all a 16-byte access needs.
+  typedef int32_t vec __attribute__((ext_vector_type(4), aligned(4)));
   __device__ __forceinline__ void load(const int32_t* p) {
-    const int4 q = *reinterpret_cast<const int4*>(p);
+    const vec q = *reinterpret_cast<const vec*>(p);
     v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
   }
   __device__ __forceinline__ void store(int32_t* p) const {
-    *reinterpret_cast<int4*>(p) = make_int4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<vec*>(p) = vec{v[0], v[1], v[2], v[3]};
   }
 };
 
@@ -150,7 +152,6 @@ __device__ __forceinline__ void finish(const PassBArgs& a, int f, int b, double 
 // would keep everything derived from it per lane).
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
-// ------------------------------------------------------------------ scan
 // ------------------------------------------------------------------ scan
 
 constexpr int SCAN_MAX_WAVES = 16;
@@ -355,8 +356,10 @@ __device__ __forceinline__ const int32_t* elem_at(const int32_t* base, int64_t e
 // lane, RI the integer type of a lane's R1/R2 sums, OFF32 when every
 // per-channel array holds fewer than 2^30 elements.
 //
-// Every lane loads: a lane past the last input reads the last group's
-// inputs (in bounds) and contributes nothing. Loads that a chunk does not
+// Every lane loads: a lane past the last input reads the last V inputs (in
+// bounds) and contributes nothing; the lane of a last group of fewer than V
+// inputs (N % V != 0) reads the last V too, counts those from its own first
+// input on, and stores what its neighbour stores for the others. Loads that a chunk does not
 // need are replaced by zeros in wavefront-uniform branches.
 template <int V, int R, typename RI, bool OFF32>
 __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, int w, int W, CombineShared& sh,
@@ -405,7 +408,7 @@ __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, i
   for (int g = w; g < n_groups; g += W) {
     const int i0 = (g * 64 + lane) * V;
     const bool active = i0 < N;
-    const int il = active ? i0 : N - V;               // the input this lane loads
+    const int il = i0 < N - V ? i0 : N - V;           // the inputs this lane loads
     IVec<V> x1[R], x2[R], old[RO], hsv[R], pck, pcl, pct;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
@@ -475,7 +478,7 @@ __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, i
         }
       }
     }
-    uint32_t use = active ? (1u << V) - 1 : 0u;
+    uint32_t use = active ? (1u << V) - 1 & ~0u << (i0 - il) : 0u;
     if (a.mask) {
 #pragma unroll
       for (int q = 0; q < V; ++q)
@@ -514,7 +517,7 @@ __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, i
             IVec<V> h;
 #pragma unroll
             for (int q = 0; q < V; ++q) h.v[q] = (int32_t)((uint32_t)pct.v[q] - pre[q]);
-            h.store(a.hs_next + ((int64_t)f * a.hist_cap + (b0 + j - B + a.hist_cap)) * N + i0);
+            h.store(a.hs_next + ((int64_t)f * a.hist_cap + (b0 + j - B + a.hist_cap)) * N + il);
           }
         }
 #pragma unroll
@@ -527,7 +530,7 @@ __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, i
         float ski[V];
 #pragma unroll
         for (int q = 0; q < V; ++q) ski[q] = per_input_sk(x1[j].v[q], x2[j].v[q], a.block_len);
-        float* dst = a.sk_i + (rowF + b0 + j) * N + i0;
+        float* dst = a.sk_i + (rowF + b0 + j) * N + il;
 #pragma unroll
         for (int q = 0; q < V; ++q) dst[q] = ski[q];
       }
