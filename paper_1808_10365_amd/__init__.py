@@ -175,9 +175,14 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# The current stream's handle without building a torch.cuda.Stream (0.1 against
+# 2.9 us a call).
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+    (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return stream.cuda_stream if stream is not None else _current_raw_stream(torch.cuda.current_device())
 
 
 def _device_tensor(t, name: str, dtype, shape, device_index: int):
@@ -197,6 +202,12 @@ def _device_tensor(t, name: str, dtype, shape, device_index: int):
     return t
 
 
+def _is_device_tensor(t, dtype, shape, device_index: int) -> bool:
+    """What _device_tensor asks for, without the messages."""
+    return (isinstance(t, torch.Tensor) and t.get_device() == device_index and t.dtype is dtype and t.shape == shape
+            and t.is_contiguous())
+
+
 def _output_specs(F: int, B: int, N: int):
     return {"s1": ((F, B, N), torch.int32), "s2": ((F, B, N), torch.int32), "r1": ((F, B), torch.int64),
             "r2": ((F, B), torch.int64), "v": ((F, B), torch.float32), "flags": ((F, B), torch.uint8),
@@ -204,12 +215,18 @@ def _output_specs(F: int, B: int, N: int):
             "significance": ((F, B), torch.float32)}
 
 
-def _check_outputs(out, F: int, B: int, N: int, device_index: int):
-    specs = _output_specs(F, B, N)
-    for k in ALL_OUTPUTS:
+def _output_pointers(out, specs, device_index: int) -> Outputs:
+    """The checked outputs' device pointers; ``specs`` from _output_specs."""
+    ptrs = []
+    for k, (shape, dtype) in specs.items():
         t = getattr(out, k)
-        if t is not None:
-            _device_tensor(t, f"output {k}", specs[k][1], specs[k][0], device_index)
+        if t is None:
+            ptrs.append(None)
+            continue
+        if not _is_device_tensor(t, dtype, shape, device_index):
+            _device_tensor(t, f"output {k}", dtype, shape, device_index)
+        ptrs.append(t.data_ptr())
+    return Outputs(*ptrs)
 
 
 def digitised_expectation(sigma: Sequence[float], block_len: int, clip: int = 7):
@@ -298,6 +315,8 @@ class Plan:
         h = ctypes.c_void_p()
         _check(self._lib.sk_plan_create(ctypes.byref(self.desc), ctypes.byref(h)))
         self.handle = h
+        self._in_shape = (n_samples, n_channels, n_inputs)
+        self._specs = _output_specs(n_channels, n_samples // block_len, n_inputs)
 
     @property
     def n_blocks(self) -> int:
@@ -381,30 +400,23 @@ class Plan:
         _check(self._lib.sk_plan_set_pass_a_variant(self.handle, int(variant), int(grid)))
 
     def alloc_outputs(self, device, want: Sequence[str] = DEFAULT_OUTPUTS) -> Result:
-        F, N, B = self.desc.n_channels, self.desc.n_inputs, self.n_blocks
-        mk = {
-            "s1": lambda: torch.empty((F, B, N), dtype=torch.int32, device=device),
-            "s2": lambda: torch.empty((F, B, N), dtype=torch.int32, device=device),
-            "r1": lambda: torch.empty((F, B), dtype=torch.int64, device=device),
-            "r2": lambda: torch.empty((F, B), dtype=torch.int64, device=device),
-            "v": lambda: torch.empty((F, B), dtype=torch.float32, device=device),
-            "flags": lambda: torch.empty((F, B), dtype=torch.uint8, device=device),
-            "n_eff": lambda: torch.empty((F, B), dtype=torch.int32, device=device),
-            "sk_i": lambda: torch.empty((F, B, N), dtype=torch.float32, device=device),
-            "significance": lambda: torch.empty((F, B), dtype=torch.float32, device=device),
-        }
-        return Result(**{k: (mk[k]() if k in want else None) for k in ALL_OUTPUTS})
+        return Result(**{k: torch.empty(shape, dtype=dtype, device=device) if k in want else None
+                         for k, (shape, dtype) in self._specs.items()})
 
     def compute_into(self, packed: torch.Tensor, out: Result, mask: Optional[torch.Tensor] = None,
                      stream: Optional[torch.cuda.Stream] = None) -> Result:
-        T, F, N = self.desc.n_samples, self.desc.n_channels, self.desc.n_inputs
         dev = self.device_index
-        _device_tensor(packed, "packed", torch.uint8, (T, F, N), dev)
+        if not _is_device_tensor(packed, torch.uint8, self._in_shape, dev):
+            _device_tensor(packed, "packed", torch.uint8, self._in_shape, dev)
         if mask is not None:
-            _device_tensor(mask, "mask", torch.uint8, (F, N), dev)
-        _check_outputs(out, F, self.n_blocks, N, dev)
-        o = Outputs(*[_ptr(getattr(out, k)) for k in ALL_OUTPUTS])
-        _check(self._lib.sk_compute(self.handle, _ptr(packed), _ptr(mask), ctypes.byref(o), _stream_handle(stream)))
+            _device_tensor(mask, "mask", torch.uint8, self._in_shape[1:], dev)
+        o = _output_pointers(out, self._specs, dev)
+        # (A plan refuses calls while another device is current, so its own
+        # device's current stream is the one.)
+        rc = self._lib.sk_compute(self.handle, packed.data_ptr(), None if mask is None else mask.data_ptr(),
+                                  ctypes.byref(o), stream.cuda_stream if stream is not None else _current_raw_stream(dev))
+        if rc:
+            _check(rc)
         return out
 
     def compute(self, packed: torch.Tensor, mask: Optional[torch.Tensor] = None,
@@ -454,9 +466,8 @@ def compute_noalloc(packed: torch.Tensor, out: "Result", block_len: int, norm_wi
         raise ValueError(f"T = {T} is not a multiple of block_len = {block_len}")
     if mask is not None:
         _device_tensor(mask, "mask", torch.uint8, (F, N), dev)
-    _check_outputs(out, F, T // block_len, N, dev)
+    o = _output_pointers(out, _output_specs(F, T // block_len, N), dev)
     d = PlanDesc(N, F, T, block_len, norm_window, estimator, k_sigma, expect_offset, sigma_override)
-    o = Outputs(*[_ptr(getattr(out, k)) for k in ALL_OUTPUTS])
     _check(load_library().sk_compute_noalloc(ctypes.byref(d), _ptr(packed), _ptr(mask), ctypes.byref(o),
                                               _stream_handle(stream)))
     return out
@@ -608,8 +619,7 @@ class Server:
                 raise ValueError(f"host frame must be a contiguous uint8 tensor of shape {(T, F, N)}")
             if not frame.is_pinned():
                 raise ValueError("host frames must be in pinned memory (asynchronous copy)")
-        _check_outputs(out, F, d.n_samples // d.block_len, N, self.device_index)
-        o = Outputs(*[_ptr(getattr(out, k)) for k in ALL_OUTPUTS])
+        o = _output_pointers(out, _output_specs(F, d.n_samples // d.block_len, N), self.device_index)
         t = ctypes.c_uint64()
         rc = self._lib.sk_stream_submit(self.handle, array_id, ctypes.c_void_p(frame.data_ptr()),
                                         0 if frame.is_cuda else 1, ctypes.byref(o), tag,
