@@ -22,7 +22,10 @@
  * and timed on the device (pass A rows per load {8, 16} x consecutive blocks
  * per task {1, 2, 4} for wide rows, then pass B chunk length {1, 2, 4}); each
  * candidate's time and the pick are cached in a JSON file keyed by the
- * device arch and the class, and a class found there is not timed again.
+ * device arch and the class, and a class found there is not timed again. Then
+ * the whole batch is timed with the classes' picks and in row phases at chunk
+ * lengths 4 and 2, and the fastest is kept (cached for batches of as many
+ * problems and bytes).
  *
  * Requirements: every problem has N % 16 == 0 and a 16-byte aligned input.
  * Errors as in sk.h.
@@ -42,7 +45,8 @@ typedef struct sk_batch_s* sk_batch_t;
 
 typedef struct {
   int32_t autotune;        /* 1: time the tile candidates of each class on the device (cached);
-                              0: 16 rows per load, 1 block per task, the plan's pass B chunk */
+                              0: 16 rows per load, 1 block per task, the plan's pass B chunk, or
+                              row phases, by the batch's sizes */
   int32_t use_graph;       /* 1: capture the launch sequence into a HIP graph */
   const char* tune_cache;  /* JSON tuning cache path; NULL: env SK_TUNE_CACHE, or none */
 } sk_batch_opts;
@@ -68,9 +72,9 @@ int sk_batch_state_reset(sk_batch_t batch, void* stream);
  * groups) and the persistent workgroup count of pass A. */
 int sk_batch_get_tiles(sk_batch_t batch, int32_t j, int32_t* lanes_per_row, int32_t* pass_a_grid);
 
-/* Tile choices of problem j: pass A rows per load, blocks per task, pass B
- * chunk length, and whether they came from the tuning cache (1) or from
- * timing or the defaults (0). */
+/* Tile choices of problem j's class: pass A rows per load, blocks per task, pass
+ * B chunk length, and whether they came from the tuning cache (1) or from
+ * timing or the defaults (0). A batch run in row phases does not use them. */
 int sk_batch_get_tuning(sk_batch_t batch, int32_t j, int32_t* rows_per_load, int32_t* blocks_per_task,
                         int32_t* pass_b_chunk, int32_t* from_cache);
 

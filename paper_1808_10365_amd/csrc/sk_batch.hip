@@ -28,6 +28,7 @@ struct BatchProb {
                                // 256 (wide rows in 256-group chunks), else 256 / lpr blocks side
                                // by side in half a workgroup
   int32_t rows;                // pass A rows per load, 8 or 16 (tuned per problem class)
+  int32_t units;               // row-phase form: 16-byte units per task (16, 32, 64 or 512); 0: the form above
   int32_t window, hist_cap, chunk, n_chunks, estimator;
   int32_t waves;               // combine waves per chunk (inputs / 256, at most 8)
   int32_t scan_waves;          // scan waves per 64-input slice (power of two, at most 8)
@@ -166,6 +167,42 @@ __global__ __launch_bounds__(512) void batch_pass_a_kernel(const BatchProb* __re
         if (P.rows == 8) pass_a_task_side_by_side<8>(P.a, P.lpr, task, lut, tid & 255, bal);
         else pass_a_task_side_by_side<16>(P.a, P.lpr, task, lut, tid & 255, bal);
       }
+    }
+  }
+}
+
+// The same over tasks of row phases (pass_a_task_phased): 16 to 64 units times 32
+// to 8 phases, or 512 units of one. A lane then walks M / 8 rows or fewer where
+// blocks are long, so no task outlasts the batch (100 blocks of 64 inputs, 4
+// channels and 1024 samples, 26 MB: 190 us when a lane walks the block), and two
+// workgroups fit a CU, so one streams while the other joins its phases. Bound by
+// HBM from about 0.3 GB on, at 5.9 TB/s with the sums' writes between the reads:
+// 12 problems, 2.1 GB: 360 us as in the other form; two of wide rows, 1.5 GB: 258
+// against 288; ten of narrow rows, 0.6 GB: 113 against 227; five, 79 MB: 25
+// against 194.
+__global__ __launch_bounds__(512, 4) void batch_pass_a_phased_kernel(const BatchProb* __restrict__ probs, int n,
+                                                                     int64_t total, uint32_t* counter) {
+  __shared__ __attribute__((aligned(16))) uint32_t lut32[LANE_LUT_DWORDS];
+  __shared__ uint32_t red[32 * phased_stride(64)];
+  __shared__ uint32_t s_unit;
+  const int tid = threadIdx.x;
+  fill_lane_packed_lut<512>(lut32, tid);
+  for (int o = tid; o < 32 * phased_stride(64); o += 512) red[o] = 0u;
+  const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
+  for (;;) {
+    if (tid == 0) s_unit = atomicAdd(counter, 1u);
+    __syncthreads();
+    const int64_t u = __builtin_amdgcn_readfirstlane(s_unit);
+    __syncthreads();
+    if (u >= total) break;
+    const BatchProb& P = probs[find_prob<&BatchProb::a_begin>(probs, n, u)];
+    const int task = (int)(u - P.a_begin);
+    const auto ready = [] {};
+    switch (P.units) {
+      case 16: pass_a_task_phased<16, false, true>(P.a, task * 16, lut, red, tid, ready); break;
+      case 32: pass_a_task_phased<32, false, true>(P.a, task * 32, lut, red, tid, ready); break;
+      case 64: pass_a_task_phased<64, false, true>(P.a, task * 64, lut, red, tid, ready); break;
+      default: pass_a_task_phased<512, false, true>(P.a, task * 512, lut, red, tid, ready); break;
     }
   }
 }
@@ -345,6 +382,16 @@ struct Layout {
   bool off32 = true;
 };
 
+// A class's tile choices: pass A rows per load and blocks per task (wide rows),
+// pass B chunk length.
+struct Pick {
+  int rows, blocks, chunk;
+};
+
+// What a batch's calls run: the classes' picks, or pass A in row phases with one
+// chunk length for every problem (so one combine launch).
+enum BatchForm { FORM_PICKS = 0, FORM_PHASED_4 = 1, FORM_PHASED_2 = 2, N_FORMS = 3 };
+
 struct sk_batch_s {
   int n = 0;
   int device = 0;
@@ -358,9 +405,11 @@ struct sk_batch_s {
   int32_t* d_members = nullptr;    // combine classes: table positions, class by class
   int64_t* d_begins = nullptr;     // and their first combine workgroups
   std::vector<void*> owned;
-  int grid_a = 0;
+  int grid_a = 0, grid_p = 0;      // pass A workgroups: the two forms
   Layout lay;                      // task ranges of the table as it is on the device
   std::vector<int> tuned_from_cache;   // per table position: 1 if its class's pick came from the cache
+  std::vector<Pick> picks;             // per table position
+  int form = FORM_PICKS;
   bool use_graph = false;
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -399,11 +448,36 @@ static void set_pass_a(BatchProb& P, int rows, int q) {
   P.a.timeline = nullptr;
   P.a.simd_balance = 1;
   P.rows = rows;
+  P.units = 0;
   P.a.block0 = 0;
   P.a.block_end = P.a.n_blocks;
   P.a.blocks_per_task = P.lpr >= 256 ? q : 256 / P.lpr;
   P.a.chunks = P.lpr >= 256 ? (P.a.col_groups + P.lpr - 1) / P.lpr : 1;
   P.a.n_tasks = (((int64_t)P.a.n_blocks + P.a.blocks_per_task - 1) / P.a.blocks_per_task) * P.a.chunks;
+}
+
+// Whether pass A's row-phase form takes a problem (24-bit rows, 32-bit offsets
+// over the blocks a task spans).
+static bool phased_fits(const BatchProb& P) {
+  const int64_t cg = P.a.col_groups, units = cg * P.a.n_blocks;
+  return P.a.row_bytes < (1 << 24) && units < ((int64_t)1 << 30) &&
+         (512 / cg + 2) * P.a.block_len * P.a.row_bytes < ((int64_t)1 << 31);
+}
+
+// Row-phase form of one problem's pass A, `total` bytes in the whole batch: 512
+// units (whole blocks, stored from registers) of blocks under 128 samples, else 64
+// units and 8 phases (12-problem draw: 362 us either way at M = 64 and 256, 382
+// with 64 units at M = 64; 2048 inputs, M = 256, 2 GiB: 352 us with 64, 376 with
+// 512), and fewer units while the batch would not give every workgroup two tasks.
+static void set_pass_a_phased(BatchProb& P, int64_t total) {
+  const int M = P.a.block_len;
+  int units = M < 128 ? 512 : 64;
+  while (units > 16 && (int64_t)units * 16 * M * 1024 > total && M * units >= 8 * 512) units = units == 512 ? 64 : units / 2;
+  P.a.cs = nullptr;
+  P.a.timeline = nullptr;
+  P.a.simd_balance = 1;
+  P.units = units;
+  P.a.n_tasks = ((int64_t)P.a.n_blocks * P.a.col_groups + units - 1) / units;
 }
 
 // Pass B chunk length of one problem. When pass A's wide-row tasks walk
@@ -412,7 +486,7 @@ static void set_pass_a(BatchProb& P, int rows, int q) {
 static void set_pass_b(BatchProb& P, int R) {
   P.chunk = R;
   P.n_chunks = (int32_t)((P.a.n_blocks + R - 1) / R);
-  const bool cs = P.cs_buf && P.lpr >= 256 && R >= 2 && P.a.blocks_per_task == R;
+  const bool cs = P.cs_buf && !P.units && P.lpr >= 256 && R >= 2 && P.a.blocks_per_task == R;
   P.a.cs = cs ? P.cs_buf : nullptr;
   // Waves per slice: enough for the units in SCAN_ROWS-unit lanes, and for
   // the history rows moved once the history is full (a call shorter than the
@@ -428,9 +502,9 @@ static Layout layout(std::vector<BatchProb>& tab) {
   for (BatchProb& P : tab) {
     const int64_t F = P.a.row_bytes / P.a.n_inputs;
     // Queue units: two per task of 512-group rows, one otherwise; every
-    // problem starts on an even unit.
-    P.a_begin = (l.ta + 1) & ~(int64_t)1;
-    l.ta = P.a_begin + P.a.n_tasks * (P.lpr == 512 ? 2 : 1);
+    // problem starts on an even unit. (Row-phase form: one per task.)
+    P.a_begin = P.units ? l.ta : (l.ta + 1) & ~(int64_t)1;
+    l.ta = P.a_begin + P.a.n_tasks * (!P.units && P.lpr == 512 ? 2 : 1);
     P.sc_begin = l.tsc;
     const int slices = (P.a.n_inputs + 63) / 64, spw = BATCH_SCAN_WAVES / P.scan_waves;
     P.sc_count = (P.a.n_blocks > 0 && pass_b_needs_scan(P.window, P.chunk, P.a.n_blocks))
@@ -479,6 +553,12 @@ static void launch_pass_a_table(const BatchProb* d_tab, int n, int64_t total, in
   batch_pass_a_kernel<<<dim3(grid), dim3(512), 0, s>>>(d_tab, n, total, counter);
 }
 
+// Pass A of the batch as it is set up.
+static void launch_pass_a_batch(const sk_batch_s* b, hipStream_t s) {
+  if (b->form == FORM_PICKS) launch_pass_a_table(b->d_probs, b->n, b->lay.ta, b->grid_a, b->d_counter, s);
+  else batch_pass_a_phased_kernel<<<dim3(b->grid_p), dim3(512), 0, s>>>(b->d_probs, b->n, b->lay.ta, b->d_counter);
+}
+
 template <int R, typename RI>
 static void launch_combine_class(const DeviceTable& d, BatchState* st, const Layout& l, hipStream_t s,
                                  const BatchFinal& fin, int last_class) {
@@ -512,18 +592,18 @@ static void launch_pass_b_table(const DeviceTable& d, BatchState* st, int n, con
                                 const BatchFinal& fin = BatchFinal{nullptr, nullptr, nullptr, 0}) {
   if (l.tsc > 0) batch_scan_kernel<<<dim3((unsigned)l.tsc), dim3(64 * BATCH_SCAN_WAVES), 0, s>>>(d.probs, st, n);
   const int last = fin.st ? last_combine_class(l) : -1;
-  launch_combine_class<4, int32_t>(d, st, l, s, fin, last);
-  launch_combine_class<2, int32_t>(d, st, l, s, fin, last);
-  launch_combine_class<1, int32_t>(d, st, l, s, fin, last);
-  launch_combine_class<4, int64_t>(d, st, l, s, fin, last);
-  launch_combine_class<2, int64_t>(d, st, l, s, fin, last);
-  launch_combine_class<1, int64_t>(d, st, l, s, fin, last);
+  launch_combine_class<4, uint32_t>(d, st, l, s, fin, last);
+  launch_combine_class<2, uint32_t>(d, st, l, s, fin, last);
+  launch_combine_class<1, uint32_t>(d, st, l, s, fin, last);
+  launch_combine_class<4, uint64_t>(d, st, l, s, fin, last);
+  launch_combine_class<2, uint64_t>(d, st, l, s, fin, last);
+  launch_combine_class<1, uint64_t>(d, st, l, s, fin, last);
 }
 
 static DeviceTable device_table(const sk_batch_s* b) { return DeviceTable{b->d_probs, b->d_members, b->d_begins}; }
 
 static int launch_sequence(sk_batch_s* b, hipStream_t s) {
-  launch_pass_a_table(b->d_probs, b->n, b->lay.ta, b->grid_a, b->d_counter, s);
+  launch_pass_a_batch(b, s);
   SK_HIP_TRY(hipGetLastError());
   const BatchFinal fin{b->d_state, b->d_counter, b->d_counter + 1, b->n};
   launch_pass_b_table(device_table(b), b->d_state, b->n, b->lay, s, fin);
@@ -564,7 +644,7 @@ static float best_time(hipStream_t s, uint32_t* counter, int reps, Fn run) {
 // Pass A of the whole batch alone (profiling), best of three.
 static float time_pass_a_batch(sk_batch_s* b, hipStream_t s) {
   return best_time(s, b->d_counter, 3,
-                   [&] { launch_pass_a_table(b->d_probs, b->n, b->lay.ta, b->grid_a, b->d_counter, s); });
+                   [&] { launch_pass_a_batch(b, s); });
 }
 
 // Autotuner. Problems are grouped by class (N, M, F). For each class not in
@@ -667,10 +747,7 @@ static int tune_batch(sk_batch_s* b, const std::string& path, hipStream_t s) {
       cache[key + "|pick"] = rows * 100 + q * 10 + R;
       dirty = true;
     }
-    for (int m : members) {
-      set_pass_a(b->host[m], rows, q);
-      set_pass_b(b->host[m], R);
-    }
+    for (int m : members) b->picks[m] = Pick{rows, q, R};
     if (rc) break;
   }
   (void)hipFree(d.probs);
@@ -679,6 +756,113 @@ static int tune_batch(sk_batch_s* b, const std::string& path, hipStream_t s) {
   if (rc == SK_OK && hipGetLastError() != hipSuccess) rc = SK_ERR_DEVICE;
   if (rc) { set_error("autotuning launch failed"); return rc; }
   if (dirty) save_cache(path, cache);
+  return SK_OK;
+}
+
+// Longest tasks first. A task's duration is set by the rows each lane
+// walks one after the other (M per block, times the blocks a wide-row task
+// walks), not by its bytes: those lead the queue and the short tasks fill
+// in behind them, so no long task starts when the queue is nearly empty.
+// Ties go to the larger problem. (Row-phase form: by the bytes of a task.)
+static void order_queue(sk_batch_s* b) {
+  auto walk = [](const BatchProb& P) {
+    return (int64_t)P.a.block_len * (P.units ? P.units : P.lpr >= 256 ? P.a.blocks_per_task : 1);
+  };
+  auto bytes = [](const BatchProb& P) { return (int64_t)P.a.n_blocks * P.a.block_len * P.a.row_bytes; };
+  const int n = b->n;
+  std::vector<int> perm(n);
+  std::iota(perm.begin(), perm.end(), 0);
+  std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) {
+    const int64_t wx = walk(b->host[x]), wy = walk(b->host[y]);
+    if (wx != wy) return wx > wy;
+    return bytes(b->host[x]) > bytes(b->host[y]);
+  });
+  std::vector<BatchProb> host(n);
+  std::vector<int> order(n), cached(n);
+  std::vector<Pick> picks(n);
+  for (int q = 0; q < n; ++q) {
+    host[q] = b->host[perm[q]];
+    order[q] = b->order[perm[q]];
+    cached[q] = b->tuned_from_cache[perm[q]];
+    picks[q] = b->picks[perm[q]];
+  }
+  b->host.swap(host);
+  b->order.swap(order);
+  b->tuned_from_cache.swap(cached);
+  b->picks.swap(picks);
+}
+
+static int64_t batch_bytes(const sk_batch_s* b) {
+  int64_t total = 0;
+  for (const BatchProb& P : b->host) total += (int64_t)P.a.n_blocks * P.a.block_len * P.a.row_bytes;
+  return total;
+}
+
+// Sets every problem up for a form and orders the queue.
+static void apply_form(sk_batch_s* b, int form) {
+  const int64_t total = batch_bytes(b);
+  for (int q = 0; q < b->n; ++q) {
+    BatchProb& P = b->host[q];
+    if (form == FORM_PICKS) {
+      set_pass_a(P, b->picks[q].rows, b->picks[q].blocks);
+      set_pass_b(P, b->picks[q].chunk);
+    } else {
+      set_pass_a_phased(P, total);
+      set_pass_b(P, form == FORM_PHASED_4 ? 4 : 2);
+    }
+  }
+  b->form = form;
+  order_queue(b);
+}
+
+// The form of a batch's calls. With a tuning path: each form's whole call is
+// timed (best of kTuneReps after one untimed) unless the cache holds the pick of
+// a batch of as many problems and bytes. Without: the picks' form for batches
+// mostly of wide rows and 1 GiB or more, whose blocks' sums are best held back
+// (2048 inputs, 4 channels, M = 256, 2 GiB: pass A 341 us against 352 in row
+// phases), row phases for the others (five problems, 79 MB: 25 us against 194;
+// ten, 598 MB: 113 against 227), at 4 blocks per chunk where that leaves 4096
+// wavefronts.
+static int choose_form(sk_batch_s* b, const std::string* path, hipStream_t s) {
+  bool fits = true;
+  int64_t wide = 0, waves = 0;
+  const int64_t total = batch_bytes(b);
+  for (const BatchProb& P : b->host) {
+    fits = fits && phased_fits(P);
+    if (P.lpr == 512 && P.a.block_len >= 128) wide += (int64_t)P.a.n_blocks * P.a.block_len * P.a.row_bytes;
+    waves += (int64_t)(P.a.row_bytes / P.a.n_inputs) * P.waves * ((P.a.n_blocks + 3) / 4);
+  }
+  int best = !fits || (wide >= ((int64_t)1 << 30) && 2 * wide >= total) ? FORM_PICKS
+             : waves >= 4096                                            ? FORM_PHASED_4
+                                                                        : FORM_PHASED_2;
+  if (path && fits) {
+    char key[256];
+    snprintf(key, sizeof key, "%s|batch|set|n=%d|bytes=%lld|form", b->arch.c_str(), b->n, (long long)total);
+    std::map<std::string, int> cache = load_cache(*path);
+    auto it = cache.find(key);
+    if (it != cache.end() && it->second >= 0 && it->second < N_FORMS) {
+      best = it->second;
+    } else {
+      float least = 1e30f;
+      for (int form = 0; form < N_FORMS; ++form) {
+        apply_form(b, form);
+        b->lay = layout(b->host);
+        if (upload_table(device_table(b), b->host, b->lay, s) != hipSuccess) {
+          set_error("batch table upload failed");
+          return SK_ERR_DEVICE;
+        }
+        const float t = best_time(s, b->d_counter, kTuneReps, [&] {
+          launch_pass_a_batch(b, s);
+          launch_pass_b_table(device_table(b), b->d_state, b->n, b->lay, s);
+        });
+        if (t < least) { least = t; best = form; }
+      }
+      if (hipGetLastError() != hipSuccess) { set_error("autotuning launch failed"); return SK_ERR_DEVICE; }
+      cache[key] = best;
+      save_cache(*path, cache);
+    }
+  }
+  apply_form(b, best);
   return SK_OK;
 }
 
@@ -707,6 +891,8 @@ int sk_batch_create(const sk_plan_desc* descs, int32_t n, const sk_batch_opts* o
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, batch_pass_a_kernel, 512, 0) != hipSuccess || occ < 1) occ = 1;
   b->grid_a = occ * prop.multiProcessorCount;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, batch_pass_a_phased_kernel, 512, 0) != hipSuccess || occ < 1) occ = 1;
+  b->grid_p = occ * prop.multiProcessorCount;
   b->use_graph = !opts || opts->use_graph;
 
   // Table order while tuning: largest problems first (the queue order is
@@ -815,39 +1001,15 @@ int sk_batch_create(const sk_plan_desc* descs, int32_t n, const sk_batch_opts* o
   // Per-class tile choices: timed on this batch's problems, or from the
   // cache keyed by (arch, N, M, F).
   b->tuned_from_cache.assign(n, 0);
-  const bool tune = !opts || opts->autotune;
-  if (tune) {
-    rc = tune_batch(b, cache_path(opts), s);
+  b->picks.resize(n);
+  for (int q = 0; q < n; ++q) b->picks[q] = Pick{b->host[q].rows, 1, b->host[q].chunk};
+  const std::string tune_path = cache_path(opts);
+  if (!opts || opts->autotune) {
+    rc = tune_batch(b, tune_path, s);
     if (rc) { batch_free(b); return rc; }
   }
-  // Longest tasks first. A task's duration is set by the rows each lane
-  // walks one after the other (M per block, times the blocks a wide-row task
-  // walks), not by its bytes: those lead the queue and the short tasks fill
-  // in behind them, so no long task starts when the queue is nearly empty.
-  // Ties go to the larger problem.
-  {
-    auto walk = [](const BatchProb& P) {
-      return (int64_t)P.a.block_len * (P.lpr >= 256 ? P.a.blocks_per_task : 1);
-    };
-    auto bytes = [](const BatchProb& P) { return (int64_t)P.a.n_blocks * P.a.block_len * P.a.row_bytes; };
-    std::vector<int> perm(n);
-    std::iota(perm.begin(), perm.end(), 0);
-    std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) {
-      const int64_t wx = walk(b->host[x]), wy = walk(b->host[y]);
-      if (wx != wy) return wx > wy;
-      return bytes(b->host[x]) > bytes(b->host[y]);
-    });
-    std::vector<BatchProb> host(n);
-    std::vector<int> order(n), cached(n);
-    for (int q = 0; q < n; ++q) {
-      host[q] = b->host[perm[q]];
-      order[q] = b->order[perm[q]];
-      cached[q] = b->tuned_from_cache[perm[q]];
-    }
-    b->host.swap(host);
-    b->order.swap(order);
-    b->tuned_from_cache.swap(cached);
-  }
+  rc = choose_form(b, opts && !opts->autotune ? nullptr : &tune_path, s);
+  if (rc) { batch_free(b); return rc; }
   {
     b->lay = layout(b->host);
     const Layout& l = b->lay;
@@ -915,7 +1077,7 @@ int sk_batch_get_tiles(sk_batch_t b, int32_t j, int32_t* lpr, int32_t* grid) {
   if (!b || j < 0 || j >= b->n || !lpr || !grid) { set_error("bad arguments"); return SK_ERR_INVALID_ARG; }
   for (int q = 0; q < b->n; ++q)
     if (b->order[q] == j) *lpr = b->host[q].lpr;
-  *grid = b->grid_a;
+  *grid = b->form == FORM_PICKS ? b->grid_a : b->grid_p;
   return SK_OK;
 }
 
@@ -929,9 +1091,9 @@ int sk_batch_get_tuning(sk_batch_t b, int32_t j, int32_t* rows, int32_t* blocks,
   for (int q = 0; q < b->n; ++q) {
     if (b->order[q] != j) continue;
     const BatchProb& P = b->host[q];
-    *rows = P.rows;
-    *blocks = P.a.blocks_per_task;
-    *chunk = P.chunk;
+    *rows = b->picks[q].rows;
+    *blocks = P.lpr >= 256 ? b->picks[q].blocks : 256 / P.lpr;
+    *chunk = b->picks[q].chunk;
     *from_cache = b->tuned_from_cache.empty() ? 0 : b->tuned_from_cache[q];
   }
   return SK_OK;

@@ -299,30 +299,6 @@ __global__ __launch_bounds__(512) void pass_a_deferred_kernel(PassATask t) {
   }
 }
 
-// Stores four columns from column c on (S1 a, S2 b) of block `blk`; they may
-// straddle channels, and the sums' rows need only 4-byte alignment.
-__device__ __forceinline__ void store_quad(const PassATask& t, int blk, int c, u32x4 a, u32x4 b) {
-  typedef u32x4 u32x4_word __attribute__((aligned(4)));
-  const int N = t.n_inputs, B = t.n_blocks;
-  int f = c / N, i = c - f * N;
-  const int64_t d = ((int64_t)f * B + blk) * N + i;
-  if (i + 4 <= N) {
-    *reinterpret_cast<u32x4_word*>(t.s1 + d) = a;
-    *reinterpret_cast<u32x4_word*>(t.s2 + d) = b;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t e = ((int64_t)f * B + blk) * N + i;
-      t.s1[e] = (int32_t)a[j];
-      t.s2[e] = (int32_t)b[j];
-      if (++i == N) {
-        i = 0;
-        ++f;
-      }
-    }
-  }
-}
-
 // Variant 5 (library choice only): packed lane table with row phases, any N and
 // any alignment. A unit is 16 consecutive bytes of a row over one block (they
 // may straddle two channels); when 16 does not divide the row, its last unit is
@@ -344,147 +320,20 @@ __device__ __forceinline__ void store_quad(const PassATask& t, int blk, int c, u
 // us (the shared table's bank conflicts before).
 template <int LPR>
 __global__ __launch_bounds__(512, 4) void pass_a_phased_kernel(PassATask t) {
-  constexpr int VEC = 16, RP = 512 / LPR;
-  constexpr int S = LPR + 1;            // accumulator row stride
-  constexpr int NV = LPR >= 64 ? 32 : LPR == 32 ? 16 : 8;   // sums a lane adds
-  // Accumulators: S1 of column k of unit g at k S + g, S2 at (16 + k) S + g;
-  // in the table's place where they would cost a second workgroup per CU.
-  constexpr bool OVER = LPR > 64;
+  constexpr int S = phased_stride(LPR);
+  // The sums where the phases meet, in the table's place where they would cost a
+  // second workgroup per CU.
+  constexpr bool OVER = LPR > 64, RED = !OVER && LPR < 512;
   __shared__ __attribute__((aligned(16))) uint32_t lut32[LANE_LUT_DWORDS];
-  __shared__ uint32_t red_own[OVER || RP == 1 ? 1 : 2 * VEC * S];
-  uint32_t* red = OVER ? lut32 : red_own;
+  __shared__ uint32_t red_own[RED ? 32 * S : 1];
   const int tid = threadIdx.x;
-  const int lc = tid % LPR;
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
-  const int M = t.block_len, ph = tid / LPR;
-  const int G = (int)t.row_bytes, cg = t.col_groups;
-  constexpr int STEP = PHASE_ROWS * RP;   // rows of the block per batch
-  const int64_t step_bytes = (int64_t)STEP * G;
-  const int u0 = (int)blockIdx.x * LPR, units = t.n_blocks * cg;
-  const int b_first = u0 / cg;            // uniform: the lanes' offsets start at this block
-  uint32_t col0;
-  {
-    const int u = u0 + lc < units ? u0 + lc : units - 1;
-    const int bl = u / cg, c = (u - bl * cg) * VEC;
-    col0 = (uint32_t)(bl - b_first) * (uint32_t)M * (uint32_t)G + (uint32_t)(c < G - VEC ? c : G - VEC);
-  }
-  const uint8_t* p = t.x + (int64_t)b_first * M * G;
-  u32x4 qa[PHASE_ROWS], qb[PHASE_ROWS];
-  phased_load_end<RP>(qa, p, M, G, ph, col0);
-  fill_lane_packed_lut<512>(lut32, tid);
-  if constexpr (!OVER && RP > 1)
-    for (int o = tid; o < 2 * VEC * S; o += 512) red[o] = 0u;
-  lds_barrier();
-  uint32_t v[2 * VEC], acc[VEC];
-#pragma unroll
-  for (int k = 0; k < 2 * VEC; ++k) v[k] = 0;
-#pragma unroll
-  for (int k = 0; k < VEC; ++k) acc[k] = 0;
-  const auto unpack = [&] {
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) {
-      v[k] += acc[k] & ((1u << PACK_SHIFT) - 1);
-      v[VEC + k] += acc[k] >> PACK_SHIFT;
-      acc[k] = 0;
-    }
-  };
-  const uint32_t off = __umul24(ph, G) + col0;
-  int left = M;
-  // Whole batches four at a time (16 rows, one packed run), the next one in
-  // flight, while another whole batch follows them; then the at most five
-  // batches that remain (20 rows still fit the packed sums: 20 * 128 < 2^12).
-  for (; left >= 5 * STEP; left -= 4 * STEP) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      p += step_bytes;
-      phased_load<RP>(qb, p, G, off);
-      phased_add(qa, lut, acc);
-      p += step_bytes;
-      phased_load<RP>(qa, p, G, off);
-      phased_add(qb, lut, acc);
-    }
-    unpack();
-  }
-  // (A fetch past the end reads the last row: under a branch instead, the wait
-  // for the batch before it would cover the fetch too.)
-  const auto fetch = [&](u32x4(&q)[PHASE_ROWS], int k) {
-    const int at = k * STEP < left ? k * STEP : left - 1;
-    phased_load_end<RP>(q, p + (int64_t)at * G, left - at, G, ph, col0);
-  };
-  const auto take = [&](u32x4(&q)[PHASE_ROWS], int k) {
-    phased_mask<RP>(q, left - k * STEP, ph);
-    phased_add(q, lut, acc);
-  };
-  fetch(qb, 1);
-  take(qa, 0);
-  if (left > STEP) {
-    fetch(qa, 2);
-    take(qb, 1);
-    if (left > 2 * STEP) {
-      fetch(qb, 3);
-      take(qa, 2);
-      if (left > 3 * STEP) {
-        fetch(qa, 4);
-        take(qb, 3);
-        if (left > 4 * STEP) take(qa, 4);
-      }
-    }
-  }
-  unpack();
-  if constexpr (RP == 1) {
-    const int u = u0 + lc;
-    if (u < units) {
-      const int blk = u / cg, c = (u - blk * cg) * VEC, c0 = c < G - VEC ? c : G - VEC;
-#pragma unroll
-      for (int k = 0; k < VEC; k += 4)
-        store_quad(t, blk, c0 + k, u32x4{v[k], v[k + 1], v[k + 2], v[k + 3]},
-                   u32x4{v[VEC + k], v[VEC + k + 1], v[VEC + k + 2], v[VEC + k + 3]});
-    }
-    return;
-  }
-  if constexpr (OVER) {
+  pass_a_task_phased<LPR, OVER, false>(t, (int)blockIdx.x * LPR, lut, OVER ? lut32 : red_own, tid, [&] {
+    fill_lane_packed_lut<512>(lut32, tid);
+    if constexpr (RED)
+      for (int o = tid; o < 32 * S; o += 512) red_own[o] = 0u;
     lds_barrier();
-    for (int o = tid; o < 2 * VEC * S; o += 512) red[o] = 0u;
-    lds_barrier();
-  }
-  // Sum over the wavefront's row groups, then over the wavefronts.
-  const int lane = tid & 63;
-  if constexpr (LPR >= 64) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) atomicAdd(&red[k * S + lc], v[k]);
-  } else {
-    uint32_t c[VEC];
-#pragma unroll
-    for (int m = 0; m < VEC; ++m) {
-      swap_halves(v[2 * m], v[2 * m + 1]);
-      c[m] = v[2 * m] + v[2 * m + 1];
-    }
-    if constexpr (LPR == 32) {
-#pragma unroll
-      for (int m = 0; m < VEC; ++m) atomicAdd(&red[(2 * m + (lane >> 5)) * S + lc], c[m]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        swap_rows(c[2 * q], c[2 * q + 1]);
-        uint32_t x = c[2 * q] + c[2 * q + 1];
-        if constexpr (LPR <= 8) x += row_rot<8>(x);
-        if constexpr (LPR <= 4) x += row_rot<4>(x);
-        if constexpr (LPR <= 2) x += row_rot<2>(x);
-        if constexpr (LPR <= 1) x += row_rot<1>(x);
-        if ((lane & 15) < LPR) atomicAdd(&red[wave_value_of_row(q, lane >> 4) * S + lc], x);
-      }
-    }
-  }
-  lds_barrier();
-  for (int o = tid; o < 4 * LPR; o += 512) {
-    const int lg = o >> 2, k = (o & 3) * 4, u = u0 + lg;
-    if (u < units) {
-      const int blk = u / cg, c = (u - blk * cg) * VEC, c0 = c < G - VEC ? c : G - VEC;
-      const uint32_t* r1 = red + k * S + lg;
-      const uint32_t* r2 = r1 + VEC * S;
-      store_quad(t, blk, c0 + k, u32x4{r1[0], r1[S], r1[2 * S], r1[3 * S]}, u32x4{r2[0], r2[S], r2[2 * S], r2[3 * S]});
-    }
-  }
+  });
 }
 
 static int launch_phased(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {
@@ -574,8 +423,9 @@ static int launch_vec(const PassATask& t, int lpr, int variant, int grid, hipStr
 //     M = 100), 12.7 / 9.5 (17 bytes): from 192 rows and 256 bytes;
 //   16-byte groups: 61 / 68 (2048 inputs, 403 MB), 43 / 51 (1024 inputs, 268 MB),
 //     11.5 / 13.8 (256 inputs, 50 MB), 21 / 65 (16 inputs, 67 MB), but 175 / 174 at
-//     1 GiB, 360 / 334 at 2 GiB and 105 / 102 for wide rows of M = 64: the variants
-//     whose lanes hold whole rows there; 5.5 / 5.3 below 1024 units (launch-bound).
+//     1 GiB, 360 / 334 at 2 GiB, 98 / 95 at 0.5 GiB of M = 128 and 105 / 102 for wide
+//     rows of M = 64: the variants whose lanes hold whole rows there; 5.5 / 5.3 below
+//     1024 units (launch-bound).
 int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len) {
   const int64_t cg = (row_bytes + 15) / 16, units = cg * n_blocks;
   // 24-bit row bytes and 32-bit offsets over the blocks a workgroup spans.
@@ -583,7 +433,8 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
       (512 / cg + 2) * block_len * row_bytes >= ((int64_t)1 << 31))
     return 0;
   if (pick_vec(x, n_inputs) == 16) {
-    if (block_len < 32 || units * block_len * 16 > ((int64_t)1 << 29) || (cg >= 512 && block_len < 128)) return 0;
+    if (block_len < 32 || units * block_len * 16 > ((int64_t)1 << (block_len < 192 ? 28 : 29)) || (cg >= 512 && block_len < 128))
+      return 0;
   } else if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0) {
     if (block_len < 16) return 0;
   } else if (block_len < 192 || cg < 16) {

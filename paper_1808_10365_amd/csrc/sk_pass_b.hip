@@ -36,10 +36,10 @@ template <int V, int R>
 static void launch_combine_r(const PassBArgs& a, bool fit32, dim3 grid, dim3 wg, hipStream_t s, hipEvent_t e0,
                              hipEvent_t e1) {
   const bool off32 = combine_offsets_fit_32(a.n_inputs, a.n_blocks, a.n_chunks, a.hist_cap);
-  if (fit32 && off32) launch_kernel(combine_kernel<V, R, int32_t, true>, grid, wg, 0, s, e0, e1, a);
-  else if (fit32) launch_kernel(combine_kernel<V, R, int32_t, false>, grid, wg, 0, s, e0, e1, a);
-  else if (off32) launch_kernel(combine_kernel<V, R, int64_t, true>, grid, wg, 0, s, e0, e1, a);
-  else launch_kernel(combine_kernel<V, R, int64_t, false>, grid, wg, 0, s, e0, e1, a);
+  if (fit32 && off32) launch_kernel(combine_kernel<V, R, uint32_t, true>, grid, wg, 0, s, e0, e1, a);
+  else if (fit32) launch_kernel(combine_kernel<V, R, uint32_t, false>, grid, wg, 0, s, e0, e1, a);
+  else if (off32) launch_kernel(combine_kernel<V, R, uint64_t, true>, grid, wg, 0, s, e0, e1, a);
+  else launch_kernel(combine_kernel<V, R, uint64_t, false>, grid, wg, 0, s, e0, e1, a);
 }
 
 template <int V>
@@ -293,9 +293,9 @@ __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, 
       iv[2 * j + 1] = acc2[j];
     }
     double dout[(NV + 3) / 4];
-    RI iout[(NV + 3) / 4];
+    uint64_t iout[(NV + 3) / 4];
     wave_sums<NV>(dv, dout);
-    wave_sums<NV>(iv, iout);
+    wave_sums_wide<NV>(iv, iout);
     if ((lane & 15) == 0) {
 #pragma unroll
       for (int q = 0; q < (NV + 3) / 4; ++q) {
@@ -378,9 +378,9 @@ static int launch_window(const PassBArgs& a, hipStream_t s, PassEvents ev) {
   const int groups = (a.n_inputs + 255) / 256;
   const dim3 grid(a.n_channels * (W * segs + groups * shift_wgs)), wg(64 * WINDOW_WAVES);
   if (combine_sums_fit_32(a.n_inputs, 4, a.block_len))
-    launch_kernel(window_kernel<R, int32_t>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
+    launch_kernel(window_kernel<R, uint32_t>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
   else
-    launch_kernel(window_kernel<R, int64_t>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
+    launch_kernel(window_kernel<R, uint64_t>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
   SK_HIP_TRY(hipGetLastError());
   return SK_OK;
 }

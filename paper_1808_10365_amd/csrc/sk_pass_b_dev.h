@@ -353,7 +353,7 @@ __device__ __forceinline__ const int32_t* elem_at(const int32_t* base, int64_t e
 }
 
 // Chunk k of channel f, wavefront w of W. R blocks per chunk, V inputs per
-// lane, RI the integer type of a lane's R1/R2 sums, OFF32 when every
+// lane, RI the unsigned type of a lane's R1/R2 sums, OFF32 when every
 // per-channel array holds fewer than 2^30 elements.
 //
 // Every lane loads: a lane past the last input reads the last V inputs (in
@@ -592,9 +592,9 @@ __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, i
       iv[2 * j + 1] = acc2[j];
     }
     double dout[(NV + 3) / 4];
-    RI iout[(NV + 3) / 4];
+    uint64_t iout[(NV + 3) / 4];
     wave_sums<NV>(dv, dout);
-    wave_sums<NV>(iv, iout);
+    wave_sums_wide<NV>(iv, iout);
     const int r = lane >> 4;
     if ((lane & 15) == 0) {
 #pragma unroll
@@ -653,14 +653,15 @@ __host__ __device__ __forceinline__ bool combine_offsets_fit_32(int n_inputs, in
   return n_blocks * n_inputs < lim && ((int64_t)n_chunks + 1) * n_inputs < lim && (int64_t)hist_cap * n_inputs < lim;
 }
 
-// Integer type of a lane's R1/R2 sums: 32 bits while a whole wavefront's
-// S2 sums fit (64 V M 2^14 < 2^31, S2 of one input <= M 2^14), over all the
-// groups a wavefront takes.
+// Integer type of a lane's R1/R2 sums: 32 bits while half a wavefront's S2 sums
+// fit (32 V M 2^14 < 2^32, S2 of one input <= M 2^14; the last addition of the
+// wavefront sum is in 64 bits), over all the groups a wavefront takes: M < 2048
+// up to 2048 inputs.
 __host__ __device__ __forceinline__ bool combine_sums_fit_32(int n_inputs, int vec, int block_len) {
   const int W = combine_waves(n_inputs, vec);
   const int64_t groups = (n_inputs + 64 * vec - 1) / (64 * vec);
   const int64_t per_wave = (groups + W - 1) / W;
-  return per_wave * 64 * vec * (int64_t)block_len * 16384 < ((int64_t)1 << 31);
+  return per_wave * 32 * vec * (int64_t)block_len * 16384 < ((int64_t)1 << 32);
 }
 
 }  // namespace sk

@@ -89,6 +89,36 @@ __device__ __forceinline__ T row_total(T v) {
   return v;
 }
 
+// The same in 32 bits up to the last addition, which is in 64: sums whose halves
+// fit (unsigned) need no wider steps before it.
+__device__ __forceinline__ uint64_t row_total_wide(uint32_t v) {
+  v = v + row_rot<8>(v);
+  v = v + row_rot<4>(v);
+  v = v + row_rot<2>(v);
+  return (uint64_t)v + row_rot<1>(v);
+}
+__device__ __forceinline__ uint64_t row_total_wide(uint64_t v) { return row_total(v); }
+
+// Integer sums of NV values (NV a power of two >= 2) over the wavefront, laid
+// out as wave_sums.
+template <int NV, typename T>
+__device__ __forceinline__ void wave_sums_wide(const T (&v)[NV], uint64_t (&out)[(NV + 3) / 4]) {
+  constexpr int NC = NV / 2;
+  T c[NC];
+#pragma unroll
+  for (int m = 0; m < NC; ++m) {
+    T x = v[2 * m], y = v[2 * m + 1];
+    swap_halves(x, y);
+    c[m] = x + y;
+  }
+#pragma unroll
+  for (int q = 0; q < (NV + 3) / 4; ++q) {
+    T x = c[2 * q], y = 2 * q + 1 < NC ? c[2 * q + 1] : c[2 * q];
+    swap_rows(x, y);
+    out[q] = row_total_wide(x + y);
+  }
+}
+
 // Sums each of NV values (NV a power of two >= 2) over the wavefront.
 // Value j ends in every lane of the row of out[j / 4] that
 // wave_value_of_row names.
