@@ -33,6 +33,7 @@ struct BatchProb {
   int32_t waves;               // combine waves per chunk (inputs / 256, at most 8)
   int32_t scan_waves;          // scan waves per 64-input slice (power of two, at most 8)
   int32_t wide_sums;           // 1: the combine's R1/R2 sums need 64 bits
+  int32_t steps;               // chunks a combine wavefront walks (the stepped combine), or 0: combine_body
   double k_sigma, expect_offset, sigma_override;
   uint32_t* pc;                // pass B prefix sums
   int32_t* cs_buf;             // chunk sums (wide rows, window >= 2; sized for chunks of 2 blocks), or null
@@ -298,6 +299,41 @@ __global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void batch_combine_kernel(
   }
 }
 
+// The same for problems of the stepped combine: a workgroup takes 8 / W runs of
+// P.steps chunks.
+template <int R, typename RI, bool OFF32>
+__global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void batch_step_kernel(
+    const BatchProb* __restrict__ probs, const BatchState* st, const int32_t* __restrict__ members,
+    const int64_t* __restrict__ begins, int count, BatchFinal fin) {
+  __shared__ StepShared sh;
+  __shared__ uint32_t last_out;
+  const int64_t task = blockIdx.x;
+  const int p = members[last_at_or_before(count, task, [&](int j) { return begins[j]; })];
+  const BatchProb& P = probs[p];
+  const int64_t lt = task - P.cb_begin;
+  if (lt < P.cb_count) {
+    const PassBArgs a = make_args(P, st[p]);
+    const int W = P.waves, cpw = COMBINE_MAX_WAVES / W, steps = P.steps;
+    const int runs = (a.n_chunks + steps - 1) / steps, groups = (runs + cpw - 1) / cpw;
+    const int f = (int)(lt / groups), run0 = (int)(lt % groups) * cpw;
+    const int w = wave_id(), sub = w / W, k0 = (run0 + sub) * steps;
+    if (sub < cpw && k0 < a.n_chunks) step_body<R, RI, OFF32>(a, k0, steps, f, w % W, w, sh);
+    __syncthreads();
+    const int t = threadIdx.x, s = t / STEP_BLOCKS, j = t % STEP_BLOCKS;
+    const int b = (run0 + s) * steps * R + j;
+    if (s < cpw && j < steps * R && b < a.n_blocks) step_finish(a, f, b, j, s * W, W, sh);
+  }
+  if (fin.st) {
+    __syncthreads();   // every wavefront of this workgroup has read the state
+    if (threadIdx.x == 0) last_out = atomicAdd(fin.done, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (last_out) {
+      advance_state(probs, fin.st, fin.n, fin.counter, threadIdx.x, blockDim.x);
+      if (threadIdx.x == 0) *fin.done = 0u;
+    }
+  }
+}
+
 // Last node: advance every problem's history and rearm the work queue.
 __global__ __launch_bounds__(256) void batch_state_kernel(const BatchProb* __restrict__ probs,
                                                           BatchState* st, int n, uint32_t* counter) {
@@ -366,11 +402,11 @@ void save_cache(const std::string& path, const std::map<std::string, int>& m) {
 
 // Task ranges of every kernel over a table of problems. Combine classes:
 // chunk length R in {1, 2, 4} (class R / 2 = 0, 1, 2) plus 3 when the R1/R2
-// sums need 64 bits.
-constexpr int N_COMBINE_CLASSES = 6;
+// sums need 64 bits, plus 6 for the stepped combine.
+constexpr int N_COMBINE_CLASSES = 12;
 
-__host__ __device__ __forceinline__ int combine_class(int chunk, int wide_sums) {
-  return (chunk == 1 ? 0 : chunk == 2 ? 1 : 2) + 3 * wide_sums;
+__host__ __device__ __forceinline__ int combine_class(int chunk, int wide_sums, bool stepped) {
+  return (chunk == 1 ? 0 : chunk == 2 ? 1 : 2) + 3 * wide_sums + (stepped ? 6 : 0);
 }
 
 struct Layout {
@@ -512,15 +548,23 @@ static Layout layout(std::vector<BatchProb>& tab) {
     l.tsc += P.sc_count;
     if (!combine_offsets_fit_32(P.a.n_inputs, P.a.n_blocks, P.n_chunks, P.hist_cap)) l.off32 = false;
   }
+  int64_t waves = 0;   // stepped combine, one chunk each
+  for (BatchProb& P : tab) {
+    P.steps = steps_suit(P.a.n_inputs, P.window, 4, P.chunk, P.a.n_blocks) ? 1 : 0;
+    if (P.steps) waves += (int64_t)(P.a.row_bytes / P.a.n_inputs) * P.n_chunks * P.waves * P.chunk;
+  }
+  for (BatchProb& P : tab)
+    if (P.steps) P.steps = step_chunks(P.chunk, waves / P.chunk);
   for (int c = 0; c < N_COMBINE_CLASSES; ++c) {
     l.cls_off[c] = (int)l.members.size();
     for (size_t q = 0; q < tab.size(); ++q) {
       BatchProb& P = tab[q];
-      if (combine_class(P.chunk, P.wide_sums) != c) continue;
+      if (combine_class(P.chunk, P.wide_sums, P.steps > 0) != c) continue;
       const int64_t F = P.a.row_bytes / P.a.n_inputs;
       const int cpw = COMBINE_MAX_WAVES / P.waves;
       P.cb_begin = l.tcb[c];
-      P.cb_count = F * ((P.n_chunks + cpw - 1) / cpw);
+      const int runs = P.steps ? (P.n_chunks + P.steps - 1) / P.steps : P.n_chunks;
+      P.cb_count = F * ((runs + cpw - 1) / cpw);
       l.tcb[c] += P.cb_count;
       l.members.push_back((int32_t)q);
       l.begins.push_back(P.cb_begin);
@@ -559,27 +603,33 @@ static void launch_pass_a_batch(const sk_batch_s* b, hipStream_t s) {
   else batch_pass_a_phased_kernel<<<dim3(b->grid_p), dim3(512), 0, s>>>(b->d_probs, b->n, b->lay.ta, b->d_counter);
 }
 
-template <int R, typename RI>
+template <int R, typename RI, bool STEPPED>
 static void launch_combine_class(const DeviceTable& d, BatchState* st, const Layout& l, hipStream_t s,
                                  const BatchFinal& fin, int last_class) {
-  const int c = combine_class(R, sizeof(RI) == 8 ? 1 : 0);
+  const int c = combine_class(R, sizeof(RI) == 8 ? 1 : 0, STEPPED);
   if (l.tcb[c] <= 0) return;
   const dim3 grid((unsigned)l.tcb[c]), wg(64 * COMBINE_MAX_WAVES);
   const int32_t* m = d.members + l.cls_off[c];
   const int64_t* bg = d.begins + l.cls_off[c];
   const BatchFinal f = c == last_class ? fin : BatchFinal{nullptr, nullptr, nullptr, 0};
-  if (l.off32) batch_combine_kernel<R, RI, true><<<grid, wg, 0, s>>>(d.probs, st, m, bg, l.cls_cnt[c], f);
-  else batch_combine_kernel<R, RI, false><<<grid, wg, 0, s>>>(d.probs, st, m, bg, l.cls_cnt[c], f);
+  if constexpr (STEPPED) {
+    if (l.off32) batch_step_kernel<R, RI, true><<<grid, wg, 0, s>>>(d.probs, st, m, bg, l.cls_cnt[c], f);
+    else batch_step_kernel<R, RI, false><<<grid, wg, 0, s>>>(d.probs, st, m, bg, l.cls_cnt[c], f);
+  } else {
+    if (l.off32) batch_combine_kernel<R, RI, true><<<grid, wg, 0, s>>>(d.probs, st, m, bg, l.cls_cnt[c], f);
+    else batch_combine_kernel<R, RI, false><<<grid, wg, 0, s>>>(d.probs, st, m, bg, l.cls_cnt[c], f);
+  }
 }
 
-// Combine classes in launch order.
-static const int kCombineOrder[N_COMBINE_CLASSES][2] = {{4, 0}, {2, 0}, {1, 0}, {4, 1}, {2, 1}, {1, 1}};
+// Combine classes in launch order: (chunk length, 64-bit sums, stepped).
+static const int kCombineOrder[N_COMBINE_CLASSES][3] = {{4, 0, 1}, {2, 0, 1}, {1, 0, 1}, {4, 1, 1}, {2, 1, 1}, {1, 1, 1},
+                                                        {4, 0, 0}, {2, 0, 0}, {1, 0, 0}, {4, 1, 0}, {2, 1, 0}, {1, 1, 0}};
 
 // The class whose combine launch comes last in a call, or -1 without one.
 static int last_combine_class(const Layout& l) {
   int last = -1;
   for (const auto& rc : kCombineOrder) {
-    const int c = combine_class(rc[0], rc[1]);
+    const int c = combine_class(rc[0], rc[1], rc[2] != 0);
     if (l.tcb[c] > 0) last = c;
   }
   return last;
@@ -592,12 +642,18 @@ static void launch_pass_b_table(const DeviceTable& d, BatchState* st, int n, con
                                 const BatchFinal& fin = BatchFinal{nullptr, nullptr, nullptr, 0}) {
   if (l.tsc > 0) batch_scan_kernel<<<dim3((unsigned)l.tsc), dim3(64 * BATCH_SCAN_WAVES), 0, s>>>(d.probs, st, n);
   const int last = fin.st ? last_combine_class(l) : -1;
-  launch_combine_class<4, uint32_t>(d, st, l, s, fin, last);
-  launch_combine_class<2, uint32_t>(d, st, l, s, fin, last);
-  launch_combine_class<1, uint32_t>(d, st, l, s, fin, last);
-  launch_combine_class<4, uint64_t>(d, st, l, s, fin, last);
-  launch_combine_class<2, uint64_t>(d, st, l, s, fin, last);
-  launch_combine_class<1, uint64_t>(d, st, l, s, fin, last);
+  launch_combine_class<4, uint32_t, true>(d, st, l, s, fin, last);
+  launch_combine_class<2, uint32_t, true>(d, st, l, s, fin, last);
+  launch_combine_class<1, uint32_t, true>(d, st, l, s, fin, last);
+  launch_combine_class<4, uint64_t, true>(d, st, l, s, fin, last);
+  launch_combine_class<2, uint64_t, true>(d, st, l, s, fin, last);
+  launch_combine_class<1, uint64_t, true>(d, st, l, s, fin, last);
+  launch_combine_class<4, uint32_t, false>(d, st, l, s, fin, last);
+  launch_combine_class<2, uint32_t, false>(d, st, l, s, fin, last);
+  launch_combine_class<1, uint32_t, false>(d, st, l, s, fin, last);
+  launch_combine_class<4, uint64_t, false>(d, st, l, s, fin, last);
+  launch_combine_class<2, uint64_t, false>(d, st, l, s, fin, last);
+  launch_combine_class<1, uint64_t, false>(d, st, l, s, fin, last);
 }
 
 static DeviceTable device_table(const sk_batch_s* b) { return DeviceTable{b->d_probs, b->d_members, b->d_begins}; }

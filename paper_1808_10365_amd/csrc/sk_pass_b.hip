@@ -32,6 +32,37 @@ __global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void combine_kernel(PassBAr
   combine_body<V, R, RI, OFF32>(a, blockIdx.x, blockIdx.y, wave_id(), blockDim.x >> 6, sh);
 }
 
+// One run of `steps` chunks per workgroup.
+template <int R, typename RI, bool OFF32>
+__global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void step_kernel(PassBArgs a, int steps) {
+  __shared__ StepShared sh;
+  const int f = blockIdx.y, k0 = (int)blockIdx.x * steps, W = blockDim.x >> 6;
+  step_body<R, RI, OFF32>(a, k0, steps, f, wave_id(), wave_id(), sh);
+  __syncthreads();
+  const int j = threadIdx.x, b = k0 * R + j;
+  if (j < steps * R && b < a.n_blocks) step_finish(a, f, b, j, 0, W, sh);
+}
+
+template <int R, bool OFF32>
+static void launch_step_r(const PassBArgs& a, bool fit32, int steps, dim3 grid, dim3 wg, hipStream_t s, hipEvent_t e0,
+                          hipEvent_t e1) {
+  if (fit32) launch_kernel(step_kernel<R, uint32_t, OFF32>, grid, wg, 0, s, e0, e1, a, steps);
+  else launch_kernel(step_kernel<R, uint64_t, OFF32>, grid, wg, 0, s, e0, e1, a, steps);
+}
+
+template <int R>
+static int launch_step(const PassBArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const bool fit32 = combine_sums_fit_32(a.n_inputs, 4, a.block_len);
+  const bool off32 = combine_offsets_fit_32(a.n_inputs, a.n_blocks, a.n_chunks, a.hist_cap);
+  const int W = combine_waves(a.n_inputs, 4);
+  const int steps = step_chunks(R, (int64_t)a.n_chunks * a.n_channels * W);
+  const dim3 grid((a.n_chunks + steps - 1) / steps, a.n_channels), wg(64 * W);
+  if (off32) launch_step_r<R, true>(a, fit32, steps, grid, wg, s, e0, e1);
+  else launch_step_r<R, false>(a, fit32, steps, grid, wg, s, e0, e1);
+  SK_HIP_TRY(hipGetLastError());
+  return SK_OK;
+}
+
 template <int V, int R>
 static void launch_combine_r(const PassBArgs& a, bool fit32, dim3 grid, dim3 wg, hipStream_t s, hipEvent_t e0,
                              hipEvent_t e1) {
@@ -413,6 +444,13 @@ int launch_pass_b(const PassBArgs& a, hipStream_t s, PassEvents ev) {
     }
     SK_HIP_TRY(hipGetLastError());
     start = nullptr;
+  }
+  if (steps_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks)) {
+    switch (a.chunk) {
+      case 1: return launch_step<1>(a, s, start, ev.stop);
+      case 2: return launch_step<2>(a, s, start, ev.stop);
+      case 4: return launch_step<4>(a, s, start, ev.stop);
+    }
   }
   const dim3 grid(a.n_chunks, F), wg(64 * combine_waves(a.n_inputs, a.vec));
   const bool fit32 = combine_sums_fit_32(a.n_inputs, a.vec, a.block_len);

@@ -634,6 +634,231 @@ __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, i
   }
 }
 
+// ------------------------------------------------------------------ stepped combine
+//
+// The combine of long calls with a window (L >= 2, up to 2048 inputs, 4 per
+// lane): a wavefront walks up to STEP_BLOCKS / R chunks of R blocks one after the
+// other, the next chunk's rows in flight while it works on one, and carries the
+// window from block to block. Only its first chunk reads prefix sums. Against one
+// chunk per wavefront: one start-up (and, batched, one problem lookup), one
+// barrier and one finish per run of blocks, and loads in flight throughout (CHIME,
+// M = 256: scan and combine 31.4 -> 28.4 us; 1024 inputs, 8 channels, M = 64, 1024
+// blocks: 39.4 -> 34.7). Bound by the memory its 106 MB come from, at about 6 TB/s.
+// Per block b the in-call window is C(b) = C(b - 1) + S1[b] - S1[b - L] (rows of
+// this call only) and the normaliser P(b) = C(b) + HS(b - L + 1), so each block
+// needs its two rows and either S1[b - L] or one history value.
+constexpr int STEP_BLOCKS = 16;
+
+struct StepShared {
+  double A[STEP_BLOCKS][COMBINE_MAX_WAVES];
+  double Q[STEP_BLOCKS][COMBINE_MAX_WAVES];
+  int64_t R1[STEP_BLOCKS][COMBINE_MAX_WAVES];
+  int64_t R2[STEP_BLOCKS][COMBINE_MAX_WAVES];
+  int32_t n[STEP_BLOCKS][COMBINE_MAX_WAVES];
+};
+
+// Whether a call takes the stepped combine (else combine_body): it has prefix sums,
+// and one group of 256 inputs per wavefront.
+__host__ __device__ __forceinline__ bool steps_suit(int n_inputs, int window, int vec, int chunk, int64_t n_blocks) {
+  return vec == 4 && n_inputs <= 2048 && pass_b_needs_scan(window, chunk, n_blocks);
+}
+
+// Chunks of R blocks a wavefront walks, `waves` being the wavefronts at one chunk
+// each: 16 blocks while that leaves two wavefronts per SIMD (8192 at 4 blocks: 28.4
+// us against 34.1 at one chunk each), else one chunk (4096: 25.1 against 27.1).
+__host__ __device__ __forceinline__ int step_chunks(int chunk, int64_t waves) {
+  return waves * chunk >= 32768 ? STEP_BLOCKS / chunk : 1;
+}
+
+template <int R>
+struct StepRows {
+  IVec<4> x1[R], x2[R], old[R];   // old: S1[b - L], or (b < L - 1) the history value of b's window
+};
+
+// Blocks [b0, b0 + R) of channel f for the 4 inputs from il on.
+template <int R, bool OFF32>
+__device__ __forceinline__ void step_load(const PassBArgs& a, const int32_t* s1c, const int32_t* s2c,
+                                          const int32_t* hsc, int b0, int il, StepRows<R>& x) {
+  const int N = a.n_inputs, L = a.window, B = a.n_blocks, H = a.hist_len;
+  if (b0 >= L && b0 + R <= B) {
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      x.x1[j].load(elem_at<OFF32>(s1c, (int64_t)(b0 + j) * N + il));
+      x.x2[j].load(elem_at<OFF32>(s2c, (int64_t)(b0 + j) * N + il));
+      x.old[j].load(elem_at<OFF32>(s1c, (int64_t)(b0 + j - L) * N + il));
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int b = b0 + j, y = b - L + 1;
+    zero(x.x1[j]);
+    zero(x.x2[j]);
+    zero(x.old[j]);
+    if (b < B) {
+      x.x1[j].load(elem_at<OFF32>(s1c, (int64_t)b * N + il));
+      x.x2[j].load(elem_at<OFF32>(s2c, (int64_t)b * N + il));
+      if (y > 0) x.old[j].load(elem_at<OFF32>(s1c, (int64_t)(y - 1) * N + il));
+      else if (y < 0 && H > 0) x.old[j].load(elem_at<OFF32>(hsc, (int64_t)((y < -H ? -H : y) + a.hist_cap) * N + il));
+    }
+  }
+}
+
+// Wavefront `w` of the W of one run: chunks [k0, k0 + steps) of channel f; its
+// sums go to column `col` of sh. Contains no barrier.
+template <int R, typename RI, bool OFF32>
+__device__ __forceinline__ void step_body(const PassBArgs& a, int k0, int steps, int f, int w, int col, StepShared& sh) {
+  constexpr int V = 4;
+  const int lane = threadIdx.x & 63;
+  const int N = a.n_inputs, L = a.window, B = a.n_blocks;
+  const int i0 = (w * 64 + lane) * V;
+  const bool active = i0 < N;
+  const int il = i0 < N - V ? i0 : N - V;
+  const int64_t rowF = (int64_t)f * B;
+  const int32_t* s1c = a.s1 + rowF * N;
+  const int32_t* s2c = a.s2 + rowF * N;
+  const int32_t* pcc = reinterpret_cast<const int32_t*>(a.pc) + (int64_t)f * (a.n_chunks + 1) * N;
+  const int32_t* hsc = a.hs + (int64_t)f * a.hist_cap * N;
+  const int run0 = k0 * R;
+  const int run_end = run0 + steps * R < B ? run0 + steps * R : B;
+  const int tail_from = B - a.hist_next_len;
+  const bool run_tail = a.hs_next && run_end > tail_from;
+  StepRows<R> cur, next;
+  step_load<R, OFF32>(a, s1c, s2c, hsc, run0, il, cur);
+  uint32_t use = active ? (1u << V) - 1 & ~0u << (i0 - il) : 0u;
+  if (a.mask) {
+#pragma unroll
+    for (int q = 0; q < V; ++q)
+      if (a.mask[(int64_t)f * N + il + q] == 0) use &= ~(1u << q);
+  }
+  // In-call window of block run0 - 1: rows [max(run0 - L, 0), run0), from prefix
+  // sums and the rows before the first chunk boundary at or after its start.
+  uint32_t C[V], suf[V];
+  {
+    IVec<V> p, q0, end;
+    zero(p);
+    zero(q0);
+    zero(end);
+    const int lo = run0 - L, kc = lo <= 0 ? 0 : (lo + R - 1) / R;
+    if (k0 > 0) p.load(elem_at<OFF32>(pcc, (int64_t)k0 * N + il));
+    if (kc > 0) q0.load(elem_at<OFF32>(pcc, (int64_t)kc * N + il));
+    if (run_tail) end.load(elem_at<OFF32>(pcc, (int64_t)a.n_chunks * N + il));
+    IVec<V> edge[R > 1 ? R - 1 : 1];
+#pragma unroll
+    for (int j = 0; j < R - 1; ++j) {
+      if (lo > 0 && lo + j < kc * R && lo + j < run0) edge[j].load(elem_at<OFF32>(s1c, (int64_t)(lo + j) * N + il));
+      else zero(edge[j]);
+    }
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      C[q] = (uint32_t)p.v[q] - (uint32_t)q0.v[q];
+#pragma unroll
+      for (int j = 0; j < R - 1; ++j) C[q] += (uint32_t)edge[j].v[q];
+      suf[q] = (uint32_t)end.v[q] - (uint32_t)p.v[q];     // S1 from the block to the call's end
+    }
+  }
+  for (int st = 0; st < steps; ++st) {
+    const int b0 = run0 + st * R;
+    if (b0 >= B) break;
+    if (st + 1 < steps && b0 + R < B) step_load<R, OFF32>(a, s1c, s2c, hsc, b0 + R, il, next);
+    const int nb = B - b0 < R ? B - b0 : R;
+    const bool tail = a.hs_next && b0 + nb > tail_from;
+    double accA[R], accQ[R];
+    RI acc1[R], acc2[R];
+    int cnt[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      accA[j] = accQ[j] = 0.0;
+      acc1[j] = acc2[j] = 0;
+      cnt[j] = 0;
+      if (j >= nb) continue;
+      const int b = b0 + j;
+      const bool gone = b >= L;                       // old is the row that leaves, else a history value
+      uint32_t P[V];
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const uint32_t o = (uint32_t)cur.old[j].v[q];
+        C[q] += (uint32_t)cur.x1[j].v[q] - (gone ? o : 0u);
+        P[q] = C[q] + (gone ? 0u : o);
+      }
+      if (tail && b >= tail_from && active) {
+        IVec<V> h;
+#pragma unroll
+        for (int q = 0; q < V; ++q) h.v[q] = (int32_t)suf[q];
+        h.store(a.hs_next + ((int64_t)f * a.hist_cap + (b - B + a.hist_cap)) * N + il);
+      }
+#pragma unroll
+      for (int q = 0; q < V; ++q) suf[q] -= (uint32_t)cur.x1[j].v[q];
+      if (a.sk_i && active) {
+        float* dst = a.sk_i + (rowF + b) * N + il;
+#pragma unroll
+        for (int q = 0; q < V; ++q) dst[q] = per_input_sk(cur.x1[j].v[q], cur.x2[j].v[q], a.block_len);
+      }
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const bool in = (use >> q & 1u) && (int32_t)P[q] > 0;
+        cnt[j] += __builtin_popcountll(__ballot(in));
+        const double rp = in ? recip_pos((double)P[q]) : 0.0;
+        accA[j] = __builtin_fma((double)cur.x1[j].v[q], rp, accA[j]);
+        accQ[j] = __builtin_fma((double)cur.x2[j].v[q] * rp, rp, accQ[j]);
+        acc1[j] += in ? (RI)cur.x1[j].v[q] : (RI)0;
+        acc2[j] += in ? (RI)cur.x2[j].v[q] : (RI)0;
+      }
+    }
+    constexpr int NV = 2 * R;
+    double dv[NV];
+    RI iv[NV];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      dv[2 * j] = accA[j];
+      dv[2 * j + 1] = accQ[j];
+      iv[2 * j] = acc1[j];
+      iv[2 * j + 1] = acc2[j];
+    }
+    double dout[(NV + 3) / 4];
+    uint64_t iout[(NV + 3) / 4];
+    wave_sums<NV>(dv, dout);
+    wave_sums_wide<NV>(iv, iout);
+    if ((lane & 15) == 0) {
+#pragma unroll
+      for (int q = 0; q < (NV + 3) / 4; ++q) {
+        const int val = wave_value_of_row(q, lane >> 4);
+        if (val < NV) {
+          const int j = st * R + (val >> 1);
+          if (val & 1) {
+            sh.Q[j][col] = dout[q];
+            sh.R2[j][col] = (int64_t)iout[q];
+          } else {
+            sh.A[j][col] = dout[q];
+            sh.R1[j][col] = (int64_t)iout[q];
+          }
+        }
+      }
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) sh.n[st * R + j][col] = cnt[j];
+    }
+    cur = next;
+  }
+}
+
+// Block j of a run whose W wavefronts hold columns col0 .. of sh: their sums in
+// order, then the estimator and flags.
+__device__ __forceinline__ void step_finish(const PassBArgs& a, int f, int b, int j, int col0, int W, const StepShared& sh) {
+  double A = 0.0, Bq = 0.0;
+  int64_t R1 = 0, R2 = 0;
+  int32_t n = 0;
+  for (int q = col0; q < col0 + W; ++q) {
+    A += sh.A[j][q];
+    Bq += sh.Q[j][q];
+    R1 += sh.R1[j][q];
+    R2 += sh.R2[j][q];
+    n += sh.n[j][q];
+  }
+  finish(a, f, b, A, Bq, R1, R2, n);
+}
+
 // Waves of a combine workgroup for N inputs at V per lane.
 __host__ __device__ __forceinline__ int combine_waves(int n_inputs, int vec) {
   const int g = (n_inputs + 64 * vec - 1) / (64 * vec);
