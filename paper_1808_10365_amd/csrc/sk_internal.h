@@ -53,12 +53,13 @@ struct PassATask {
                         // sk_plan_pass_a_timeline), one task per workgroup
   int32_t simd_balance; // variant 4: 1 = wavefronts of a SIMD kept level (the library's
                         // setting), 0 = left to the arbiter (timeline comparisons only)
+  int32_t by_xcd;       // variants 5, 6: consecutive tasks on one XCD, not in turn over all
 };
 
 struct PassAConfig {
   int vec;     // 16, 4 or 1 bytes per lane per row
   int lpr;     // lanes per row: power of two, 1..256
-  int variant; // 0 shared table; 16-byte path: 1, 2 packed, 3 side by side, 4 deferred stores; 5 phased
+  int variant; // 0 shared table; 16-byte path: 1, 2 packed, 3 side by side, 4 deferred stores; 5 phased, 6 shifted
   int grid;    // workgroups launched (<= tasks; grid-stride beyond)
 };
 
@@ -83,6 +84,8 @@ int launch_pass_a(const PassATask& t, const PassAConfig& c, hipStream_t s, PassE
 int pick_vec(const uint8_t* x, int32_t n_inputs);
 // Variant 5: units of 16 columns per workgroup, or 0 where it does not suit.
 int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len);
+// Variant 6: the same for rows off 4-byte boundaries (one unit is read twice).
+int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len);
 // Lanes per row the variant supports; the planner clamps into [lo, hi].
 void pass_a_lane_range(int vec, int variant, int* lo, int* hi);
 // Whether the variant uses the packed lane table (tasks may span several blocks).

@@ -314,7 +314,7 @@ __global__ __launch_bounds__(512) void pass_a_deferred_kernel(PassATask t) {
 // per value left.
 //
 // Bound by HBM for calls of about 50 MB to 0.5 GB, at 80 to 93 % of the read
-// ceiling: 1000 inputs, 3 channels, 98 MB 31.7 -> 20.2 us (4.9 TB/s; 4-byte lanes
+// ceiling: 1000 inputs, 3 channels, 98 MB 31.7 -> 18.8 us (5.2 TB/s; 4-byte lanes
 // before), 2048 inputs, 403 MB 68 -> 61 us (6.6 TB/s), 1024 inputs, 268 MB 51 ->
 // 43 us (6.2 TB/s; one wavefront per SIMD before), 256 inputs, 50 MB 13.8 -> 11.5
 // us (the shared table's bank conflicts before).
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(512, 4) void pass_a_phased_kernel(PassATask t) {
   __shared__ uint32_t red_own[RED ? 32 * S : 1];
   const int tid = threadIdx.x;
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
-  pass_a_task_phased<LPR, OVER, false>(t, (int)blockIdx.x * LPR, lut, OVER ? lut32 : red_own, tid, [&] {
+  pass_a_task_phased<LPR, OVER, false>(t, pass_a_task_of(t) * LPR, lut, OVER ? lut32 : red_own, tid, [&] {
     fill_lane_packed_lut<512>(lut32, tid);
     if constexpr (RED)
       for (int o = tid; o < 32 * S; o += 512) red_own[o] = 0u;
@@ -351,6 +351,47 @@ static int launch_phased(const PassATask& t, int lpr, int grid, hipStream_t s, P
     case 512: launch_kernel(pass_a_phased_kernel<512>, g, w, 0, s, ev.start, ev.stop, t); break;
     default:
       set_error("pass A: phased variant needs 1..512 lanes per row, got %d", lpr);
+      return SK_ERR_INVALID_ARG;
+  }
+  SK_HIP_TRY(hipGetLastError());
+  return SK_OK;
+}
+
+// Variant 6 (library choice only): row phases for rows that do not keep to 4-byte
+// boundaries. The phases are a multiple of four, so all rows of a lane start at the
+// same place within a dword, and the lane reads its 16 bytes from the aligned dword
+// at or before its unit: whole 16-byte loads of dwords, where the hardware splits
+// loads off a dword boundary, and byte loads cost a lane per column. The windows of
+// different phases lie up to 3 columns apart, so the phases meet in LDS column by
+// column, and a workgroup reads one unit more than it stores for the columns that
+// shifted windows of the next unit hold. Only aligned dwords that hold a byte of the
+// frame are read. 3003-byte rows, M = 256, 98 MB: 25 -> 20 us (5.0 TB/s, as rows of
+// 3000 bytes); M = 128, 0.4 GB: 95 -> 77; 65 MB of 2545-byte rows 20 -> 13.4. Bound by
+// the lines that the ends of a workgroup's rows share with others', and at short
+// blocks by the rows a last batch masks.
+template <int LPR>
+__global__ __launch_bounds__(512, 4) void pass_a_shifted_kernel(PassATask t) {
+  constexpr int S = shifted_stride(LPR);
+  __shared__ __attribute__((aligned(16))) uint32_t lut32[LANE_LUT_DWORDS];
+  __shared__ uint32_t red[32 * S];
+  const int tid = threadIdx.x;
+  const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
+  pass_a_task_shifted<LPR>(t, pass_a_task_of(t) * (LPR - 1), lut, red, tid, [&] {
+    fill_lane_packed_lut<512>(lut32, tid);
+    for (int o = tid; o < 32 * S; o += 512) red[o] = 0u;
+    lds_barrier();
+  });
+}
+
+static int launch_shifted(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {
+  const dim3 g(grid), w(512);
+  switch (lpr) {
+    case 16: launch_kernel(pass_a_shifted_kernel<16>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 32: launch_kernel(pass_a_shifted_kernel<32>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 64: launch_kernel(pass_a_shifted_kernel<64>, g, w, 0, s, ev.start, ev.stop, t); break;
+    case 128: launch_kernel(pass_a_shifted_kernel<128>, g, w, 0, s, ev.start, ev.stop, t); break;
+    default:
+      set_error("pass A: shifted variant needs 16..128 lanes per row, got %d", lpr);
       return SK_ERR_INVALID_ARG;
   }
   SK_HIP_TRY(hipGetLastError());
@@ -387,6 +428,7 @@ static int launch_vec(const PassATask& t, int lpr, int variant, int grid, hipStr
     switch (variant) {
       case 1: return launch_packed<8>(t, lpr, grid, s, ev);
       case 5: return launch_phased(t, lpr, grid, s, ev);
+      case 6: return launch_shifted(t, lpr, grid, s, ev);
       case 2: return launch_packed<16>(t, lpr, grid, s, ev);
       case 3:
         launch_kernel(pass_a_side_by_side_kernel<16>, g, dim3(256), 0, s, ev.start, ev.stop, t, lpr);
@@ -412,6 +454,10 @@ static int launch_vec(const PassATask& t, int lpr, int variant, int grid, hipStr
   }
   return launch_shared<VEC>(t, lpr, grid, s, ev);
 }
+
+// Two workgroups fit a CU: with somewhat more than one each, some CUs have twice the
+// others' work (2044 inputs, 2 channels, 314 MB: 68 us with 300, 58 with 600).
+static bool uneven_workgroups(int64_t n) { return n > 256 && n < 440; }
 
 // Units a workgroup of variant 5 takes for a call it suits, else 0. Measured,
 // pass A alone (us, variant 5 against the best other):
@@ -448,8 +494,33 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
   int lanes = 16;
   if (cg >= 16 && units >= (1 << 14))
     while (lanes < (block_len < 128 ? 256 : 512) && 160 * 2 * lanes <= units) lanes *= 2;
+  if (lanes > 32 && uneven_workgroups(units / lanes)) lanes /= 2;
   while (lanes < 256 && lanes * block_len < 2048) lanes *= 2;
   return lanes;
+}
+
+// Units a workgroup of variant 6 takes for a call it suits, else 0. Measured, pass A
+// alone (us, variant 6 against the best other):
+//   20 / 25 (3003 bytes, M = 256, 98 MB), 13 / 19 (2545 bytes, M = 256, 65 MB), 14 / 27
+//     (202 bytes, M = 1000, 26 MB), 8 / 13 (297 bytes, M = 150), 6.6 / 12.5 (129
+//     bytes, M = 256), 77 / 95 (3003 bytes, M = 128, 0.4 GB), 5.1 / 6.7 (602 bytes, M =
+//     128, 4.6 MB); 5.6 / 4.2 below 4 MB (297 bytes, M = 128); rows of under 8 units
+//     66 / 37 (47 bytes, M = 1100);
+//   short blocks only in wide rows and where there are many: 217 / 255 (2545 bytes, M =
+//     100, 1 GB), 57 / 64 (4095 bytes, M = 64, 262 MB), but 19.1 / 19.1 with 65 MB of
+//     the first, 40.6 / 40 (131 bytes, M = 64) and 10 / 8.4 (189 bytes, M = 64);
+//   long blocks in many units stay with variant 5 (split loads, but whole rows a
+//     workgroup): 56 / 52 (2047 bytes, M = 256, 268 MB).
+int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len) {
+  const int64_t cg = (row_bytes + 18) / 16, units = cg * n_blocks;
+  if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0) return 0;
+  if (cg < (block_len < 128 ? 64 : 8) || block_len < 64 || units < (block_len < 128 ? 1 << 17 : 1024) ||
+      units * block_len < 1 << 18 || (block_len >= 192 && units > 60000) ||
+      row_bytes >= (1 << 24) || units >= ((int64_t)1 << 30) || (512 / cg + 2) * block_len * row_bytes >= ((int64_t)1 << 31))
+    return 0;
+  int lanes = 16;
+  while (lanes < 128 && units / (2 * lanes - 1) >= 150) lanes *= 2;
+  return lanes > 16 && uneven_workgroups(units / (lanes - 1)) ? lanes / 2 : lanes;
 }
 
 int pick_vec(const uint8_t* x, int32_t n_inputs) {

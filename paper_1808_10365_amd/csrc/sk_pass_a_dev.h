@@ -126,16 +126,16 @@ __device__ __forceinline__ void phased_load(u32x4 (&q)[PHASE_ROWS], const uint8_
 }
 
 // A batch `left` rows before the block ends: a row past the end reads the last
-// one in its place (phased_mask clears it). Row offsets are 24-bit products:
-// the row index is below PHASE_ROWS RP and G below 2^24.
+// one in its place, from column `past` on (phased_mask clears it). Row offsets are
+// 24-bit products: the row index is below PHASE_ROWS RP and G below 2^24.
 template <int RP>
 __device__ __forceinline__ void phased_load_end(u32x4 (&q)[PHASE_ROWS], const uint8_t* p, int left, uint32_t G, int ph,
-                                                uint32_t col) {
+                                                uint32_t col, uint32_t past) {
   asm("" : "+v"(ph));   // offsets formed here, not kept from the first batch
 #pragma unroll
   for (int u = 0; u < PHASE_ROWS; ++u) {
     const int r = ph + u * RP;
-    q[u] = load16_any(p, __umul24((uint32_t)(r < left ? r : left - 1), G) + col);
+    q[u] = load16_any(p, __umul24((uint32_t)(r < left ? r : left - 1), G) + (r < left ? col : past));
   }
 }
 
@@ -402,7 +402,8 @@ __device__ __forceinline__ void pass_a_task_deferred(const PassATask& t, int64_t
 }
 
 // Stores four columns from column c on (S1 a, S2 b) of block `blk`; they may
-// straddle channels, and the sums' rows need only 4-byte alignment.
+// straddle channels or pass the row's end, and the sums' rows need only 4-byte
+// alignment.
 __device__ __forceinline__ void store_quad(const PassATask& t, int blk, int c, u32x4 a, u32x4 b) {
   typedef u32x4 u32x4_word __attribute__((aligned(4)));
   const int N = t.n_inputs, B = t.n_blocks;
@@ -414,6 +415,7 @@ __device__ __forceinline__ void store_quad(const PassATask& t, int blk, int c, u
   } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
+      if (c + j >= t.row_bytes) break;
       const int64_t e = ((int64_t)f * B + blk) * N + i;
       t.s1[e] = (int32_t)a[j];
       t.s2[e] = (int32_t)b[j];
@@ -425,39 +427,19 @@ __device__ __forceinline__ void store_quad(const PassATask& t, int blk, int c, u
   }
 }
 
-// Accumulator row stride of pass_a_task_phased: S1 of column k of unit g lies at
-// k S + g of `red`, S2 at (16 + k) S + g (32 S words).
-__host__ __device__ constexpr int phased_stride(int lpr) { return lpr + 1; }
-
-// One task of row phases on a 512-lane workgroup (see pass_a_phased_kernel):
-// units u0 .. u0 + LPR - 1 times 512 / LPR phases. prepare() runs with the first
-// rows in flight and leaves the table filled; red holds zeros then, or, with
-// OVER, is cleared here once the table is no longer needed. AGAIN: red holds
-// zeros again at the end (the caller's next barrier makes them seen).
-template <int LPR, bool OVER, bool AGAIN, typename Prepare>
-__device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, const LanePackedLut& lut, uint32_t* red,
-                                                   int tid, Prepare&& prepare) {
-  constexpr int VEC = 16, RP = 512 / LPR;
-  constexpr int S = phased_stride(LPR);
-  constexpr int NV = LPR >= 64 ? 32 : LPR == 32 ? 16 : 8;   // sums a lane adds
-  const int lc = tid % LPR;
-  const int M = t.block_len, ph = tid / LPR;
-  const int G = (int)t.row_bytes, cg = t.col_groups;
-  constexpr int STEP = PHASE_ROWS * RP;   // rows of the block per batch
+// Sums (S1 in v[0 .. 15], S2 in v[16 .. 31]) of rows ph, ph + RP, ... < M of this
+// lane's 16 columns, `col0` from the uniform pointer p on; `past` is where a load
+// past the last row goes. prepare() runs with the first rows in flight and leaves
+// the table filled.
+template <int RP, typename Prepare>
+__device__ __forceinline__ void phased_sums(const uint8_t* p, int G, int M, int ph, uint32_t col0, uint32_t past,
+                                            const LanePackedLut& lut, uint32_t (&v)[32], Prepare&& prepare) {
+  constexpr int VEC = 16, STEP = PHASE_ROWS * RP;   // rows of the block per batch
   const int64_t step_bytes = (int64_t)STEP * G;
-  const int units = t.n_blocks * cg;
-  const int b_first = u0 / cg;            // uniform: the lanes' offsets start at this block
-  uint32_t col0;
-  {
-    const int u = u0 + lc < units ? u0 + lc : units - 1;
-    const int bl = u / cg, c = (u - bl * cg) * VEC;
-    col0 = (uint32_t)(bl - b_first) * (uint32_t)M * (uint32_t)G + (uint32_t)(c < G - VEC ? c : G - VEC);
-  }
-  const uint8_t* p = t.x + (int64_t)b_first * M * G;
   u32x4 qa[PHASE_ROWS], qb[PHASE_ROWS];
-  phased_load_end<RP>(qa, p, M, G, ph, col0);
+  phased_load_end<RP>(qa, p, M, G, ph, col0, past);
   prepare();
-  uint32_t v[2 * VEC], acc[VEC];
+  uint32_t acc[VEC];
 #pragma unroll
   for (int k = 0; k < 2 * VEC; ++k) v[k] = 0;
 #pragma unroll
@@ -491,7 +473,7 @@ __device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, c
   // for the batch before it would cover the fetch too.)
   const auto fetch = [&](u32x4(&q)[PHASE_ROWS], int k) {
     const int at = k * STEP < left ? k * STEP : left - 1;
-    phased_load_end<RP>(q, p + (int64_t)at * G, left - at, G, ph, col0);
+    phased_load_end<RP>(q, p + (int64_t)at * G, left - at, G, ph, col0, past);
   };
   const auto take = [&](u32x4(&q)[PHASE_ROWS], int k) {
     phased_mask<RP>(q, left - k * STEP, ph);
@@ -513,6 +495,45 @@ __device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, c
     }
   }
   unpack();
+}
+
+// Task of this workgroup. by_xcd: consecutive tasks on one XCD (workgroups go round
+// the eight), so a line that two tasks share is fetched into one L2.
+__device__ __forceinline__ int pass_a_task_of(const PassATask& t) {
+  const int id = blockIdx.x, n = gridDim.x;
+  if (!t.by_xcd) return id;
+  const int q = n >> 3, r = n & 7, x = id & 7;
+  return x * q + (x < r ? x : r) + (id >> 3);
+}
+
+// Accumulator row stride of pass_a_task_phased: S1 of column k of unit g lies at
+// k S + g of `red`, S2 at (16 + k) S + g (32 S words).
+__host__ __device__ constexpr int phased_stride(int lpr) { return lpr + 1; }
+
+// One task of row phases on a 512-lane workgroup (see pass_a_phased_kernel):
+// units u0 .. u0 + LPR - 1 times 512 / LPR phases. prepare() runs with the first
+// rows in flight and leaves the table filled; red holds zeros then, or, with
+// OVER, is cleared here once the table is no longer needed. AGAIN: red holds
+// zeros again at the end (the caller's next barrier makes them seen).
+template <int LPR, bool OVER, bool AGAIN, typename Prepare>
+__device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, const LanePackedLut& lut, uint32_t* red,
+                                                   int tid, Prepare&& prepare) {
+  constexpr int VEC = 16, RP = 512 / LPR;
+  constexpr int S = phased_stride(LPR);
+  constexpr int NV = LPR >= 64 ? 32 : LPR == 32 ? 16 : 8;   // sums a lane adds
+  const int lc = tid % LPR;
+  const int M = t.block_len, ph = tid / LPR;
+  const int G = (int)t.row_bytes, cg = t.col_groups;
+  const int units = t.n_blocks * cg;
+  const int b_first = u0 / cg;            // uniform: the lanes' offsets start at this block
+  uint32_t col0;
+  {
+    const int u = u0 + lc < units ? u0 + lc : units - 1;
+    const int bl = u / cg, c = (u - bl * cg) * VEC;
+    col0 = (uint32_t)(bl - b_first) * (uint32_t)M * (uint32_t)G + (uint32_t)(c < G - VEC ? c : G - VEC);
+  }
+  uint32_t v[2 * VEC];
+  phased_sums<RP>(t.x + (int64_t)b_first * M * G, G, M, ph, col0, col0, lut, v, prepare);
   if constexpr (RP == 1) {
     const int u = u0 + lc;
     if (u < units) {
@@ -569,6 +590,86 @@ __device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, c
     if constexpr (AGAIN)
 #pragma unroll
       for (int j = 0; j < 4; ++j) red[(k + j) * S + lg] = red[(VEC + k + j) * S + lg] = 0u;
+  }
+}
+
+// Accumulator row stride of pass_a_task_shifted: column q of unit g at q S + g of
+// `red` (S1; S2 at (16 + q) S + g), 32 S words. 128 units take no pad: two workgroups
+// with table and sums just fill a CU's LDS.
+__host__ __device__ constexpr int shifted_stride(int lpr) { return lpr < 128 ? lpr + 1 : lpr; }
+
+// One task of shifted row phases on a 512-lane workgroup (see
+// pass_a_shifted_kernel): units u0 .. u0 + LPR - 1, of which the last is only read
+// for the columns it has of the one before. prepare() runs with the first rows in
+// flight and ends with a barrier behind which the table is filled and red holds
+// zeros; red holds zeros again at the end (the next barrier makes them seen).
+template <int LPR, typename Prepare>
+__device__ __forceinline__ void pass_a_task_shifted(const PassATask& t, int u0, const LanePackedLut& lut, uint32_t* red,
+                                                    int tid, Prepare&& prepare) {
+  constexpr int VEC = 16, RP = 512 / LPR, S = shifted_stride(LPR);
+  static_assert(RP % 4 == 0, "a lane's rows lie a multiple of 4 bytes apart");
+  // A wavefront takes UW units and 64 / UW phases that are equal mod 4: one shift a unit.
+  constexpr int UW = LPR <= 32 ? 16 : LPR / 2;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lc = (LPR > UW ? (wave >> 2) * UW : 0) + lane % UW;
+  const int ph = (wave & 3) + 4 * (lane / UW + (LPR > UW ? 0 : (wave >> 2) * (64 / UW)));
+  const int M = t.block_len, G = (int)t.row_bytes, cg = t.col_groups;
+  const int units = t.n_blocks * cg;
+  const int b_first = u0 / cg;
+  const bool live = u0 + lc < units;
+  const int u = live ? u0 + lc : units - 1;
+  const int blk = u / cg, c16 = (u - blk * cg) * VEC;
+  // Bytes from an aligned dword to the lane's first row; its rows' windows start
+  // that many columns before the unit, or as far on as the row's end allows.
+  const int s = (int)(((uint32_t)(uintptr_t)t.x + ((uint32_t)blk * (uint32_t)M + (uint32_t)ph) * (uint32_t)G) & 3u);
+  const int end = G - VEC + (-(s + G - VEC) & 3);
+  const int c = c16 - s < end ? c16 - s : end;
+  // Offsets count from 4 bytes before the block: a window may start before its row.
+  const uint32_t at = (uint32_t)(blk - b_first) * (uint32_t)M * (uint32_t)G + 4u;
+  const uint32_t col0 = at + (uint32_t)c, past = at + (uint32_t)(c < G - VEC ? c : G - VEC);
+  uint32_t v[2 * VEC];
+  phased_sums<RP>(t.x + (int64_t)b_first * M * G - 4, G, M, ph, col0, past, lut, v, prepare);
+  // Column c + k goes to place d = c + k - c16 of the unit (below 0: of the unit
+  // before); what lies in another row, or is summed by the unit before, is left out.
+  const int first = lc == 0 ? c16 : c16 - s > 0 ? c16 - s : 0;
+  const int lo = first - c;
+  const int hi = G - c < VEC ? G - c : VEC;
+  const uint32_t n = live && hi > lo ? (uint32_t)(hi - lo) : 0u;
+  const auto add = [&](int val, uint32_t x) {
+    const int k = val & 15, d = c - c16 + k;
+    if ((uint32_t)(k - lo) < n) atomicAdd(red + ((val & 16) + (d & 15)) * S + lc + (d >> 4), x);
+  };
+  if constexpr (UW == 64) {
+#pragma unroll
+    for (int k = 0; k < 2 * VEC; ++k) add(k, v[k]);
+  } else {
+    uint32_t x[VEC];
+#pragma unroll
+    for (int m = 0; m < VEC; ++m) {
+      swap_halves(v[2 * m], v[2 * m + 1]);
+      x[m] = v[2 * m] + v[2 * m + 1];
+    }
+    if constexpr (UW == 32) {
+#pragma unroll
+      for (int m = 0; m < VEC; ++m) add(2 * m + (lane >> 5), x[m]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < VEC / 2; ++q) {
+        swap_rows(x[2 * q], x[2 * q + 1]);
+        add(wave_value_of_row(q, lane >> 4), x[2 * q] + x[2 * q + 1]);
+      }
+    }
+  }
+  lds_barrier();
+  for (int o = tid; o < 4 * LPR; o += 512) {
+    const int lg = o >> 2, k = (o & 3) * 4, w = u0 + lg;
+    uint32_t* r1 = red + k * S + lg;
+    uint32_t* r2 = r1 + VEC * S;
+    if (lg < LPR - 1 && w < units) {
+      const int b = w / cg, col = (w - b * cg) * VEC + k;
+      if (col < G)
+        store_quad(t, b, col, u32x4{r1[0], r1[S], r1[2 * S], r1[3 * S]}, u32x4{r2[0], r2[S], r2[2 * S], r2[3 * S]});
+    }
   }
 }
 

