@@ -31,7 +31,7 @@ struct BatchProb {
   int32_t units;               // row-phase form: 16-byte units per task (16, 32, 64 or 512); 0: the form above
   int32_t window, hist_cap, chunk, n_chunks, estimator;
   int32_t waves;               // combine waves per chunk (inputs / 256, at most 8)
-  int32_t scan_waves;          // scan waves per 64-input slice (power of two, at most 8)
+  int32_t scan_waves;          // scan waves per slice of SCAN_INPUTS inputs (power of two, at most 8)
   int32_t wide_sums;           // 1: the combine's R1/R2 sums need 64 bits
   int32_t steps;               // chunks a combine wavefront walks (the stepped combine), or 0: combine_body
   double k_sigma, expect_offset, sigma_override;
@@ -86,6 +86,7 @@ __device__ __forceinline__ PassBArgs make_args(const BatchProb& P, const BatchSt
   a.hist_next_len = (int32_t)(total < P.hist_cap ? total : P.hist_cap);
   a.chunk = P.chunk;
   a.n_chunks = P.n_chunks;
+  a.steps = P.steps ? P.steps : 1;
   a.vec = 4;
   a.estimator = P.estimator;
   a.k_sigma = P.k_sigma;
@@ -213,8 +214,8 @@ __global__ __launch_bounds__(512, 4) void batch_pass_a_phased_kernel(const Batch
 // sixteen wavefronts, so more rows are in flight.
 constexpr int BATCH_SCAN_WAVES = 8;
 
-// Scan workgroups of the whole batch: (problem, channel, group of 64-input
-// slices), BATCH_SCAN_WAVES wavefronts, Ws per slice (the problem's
+// Scan workgroups of the whole batch: (problem, channel, group of slices of
+// SCAN_INPUTS inputs), BATCH_SCAN_WAVES wavefronts, Ws per slice (the problem's
 // scan_waves) and BATCH_SCAN_WAVES / Ws slices per workgroup. The chunk
 // length is read at run time (scan_body_rows); the prefix sums are exact
 // integers, so they equal the single-plan kernel's.
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(64 * BATCH_SCAN_WAVES) void batch_scan_kernel(const
   if (lt >= P.sc_count) return;                       // whole workgroup
   const PassBArgs a = make_args(P, st[p]);
   const int Ws = P.scan_waves, spw = BATCH_SCAN_WAVES / Ws;
-  const int slices = (a.n_inputs + 63) / 64;
+  const int slices = (a.n_inputs + SCAN_INPUTS - 1) / SCAN_INPUTS;
   const int groups = (slices + spw - 1) / spw;
   const int f = (int)(lt / groups);
   const int w = wave_id(), sub = w / Ws;
@@ -542,7 +543,7 @@ static Layout layout(std::vector<BatchProb>& tab) {
     P.a_begin = P.units ? l.ta : (l.ta + 1) & ~(int64_t)1;
     l.ta = P.a_begin + P.a.n_tasks * (!P.units && P.lpr == 512 ? 2 : 1);
     P.sc_begin = l.tsc;
-    const int slices = (P.a.n_inputs + 63) / 64, spw = BATCH_SCAN_WAVES / P.scan_waves;
+    const int slices = (P.a.n_inputs + SCAN_INPUTS - 1) / SCAN_INPUTS, spw = BATCH_SCAN_WAVES / P.scan_waves;
     P.sc_count = (P.a.n_blocks > 0 && pass_b_needs_scan(P.window, P.chunk, P.a.n_blocks))
                      ? F * ((slices + spw - 1) / spw) : 0;
     l.tsc += P.sc_count;

@@ -32,11 +32,11 @@ __global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void combine_kernel(PassBAr
   combine_body<V, R, RI, OFF32>(a, blockIdx.x, blockIdx.y, wave_id(), blockDim.x >> 6, sh);
 }
 
-// One run of `steps` chunks per workgroup.
+// One run of a.steps chunks per workgroup.
 template <int R, typename RI, bool OFF32>
-__global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void step_kernel(PassBArgs a, int steps) {
+__global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void step_kernel(PassBArgs a) {
   __shared__ StepShared sh;
-  const int f = blockIdx.y, k0 = (int)blockIdx.x * steps, W = blockDim.x >> 6;
+  const int steps = a.steps, f = blockIdx.y, k0 = (int)blockIdx.x * steps, W = blockDim.x >> 6;
   step_body<R, RI, OFF32>(a, k0, steps, f, wave_id(), wave_id(), sh);
   __syncthreads();
   const int j = threadIdx.x, b = k0 * R + j;
@@ -44,10 +44,10 @@ __global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void step_kernel(PassBArgs 
 }
 
 template <int R, bool OFF32>
-static void launch_step_r(const PassBArgs& a, bool fit32, int steps, dim3 grid, dim3 wg, hipStream_t s, hipEvent_t e0,
+static void launch_step_r(const PassBArgs& a, bool fit32, dim3 grid, dim3 wg, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1) {
-  if (fit32) launch_kernel(step_kernel<R, uint32_t, OFF32>, grid, wg, 0, s, e0, e1, a, steps);
-  else launch_kernel(step_kernel<R, uint64_t, OFF32>, grid, wg, 0, s, e0, e1, a, steps);
+  if (fit32) launch_kernel(step_kernel<R, uint32_t, OFF32>, grid, wg, 0, s, e0, e1, a);
+  else launch_kernel(step_kernel<R, uint64_t, OFF32>, grid, wg, 0, s, e0, e1, a);
 }
 
 template <int R>
@@ -55,10 +55,9 @@ static int launch_step(const PassBArgs& a, hipStream_t s, hipEvent_t e0, hipEven
   const bool fit32 = combine_sums_fit_32(a.n_inputs, 4, a.block_len);
   const bool off32 = combine_offsets_fit_32(a.n_inputs, a.n_blocks, a.n_chunks, a.hist_cap);
   const int W = combine_waves(a.n_inputs, 4);
-  const int steps = step_chunks(R, (int64_t)a.n_chunks * a.n_channels * W);
-  const dim3 grid((a.n_chunks + steps - 1) / steps, a.n_channels), wg(64 * W);
-  if (off32) launch_step_r<R, true>(a, fit32, steps, grid, wg, s, e0, e1);
-  else launch_step_r<R, false>(a, fit32, steps, grid, wg, s, e0, e1);
+  const dim3 grid((a.n_chunks + a.steps - 1) / a.steps, a.n_channels), wg(64 * W);
+  if (off32) launch_step_r<R, true>(a, fit32, grid, wg, s, e0, e1);
+  else launch_step_r<R, false>(a, fit32, grid, wg, s, e0, e1);
   SK_HIP_TRY(hipGetLastError());
   return SK_OK;
 }
@@ -416,7 +415,8 @@ static int launch_window(const PassBArgs& a, hipStream_t s, PassEvents ev) {
   return SK_OK;
 }
 
-int launch_pass_b(const PassBArgs& a, hipStream_t s, PassEvents ev) {
+int launch_pass_b(const PassBArgs& args, hipStream_t s, PassEvents ev) {
+  PassBArgs a = args;
   if (a.n_blocks <= 0) return SK_OK;
   if (a.direct) {
     switch (a.chunk) {
@@ -429,6 +429,8 @@ int launch_pass_b(const PassBArgs& a, hipStream_t s, PassEvents ev) {
   }
   const int F = a.n_channels;
   hipEvent_t start = ev.start;
+  const bool stepped = steps_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks);
+  if (stepped) a.steps = step_chunks(a.chunk, (int64_t)a.n_chunks * F * combine_waves(a.n_inputs, 4));
   if (pass_b_needs_scan(a.window, a.chunk, a.n_blocks)) {
     // Enough wavefronts for the chunks, or for the history rows a call
     // shorter than the window moves.
@@ -445,7 +447,7 @@ int launch_pass_b(const PassBArgs& a, hipStream_t s, PassEvents ev) {
     SK_HIP_TRY(hipGetLastError());
     start = nullptr;
   }
-  if (steps_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks)) {
+  if (stepped) {
     switch (a.chunk) {
       case 1: return launch_step<1>(a, s, start, ev.stop);
       case 2: return launch_step<2>(a, s, start, ev.stop);

@@ -192,6 +192,14 @@ __host__ __device__ __forceinline__ int64_t shift_groups(int64_t hist_next_len, 
   return rows > 0 ? (rows + SHIFT_ROWS - 1) / SHIFT_ROWS : 0;
 }
 
+// Whether prefix row k is read: of the stepped combine's runs (a.steps chunks each)
+// only their first rows and the ones their windows start at, and the call's total;
+// every row at one chunk per run.
+__device__ __forceinline__ bool prefix_row_read(const PassBArgs& a, int k, int window_chunks) {
+  const int m = a.steps - 1;
+  return (k & m) == 0 || ((k + window_chunks) & m) == 0 || k == a.n_chunks;
+}
+
 // Chunks a scan lane holds per round: 64 rows of S1 in flight at most.
 template <int R>
 constexpr int scan_chunks_per_lane() { return 64 / R; }
@@ -249,7 +257,7 @@ __device__ __forceinline__ void scan_body(const PassBArgs& a, int f, int slice, 
     if (active) {
 #pragma unroll
       for (int j = 0; j < C; ++j)
-        if (k0 + j < nk) pc[(int64_t)(k0 + j + 1) * rowN] = off + cs[j];
+        if (k0 + j < nk && prefix_row_read(a, k0 + j + 1, a.window / R)) pc[(int64_t)(k0 + j + 1) * rowN] = off + cs[j];
     }
     __syncthreads();
   }
@@ -262,7 +270,12 @@ __device__ __forceinline__ void scan_body(const PassBArgs& a, int f, int slice, 
 // chunk end, so the registers do not depend on the chunk length. Rounds are
 // SCAN_ROWS W units; R (a power of two) divides SCAN_ROWS. The prefix values
 // are exact integers mod 2^32, equal to scan_body's.
-constexpr int SCAN_ROWS = 32;
+constexpr int SCAN_ROWS = 32;   // two runs of the stepped combine
+
+// Inputs per slice: a wavefront's lanes are SCAN_PARTS walkers, each of its own rows.
+// Two: twice the workgroups and half the rounds for loads of whole 128-byte lines (36.9
+// us with one, 30.5 with two, 37.5 with four walkers, before the plain rounds below).
+constexpr int SCAN_PARTS = 2, SCAN_INPUTS = 64 / SCAN_PARTS;
 
 __device__ __forceinline__ void scan_body_rows(const PassBArgs& a, int f, int slice, int w, int W, uint32_t* lds) {
   // Units: the chunk sums from pass A when the call has them (every unit
@@ -270,39 +283,68 @@ __device__ __forceinline__ void scan_body_rows(const PassBArgs& a, int f, int sl
   const int nk = a.n_chunks, B = a.n_blocks;
   const int U = a.cs ? nk : B;
   const int R = a.cs ? 1 : a.chunk, lgR = __builtin_ctz((unsigned)R);
-  const int lane = threadIdx.x & 63;
-  const int i = slice * 64 + lane;
+  const int window_chunks = a.window >> __builtin_ctz((unsigned)a.chunk);
+  const int lane = threadIdx.x & (SCAN_INPUTS - 1);
+  w = w * SCAN_PARTS + (int)(threadIdx.x & 63) / SCAN_INPUTS;
+  W *= SCAN_PARTS;
+  const int i = slice * SCAN_INPUTS + lane;
   const bool active = i < a.n_inputs;
   const int64_t rowN = a.n_inputs;
   uint32_t* pc = a.pc + (int64_t)f * (nk + 1) * rowN + i;
   if (w == 0 && active) pc[0] = 0u;
   const int32_t* src = a.cs ? a.cs + (int64_t)f * nk * rowN + i : a.s1 + (int64_t)f * B * rowN + i;
   uint32_t carry = 0;
+  // Rounds wholly inside the call where only every 16th row's sum is read: no row
+  // bounds and two stores a lane (bound by its instructions otherwise: 30.5 -> 21 us for
+  // 71 MB of S1 in 12 problems). Offsets of 32 bits from the round's first row.
+  const bool by_16 = a.chunk * a.steps == 16 && (window_chunks & (a.steps - 1)) == 0 && !a.cs &&
+                     rowN <= 1 << 20;
+  const uint32_t lane_off = (uint32_t)(w * SCAN_ROWS) * (uint32_t)rowN * 4u + (uint32_t)(active ? i : a.n_inputs - 1) * 4u;
+  const uint8_t* chan = reinterpret_cast<const uint8_t*>(a.s1 + (int64_t)f * B * rowN);
   for (int base = 0; base < U; base += SCAN_ROWS * W) {
     const int r0 = base + w * SCAN_ROWS;
     uint32_t x[SCAN_ROWS];
-    const int32_t* p = src + (int64_t)r0 * rowN;
+    const bool plain = by_16 && base + SCAN_ROWS * W <= U;
+    if (plain) {
+      const uint8_t* row = chan + (int64_t)base * rowN * 4;
 #pragma unroll
-    for (int r = 0; r < SCAN_ROWS; ++r) x[r] = (active && r0 + r < U) ? (uint32_t)p[(int64_t)r * rowN] : 0u;
-    uint32_t tot = 0;
+      for (int r = 0; r < SCAN_ROWS; ++r) {
+        x[r] = *reinterpret_cast<const uint32_t*>(row + lane_off);
+        row += rowN * 4;
+      }
+    } else {
+      const int32_t* p = src + (int64_t)r0 * rowN;
 #pragma unroll
-    for (int r = 0; r < SCAN_ROWS; ++r) tot += x[r];
-    lds[w * 64 + lane] = tot;
+      for (int r = 0; r < SCAN_ROWS; ++r) x[r] = (active && r0 + r < U) ? (uint32_t)p[(int64_t)r * rowN] : 0u;
+    }
+    uint32_t half = 0, tot = 0;
+#pragma unroll
+    for (int r = 0; r < SCAN_ROWS / 2; ++r) {
+      half += x[r];
+      tot += x[SCAN_ROWS / 2 + r];
+    }
+    tot += half;
+    lds[w * SCAN_INPUTS + lane] = tot;
     __syncthreads();
     uint32_t off = carry, all = carry;
     for (int q = 0; q < W; ++q) {
-      const uint32_t t = lds[q * 64 + lane];
+      const uint32_t t = lds[q * SCAN_INPUTS + lane];
       if (q < w) off += t;
       all += t;
     }
     carry = all;
-    if (active) {
+    if (active && plain) {
+      pc[(int64_t)((r0 + 16) >> lgR) * rowN] = off + half;
+      pc[(int64_t)((r0 + 32) >> lgR) * rowN] = off + tot;
+    } else if (active) {
 #pragma unroll
       for (int r = 0; r < SCAN_ROWS; ++r) {
         off += x[r];
         const int row = r0 + r;
         // Chunk c ends at unit c R + R - 1, or at U - 1 for a short last chunk.
-        if (row < U && (((row + 1) & (R - 1)) == 0 || row == U - 1)) pc[(int64_t)((row + R) >> lgR) * rowN] = off;
+        const int k = (row + R) >> lgR;
+        if (row < U && (((row + 1) & (R - 1)) == 0 || row == U - 1) && prefix_row_read(a, k, window_chunks))
+          pc[(int64_t)k * rowN] = off;
       }
     }
     __syncthreads();
@@ -315,7 +357,7 @@ __device__ __forceinline__ void scan_body_rows(const PassBArgs& a, int f, int sl
 // workgroup's wavefronts, so slices tile it).
 __host__ __device__ __forceinline__ int scan_rows_waves(int64_t n_blocks, int max_waves) {
   int W = 1;
-  while (W < max_waves && (int64_t)W * SCAN_ROWS < n_blocks) W *= 2;
+  while (W < max_waves && (int64_t)W * SCAN_PARTS * SCAN_ROWS < n_blocks) W *= 2;
   return W;
 }
 
