@@ -93,7 +93,7 @@ int sk_read_probe(const uint8_t* d_x, int64_t bytes, int32_t workgroups, uint32_
 
 /* Result of sk_plan_autotune: the settings kept and their times. */
 typedef struct {
-  int32_t pass_a_variant;      /* 0..4, as SK_PASS_A_*; 5: row phases over 16-byte units (library choice) */
+  int32_t pass_a_variant;      /* 0..4, as SK_PASS_A_*; 5, 6: row phases over 16-byte units (library choice) */
   int32_t pass_a_lanes;        /* lanes per row */
   int32_t pass_a_blocks;       /* consecutive blocks per task */
   int32_t pass_a_chunk_sums;   /* 1: pass A writes the chunk sums the scan reads */

@@ -47,7 +47,7 @@ struct BatchProb {
   float* sk_i;
   float* significance;
   // Task ranges of each kernel over the whole batch: pass A tasks, scan
-  // workgroups (channel, group of 64-input slices), combine workgroups
+  // workgroups (channel, group of SCAN_INPUTS-input slices), combine workgroups
   // (channel, group of chunks; counted within the problem's combine class).
   int64_t a_begin, sc_begin, sc_count, cb_begin, cb_count;
 };

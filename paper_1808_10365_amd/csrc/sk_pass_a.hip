@@ -22,6 +22,8 @@
 //     with every block's sums held in registers and stored at the task's end.
 //   5 packed table, 512-lane workgroups of row phases over runs of 16-byte units,
 //     any N and alignment (library choice only).
+//   6 the same from aligned dwords, for rows off 4-byte boundaries (library choice
+//     only).
 #include <hip/hip_runtime.h>
 
 #include "sk_internal.h"

@@ -28,6 +28,8 @@
 //            fixed tree, wavefronts joined in LDS in a fixed order, then the
 //            estimator and flags of the chunk's blocks. It also writes the
 //            next call's history suffix sums for its blocks.
+//   step     the combine for calls with prefix sums, 4 inputs per lane and at most
+//            2048 inputs: a wavefront walks a run of up to 16 blocks (below).
 // Every load of a wavefront is issued before any of them is used, so a
 // combine wavefront costs one memory round trip.
 #pragma once
@@ -268,8 +270,8 @@ __device__ __forceinline__ void scan_body(const PassBArgs& a, int f, int slice, 
 // kernel's problems differ in it): each lane holds SCAN_ROWS units (rows of
 // S1, or pass A's chunk sums) per round and writes its running sum at every
 // chunk end, so the registers do not depend on the chunk length. Rounds are
-// SCAN_ROWS W units; R (a power of two) divides SCAN_ROWS. The prefix values
-// are exact integers mod 2^32, equal to scan_body's.
+// SCAN_ROWS times the walkers; R (a power of two) divides SCAN_ROWS. The prefix
+// values are exact integers mod 2^32, equal to scan_body's.
 constexpr int SCAN_ROWS = 32;   // two runs of the stepped combine
 
 // Inputs per slice: a wavefront's lanes are SCAN_PARTS walkers, each of its own rows.

@@ -4,7 +4,7 @@ Reads the SQLite database rocprofv3 writes (``-d DIR -o run``) and prints:
 
 * ``trace DIR``: per-kernel dispatch count and duration (average, median,
   min, max, total) from the kernel trace; with ``--calls`` also the
-  batched form's graph calls (a ``batch_pass_a_kernel`` dispatch followed
+  batched form's graph calls (a ``batch_pass_a_kernel`` or ``batch_pass_a_phased_kernel`` dispatch followed
   by the batched scan / combine / state kernels up to the next pass A),
   grouped by their kernel sequence. The autotuner's and the pass A timer's
   launches each follow a device fill (the queue counter cleared with a
@@ -29,6 +29,9 @@ import re
 import sqlite3
 import statistics
 import sys
+
+
+_PASS_A = re.compile("batch_pass_a_(phased_)?kernel")
 
 
 def _db(d: str) -> sqlite3.Connection:
@@ -67,11 +70,11 @@ def trace(d: str, calls: bool = False, include: str = "") -> str:
         i = 0
         while i < len(rows):
             trial = i > 0 and "fillBuffer" in rows[i - 1][0]
-            if "batch_pass_a_kernel" in rows[i][0] and not trial and i + 1 < len(rows) and \
-                    ("batch_scan_kernel" in rows[i + 1][0] or "batch_combine_kernel" in rows[i + 1][0]):
+            if _PASS_A.search(rows[i][0]) and not trial and i + 1 < len(rows) and \
+                    any(k in rows[i + 1][0] for k in ("batch_scan_kernel", "batch_combine_kernel", "batch_step_kernel")):
                 j = i + 1
                 while j < len(rows) and rows[j][0].lstrip("void ").startswith("sk::batch_") and \
-                        "batch_pass_a_kernel" not in rows[j][0]:
+                        not _PASS_A.search(rows[j][0]):
                     j += 1
                 seqs.append(rows[i:j])
                 i = j
