@@ -217,7 +217,7 @@ constexpr int BATCH_SCAN_WAVES = 8;
 // Scan workgroups of the whole batch: (problem, channel, group of slices of
 // SCAN_INPUTS inputs), BATCH_SCAN_WAVES wavefronts, Ws per slice (the problem's
 // scan_waves) and BATCH_SCAN_WAVES / Ws slices per workgroup. The chunk
-// length is read at run time (scan_body_rows); the prefix sums are exact
+// length is read at run time (scan_body); the prefix sums are exact
 // integers, so they equal the single-plan kernel's.
 __global__ __launch_bounds__(64 * BATCH_SCAN_WAVES) void batch_scan_kernel(const BatchProb* __restrict__ probs,
                                                                         const BatchState* __restrict__ st, int n) {
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(64 * BATCH_SCAN_WAVES) void batch_scan_kernel(const
   const int f = (int)(lt / groups);
   const int w = wave_id(), sub = w / Ws;
   const int slice = (int)(lt % groups) * spw + sub;   // >= slices: every lane idle, barriers kept
-  scan_body_rows(a, f, slice, w % Ws, Ws, lds + sub * Ws * 64);
+  scan_body(a, f, slice, w % Ws, Ws, lds + sub * Ws * 64);
 }
 
 // What a call does after its last kernel: advance every problem's history

@@ -20,10 +20,9 @@
 
 namespace sk {
 
-template <int R>
 __global__ __launch_bounds__(64 * SCAN_MAX_WAVES) void scan_kernel(PassBArgs a) {
   __shared__ uint32_t lds[SCAN_MAX_WAVES * 64];
-  scan_body<R>(a, blockIdx.y, blockIdx.x, wave_id(), blockDim.x >> 6, lds);
+  scan_body(a, blockIdx.y, blockIdx.x, wave_id(), blockDim.x >> 6, lds);
 }
 
 template <int V, int R, typename RI, bool OFF32>
@@ -437,15 +436,10 @@ int launch_pass_b(const PassBArgs& args, hipStream_t s, PassEvents ev) {
     // Enough wavefronts for the chunks, or for the history rows a call
     // shorter than the window moves.
     const int64_t sg = shift_groups(a.hist_next_len, a.n_blocks);
-    const dim3 grid((a.n_inputs + 63) / 64, F), wg(64 * scan_waves(sg > a.n_chunks ? (int)sg : a.n_chunks));
-    switch (a.chunk) {
-      case 1: launch_kernel(scan_kernel<1>, grid, wg, 0, s, start, nullptr, a); break;
-      case 2: launch_kernel(scan_kernel<2>, grid, wg, 0, s, start, nullptr, a); break;
-      case 4: launch_kernel(scan_kernel<4>, grid, wg, 0, s, start, nullptr, a); break;
-      default:
-        set_error("pass B: chunk length %d is not 1, 2 or 4", a.chunk);
-        return SK_ERR_INVALID_ARG;
-    }
+    int W = scan_rows_waves(a.cs ? a.n_chunks : a.n_blocks, SCAN_MAX_WAVES);
+    while (W < SCAN_MAX_WAVES && W * SCAN_PARTS < sg) W *= 2;
+    const dim3 grid((a.n_inputs + SCAN_INPUTS - 1) / SCAN_INPUTS, F), wg(64 * W);
+    launch_kernel(scan_kernel, grid, wg, 0, s, start, nullptr, a);
     SK_HIP_TRY(hipGetLastError());
     start = nullptr;
   }

@@ -202,76 +202,16 @@ __device__ __forceinline__ bool prefix_row_read(const PassBArgs& a, int k, int w
   return (k & m) == 0 || ((k + window_chunks) & m) == 0 || k == a.n_chunks;
 }
 
-// Chunks a scan lane holds per round: 64 rows of S1 in flight at most.
-template <int R>
-constexpr int scan_chunks_per_lane() { return 64 / R; }
-
-// One workgroup of W wavefronts: channel f, inputs [64 slice, 64 slice + 64),
-// one input per lane. Wavefront w takes chunks [k0, k0 + C) of each round of
-// C W chunks (C = 64 / R); the rounds carry the running prefix. S1 of a
-// chunk is the pass A chunk sum when the call has them (a.cs), else the sum
-// of its R rows. lds: W * 64 words.
-template <int R>
-__device__ __forceinline__ void scan_body(const PassBArgs& a, int f, int slice, int w, int W, uint32_t* lds) {
-  constexpr int C = scan_chunks_per_lane<R>();
-  const int lane = threadIdx.x & 63;
-  const int i = slice * 64 + lane;
-  const bool active = i < a.n_inputs;
-  const int nk = a.n_chunks, B = a.n_blocks;
-  const int64_t rowN = a.n_inputs;
-  uint32_t* pc = a.pc + (int64_t)f * (nk + 1) * rowN + i;
-  if (w == 0 && active) pc[0] = 0u;
-  uint32_t carry = 0;   // prefix before this round, for this lane's input
-  for (int base = 0; base < nk; base += C * W) {
-    const int k0 = base + w * C;
-    uint32_t cs[C];
-    if (a.cs) {
-      const int32_t* p = a.cs + ((int64_t)f * nk + k0) * rowN + i;
-#pragma unroll
-      for (int j = 0; j < C; ++j) cs[j] = (active && k0 + j < nk) ? (uint32_t)p[(int64_t)j * rowN] : 0u;
-    } else {
-      uint32_t x[C][R];
-      const int32_t* p = a.s1 + ((int64_t)f * B + (int64_t)k0 * R) * rowN + i;
-#pragma unroll
-      for (int j = 0; j < C; ++j)
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          x[j][r] = (active && (k0 + j) * R + r < B) ? (uint32_t)p[(int64_t)(j * R + r) * rowN] : 0u;
-#pragma unroll
-      for (int j = 0; j < C; ++j) {
-        uint32_t t = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) t += x[j][r];
-        cs[j] = t;
-      }
-    }
-#pragma unroll
-    for (int j = 1; j < C; ++j) cs[j] += cs[j - 1];
-    lds[w * 64 + lane] = cs[C - 1];
-    __syncthreads();
-    uint32_t off = carry, all = carry;
-    for (int q = 0; q < W; ++q) {
-      const uint32_t t = lds[q * 64 + lane];
-      if (q < w) off += t;
-      all += t;
-    }
-    carry = all;
-    if (active) {
-#pragma unroll
-      for (int j = 0; j < C; ++j)
-        if (k0 + j < nk && prefix_row_read(a, k0 + j + 1, a.window / R)) pc[(int64_t)(k0 + j + 1) * rowN] = off + cs[j];
-    }
-    __syncthreads();
-  }
-  shift_history(a, f, i, active, carry, w, W);
-}
-
-// The same scan for a chunk length known only at run time (the batched
-// kernel's problems differ in it): each lane holds SCAN_ROWS units (rows of
-// S1, or pass A's chunk sums) per round and writes its running sum at every
-// chunk end, so the registers do not depend on the chunk length. Rounds are
-// SCAN_ROWS times the walkers; R (a power of two) divides SCAN_ROWS. The prefix
-// values are exact integers mod 2^32, equal to scan_body's.
+// One workgroup of W wavefronts: channel f, slice `slice` of SCAN_INPUTS inputs, one
+// input per lane. Each walker holds SCAN_ROWS units (rows of S1, or pass A's chunk
+// sums) per round of SCAN_ROWS times the walkers and writes its running sum at every
+// chunk end that is read; the rounds carry the running prefix. The chunk length is
+// read at run time (the batched kernel's problems differ in it) and divides
+// SCAN_ROWS, so the registers do not depend on it. lds: W * 64 words.
+//
+// Bound by its rounds' round trips: 1024 inputs, 2000 blocks, L = 1024: pass B 40.4 ->
+// 27.9 us against one walker of 64 inputs and 64 rows per wavefront; 2048 inputs, 4
+// channels, 1024 blocks by chunk sums 28.4 -> 27.7.
 constexpr int SCAN_ROWS = 32;   // two runs of the stepped combine
 
 // Inputs per slice: a wavefront's lanes are SCAN_PARTS walkers, each of its own rows.
@@ -279,7 +219,7 @@ constexpr int SCAN_ROWS = 32;   // two runs of the stepped combine
 // us with one, 30.5 with two, 37.5 with four walkers, before the plain rounds below).
 constexpr int SCAN_PARTS = 2, SCAN_INPUTS = 64 / SCAN_PARTS;
 
-__device__ __forceinline__ void scan_body_rows(const PassBArgs& a, int f, int slice, int w, int W, uint32_t* lds) {
+__device__ __forceinline__ void scan_body(const PassBArgs& a, int f, int slice, int w, int W, uint32_t* lds) {
   // Units: the chunk sums from pass A when the call has them (every unit
   // ends a chunk), else the rows of S1 (a chunk ends every R rows).
   const int nk = a.n_chunks, B = a.n_blocks;
@@ -354,7 +294,7 @@ __device__ __forceinline__ void scan_body_rows(const PassBArgs& a, int f, int sl
   shift_history(a, f, i, active, carry, w, W);
 }
 
-// Waves per slice of the batched scan: a power of two covering the call's
+// Waves per slice of a scan: a power of two covering the call's
 // rows in SCAN_ROWS-row lanes, at most max_waves (a power of two: the
 // workgroup's wavefronts, so slices tile it).
 __host__ __device__ __forceinline__ int scan_rows_waves(int64_t n_blocks, int max_waves) {
@@ -907,11 +847,6 @@ __device__ __forceinline__ void step_finish(const PassBArgs& a, int f, int b, in
 __host__ __device__ __forceinline__ int combine_waves(int n_inputs, int vec) {
   const int g = (n_inputs + 64 * vec - 1) / (64 * vec);
   return g < COMBINE_MAX_WAVES ? g : COMBINE_MAX_WAVES;
-}
-
-// Waves of a scan workgroup for nk chunks.
-__host__ __device__ __forceinline__ int scan_waves(int n_chunks) {
-  return n_chunks < SCAN_MAX_WAVES ? (n_chunks > 0 ? n_chunks : 1) : SCAN_MAX_WAVES;
 }
 
 // Whether every per-channel array of a call (S1, S2, prefix sums, history)
