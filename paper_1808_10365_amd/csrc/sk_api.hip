@@ -306,8 +306,8 @@ int sk_plan_set_pass_b_tile(sk_plan_t p, int32_t chunk, int32_t vec) {
     set_error("pass B tile: chunk must be 0, 1, 2 or 4 and inputs per lane 0, 1 or 4");
     return SK_ERR_INVALID_ARG;
   }
-  const int32_t R = chunk ? chunk
-                          : pass_b_plan_chunk(p->d.n_inputs, p->d.n_channels, p->n_blocks, p->d.norm_window_blocks);
+  const int32_t N = p->d.n_inputs, F = p->d.n_channels, L = p->d.norm_window_blocks;
+  const int32_t R = chunk ? chunk : vec == 1 ? pass_b_chunk(N, F, p->n_blocks, L) : pass_b_plan_chunk(N, F, p->n_blocks, L);
   if (p->d.norm_window_blocks >= 2) {
     const size_t need = pass_b_prefix_bytes(p->d.n_inputs, p->d.n_channels, p->n_blocks, R);
     if (need > p->pc_bytes) {

@@ -103,8 +103,8 @@ PassAConfig default_pass_a_config(int vec, int64_t row_bytes, int64_t n_blocks, 
 // ---------------------------------------------------------------- pass B
 // Normaliser window, array combine, estimator and flags (Eq. discreteMean,
 // normedSum1/2, avgSK, final; Sec. 3.2). Kernels and positions: see
-// sk_pass_b_dev.h. A call runs the scan kernel (L >= 2), then the combine
-// kernel.
+// sk_pass_b_dev.h. A call runs the window kernel, or the scan kernel (L >= 2) and
+// then the combine or the stepped combine.
 struct PassBArgs {
   const int32_t* s1;      // [F][B][N]
   const int32_t* s2;      // [F][B][N]
@@ -142,7 +142,7 @@ bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32
 size_t pass_b_direct_part_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
 size_t pass_b_direct_done_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
 // Library choice of R: blocks per wavefront of the window kernel where a call
-// takes it, else as pass_b_chunk.
+// takes it, 1 for the stepped combine's runs of 16 blocks, else as pass_b_chunk.
 int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window);
 // Device bytes of the prefix buffer: F (ceil(B / R) + 1) N uint32.
 size_t pass_b_prefix_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t chunk);

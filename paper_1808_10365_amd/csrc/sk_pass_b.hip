@@ -512,8 +512,15 @@ int pass_b_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t
 
 int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window) {
   const int R = window_chunk(n_inputs, n_channels, n_blocks, window);
-  return pass_b_direct(n_inputs, n_channels, n_blocks, window, R, pass_b_vec(n_inputs))
-             ? R : pass_b_chunk(n_inputs, n_channels, n_blocks, window);
+  if (pass_b_direct(n_inputs, n_channels, n_blocks, window, R, pass_b_vec(n_inputs))) return R;
+  // Runs of 16 blocks cost least at one block a step: fewer registers, and pass A then
+  // writes no chunk sums for the scan (whole calls, R = 1 against 4, us: 363.9 / 366.4
+  // CHIME M = 256, 206.4 / 211.1 M = 128, 134.8 / 138.4 1024 inputs, 8 channels, M = 64,
+  // 249.3 / 251.9 2048 inputs, 4096 blocks, L = 500; 366.8 / 366.6 1024 inputs, L = 300).
+  if (steps_suit(n_inputs, window, pass_b_vec(n_inputs), 1, n_blocks) &&
+      step_chunks(1, n_blocks * n_channels * combine_waves(n_inputs, 4)) > 1)
+    return 1;
+  return pass_b_chunk(n_inputs, n_channels, n_blocks, window);
 }
 
 size_t pass_b_prefix_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t chunk) {
