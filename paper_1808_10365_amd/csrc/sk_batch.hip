@@ -426,8 +426,10 @@ struct Pick {
 };
 
 // What a batch's calls run: the classes' picks, or pass A in row phases with one
-// chunk length for every problem (so one combine launch).
-enum BatchForm { FORM_PICKS = 0, FORM_PHASED_4 = 1, FORM_PHASED_2 = 2, N_FORMS = 3 };
+// chunk length for every problem of the stepped combine (so one launch for them): 1,
+// the least of 1, 2 and 4 in every batch tried (12 problems, 2.2 GB: 441 / 446 / 449 us
+// a call; six of M = 64, 0.5 GB: 151 / 152 / 157; five, 79 MB: 49 each).
+enum BatchForm { FORM_PICKS = 0, FORM_PHASED = 1, N_FORMS = 2 };
 
 struct sk_batch_s {
   int n = 0;
@@ -858,6 +860,10 @@ static int64_t batch_bytes(const sk_batch_s* b) {
 // Sets every problem up for a form and orders the queue.
 static void apply_form(sk_batch_s* b, int form) {
   const int64_t total = batch_bytes(b);
+  const auto stepped = [](const BatchProb& P) { return steps_suit(P.a.n_inputs, P.window, 4, 1, P.a.n_blocks); };
+  int64_t waves = 0;   // of the other problems' combine, at 4 blocks per chunk
+  for (const BatchProb& P : b->host)
+    if (!stepped(P)) waves += (int64_t)(P.a.row_bytes / P.a.n_inputs) * P.waves * ((P.a.n_blocks + 3) / 4);
   for (int q = 0; q < b->n; ++q) {
     BatchProb& P = b->host[q];
     if (form == FORM_PICKS) {
@@ -865,7 +871,7 @@ static void apply_form(sk_batch_s* b, int form) {
       set_pass_b(P, b->picks[q].chunk);
     } else {
       set_pass_a_phased(P, total);
-      set_pass_b(P, form == FORM_PHASED_4 ? 4 : 2);
+      set_pass_b(P, stepped(P) ? 1 : waves >= 4096 ? 4 : 2);
     }
   }
   b->form = form;
@@ -878,20 +884,16 @@ static void apply_form(sk_batch_s* b, int form) {
 // mostly of wide rows and 1 GiB or more, whose blocks' sums are best held back
 // (2048 inputs, 4 channels, M = 256, 2 GiB: pass A 341 us against 352 in row
 // phases), row phases for the others (five problems, 79 MB: 25 us against 194;
-// ten, 598 MB: 113 against 227), at 4 blocks per chunk where that leaves 4096
-// wavefronts.
+// ten, 598 MB: 113 against 227).
 static int choose_form(sk_batch_s* b, const std::string* path, hipStream_t s) {
   bool fits = true;
-  int64_t wide = 0, waves = 0;
+  int64_t wide = 0;
   const int64_t total = batch_bytes(b);
   for (const BatchProb& P : b->host) {
     fits = fits && phased_fits(P);
     if (P.lpr == 512 && P.a.block_len >= 128) wide += (int64_t)P.a.n_blocks * P.a.block_len * P.a.row_bytes;
-    waves += (int64_t)(P.a.row_bytes / P.a.n_inputs) * P.waves * ((P.a.n_blocks + 3) / 4);
   }
-  int best = !fits || (wide >= ((int64_t)1 << 30) && 2 * wide >= total) ? FORM_PICKS
-             : waves >= 4096                                            ? FORM_PHASED_4
-                                                                        : FORM_PHASED_2;
+  int best = !fits || (wide >= ((int64_t)1 << 30) && 2 * wide >= total) ? FORM_PICKS : FORM_PHASED;
   if (path && fits) {
     char key[256];
     snprintf(key, sizeof key, "%s|batch|set|n=%d|bytes=%lld|form", b->arch.c_str(), b->n, (long long)total);

@@ -20,7 +20,7 @@ PROBS = [(1024, 8, 2, 1030, 1024), (96, 2, 2, 512, 64), (48, 1, 4, 1500, 48), (1
          (2048, 1, 2, 511, 500), (112, 1, 2, 300, 4096), (64, 4, 2, 1024, 1025)]
 
 
-@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("form", [0, 1])
 def test_batch_scan_equals_plans(form, tmp_path):
     arch = torch.cuda.get_device_properties(0).gcnArchName
     total = sum(N * F * M * B for N, F, M, B, _ in PROBS)
