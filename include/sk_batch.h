@@ -23,9 +23,8 @@
  * per task {1, 2, 4} for wide rows, then pass B chunk length {1, 2, 4}); each
  * candidate's time and the pick are cached in a JSON file keyed by the
  * device arch and the class, and a class found there is not timed again. Then
- * the whole batch is timed with the classes' picks and in row phases at chunk
- * lengths 4 and 2, and the fastest is kept (cached for batches of as many
- * problems and bytes).
+ * the whole batch is timed with the classes' picks and in row phases, and the
+ * faster is kept (cached for batches of as many problems and bytes).
  *
  * Requirements: every problem has N % 16 == 0 and a 16-byte aligned input.
  * Errors as in sk.h.
