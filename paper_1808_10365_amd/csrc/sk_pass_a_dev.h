@@ -125,9 +125,30 @@ __device__ __forceinline__ void phased_load(u32x4 (&q)[PHASE_ROWS], const uint8_
   }
 }
 
-// A batch `left` rows before the block ends: a row past the end reads the last
-// one in its place, from column `past` on (phased_mask clears it). Row offsets are
-// 24-bit products: the row index is below PHASE_ROWS RP and G below 2^24.
+// Row r of a batch `left` rows before the block ends, and where it is read from: a
+// row past the end reads the last one in its place, from column `past` on. (On the
+// host too, where a test follows every address.)
+__host__ __device__ __forceinline__ int phased_end_row(int r, int left) { return r < left ? r : left - 1; }
+__host__ __device__ __forceinline__ uint32_t phased_end_col(int r, int left, uint32_t col, uint32_t past) {
+  return r < left ? col : past;
+}
+
+// Where batch k of the last ones of a block is fetched, `left` rows before its end:
+// row `at` on, of which `rows` are the block's, from column `col`. A batch past the
+// end reads the last row, and from `past` in every lane: `col0` suits a lane's own
+// rows, and the last row need not start where they do within a dword.
+struct PhasedFetch {
+  int at, rows;
+  uint32_t col;
+};
+__host__ __device__ __forceinline__ PhasedFetch phased_fetch(int k, int step, int left, uint32_t col0, uint32_t past) {
+  const bool any = k * step < left;
+  const int at = any ? k * step : left - 1;
+  return PhasedFetch{at, left - at, any ? col0 : past};
+}
+
+// A batch `left` rows before the block ends (phased_mask clears the rows past it).
+// Row offsets are 24-bit products: the row index is below PHASE_ROWS RP and G below 2^24.
 template <int RP>
 __device__ __forceinline__ void phased_load_end(u32x4 (&q)[PHASE_ROWS], const uint8_t* p, int left, uint32_t G, int ph,
                                                 uint32_t col, uint32_t past) {
@@ -135,7 +156,7 @@ __device__ __forceinline__ void phased_load_end(u32x4 (&q)[PHASE_ROWS], const ui
 #pragma unroll
   for (int u = 0; u < PHASE_ROWS; ++u) {
     const int r = ph + u * RP;
-    q[u] = load16_any(p, __umul24((uint32_t)(r < left ? r : left - 1), G) + (r < left ? col : past));
+    q[u] = load16_any(p, __umul24((uint32_t)phased_end_row(r, left), G) + phased_end_col(r, left, col, past));
   }
 }
 
@@ -472,8 +493,8 @@ __device__ __forceinline__ void phased_sums(const uint8_t* p, int G, int M, int 
   // (A fetch past the end reads the last row: under a branch instead, the wait
   // for the batch before it would cover the fetch too.)
   const auto fetch = [&](u32x4(&q)[PHASE_ROWS], int k) {
-    const int at = k * STEP < left ? k * STEP : left - 1;
-    phased_load_end<RP>(q, p + (int64_t)at * G, left - at, G, ph, col0, past);
+    const PhasedFetch f = phased_fetch(k, STEP, left, col0, past);
+    phased_load_end<RP>(q, p + (int64_t)f.at * G, f.rows, G, ph, f.col, past);
   };
   const auto take = [&](u32x4(&q)[PHASE_ROWS], int k) {
     phased_mask<RP>(q, left - k * STEP, ph);
@@ -510,6 +531,13 @@ __device__ __forceinline__ int pass_a_task_of(const PassATask& t) {
 // k S + g of `red`, S2 at (16 + k) S + g (32 S words).
 __host__ __device__ constexpr int phased_stride(int lpr) { return lpr + 1; }
 
+// Column a lane of unit u reads from, from the block of unit u0 on (on the host too,
+// as above).
+__host__ __device__ __forceinline__ uint32_t phased_column(int u, int u0, int M, int G, int cg, int units) {
+  const int w = u < units ? u : units - 1, bl = w / cg, c = (w - bl * cg) * 16;
+  return (uint32_t)(bl - u0 / cg) * (uint32_t)M * (uint32_t)G + (uint32_t)(c < G - 16 ? c : G - 16);
+}
+
 // One task of row phases on a 512-lane workgroup (see pass_a_phased_kernel):
 // units u0 .. u0 + LPR - 1 times 512 / LPR phases. prepare() runs with the first
 // rows in flight and leaves the table filled; red holds zeros then, or, with
@@ -526,12 +554,7 @@ __device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, c
   const int G = (int)t.row_bytes, cg = t.col_groups;
   const int units = t.n_blocks * cg;
   const int b_first = u0 / cg;            // uniform: the lanes' offsets start at this block
-  uint32_t col0;
-  {
-    const int u = u0 + lc < units ? u0 + lc : units - 1;
-    const int bl = u / cg, c = (u - bl * cg) * VEC;
-    col0 = (uint32_t)(bl - b_first) * (uint32_t)M * (uint32_t)G + (uint32_t)(c < G - VEC ? c : G - VEC);
-  }
+  const uint32_t col0 = phased_column(u0 + lc, u0, M, G, cg, units);
   uint32_t v[2 * VEC];
   phased_sums<RP>(t.x + (int64_t)b_first * M * G, G, M, ph, col0, col0, lut, v, prepare);
   if constexpr (RP == 1) {
@@ -598,6 +621,39 @@ __device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, c
 // with table and sums just fill a CU's LDS.
 __host__ __device__ constexpr int shifted_stride(int lpr) { return lpr < 128 ? lpr + 1 : lpr; }
 
+// What a lane of pass_a_task_shifted reads (on the host too, as above): its unit
+// `lc` of the task's, its row phase, its unit's block and first column, and the
+// columns its loads start at, from 4 bytes before the task's first block on.
+struct ShiftedLane {
+  int lc, ph, blk, c16, shift, c;   // c: first column of the lane's windows
+  bool live;
+  uint32_t col0, past;
+};
+template <int LPR>
+__host__ __device__ __forceinline__ ShiftedLane shifted_lane(uintptr_t x, int u0, int tid, int M, int G, int cg, int units) {
+  constexpr int VEC = 16;
+  // A wavefront takes UW units and 64 / UW phases that are equal mod 4: one shift a unit.
+  constexpr int UW = LPR <= 32 ? 16 : LPR / 2;
+  const int lane = tid & 63, wave = tid >> 6;
+  ShiftedLane l;
+  l.lc = (LPR > UW ? (wave >> 2) * UW : 0) + lane % UW;
+  l.ph = (wave & 3) + 4 * (lane / UW + (LPR > UW ? 0 : (wave >> 2) * (64 / UW)));
+  l.live = u0 + l.lc < units;
+  const int u = l.live ? u0 + l.lc : units - 1;
+  l.blk = u / cg;
+  l.c16 = (u - l.blk * cg) * VEC;
+  // Bytes from an aligned dword to the lane's first row; its rows' windows start
+  // that many columns before the unit, or as far on as the row's end allows.
+  l.shift = (int)(((uint32_t)x + ((uint32_t)l.blk * (uint32_t)M + (uint32_t)l.ph) * (uint32_t)G) & 3u);
+  const int end = G - VEC + (-(l.shift + G - VEC) & 3);
+  l.c = l.c16 - l.shift < end ? l.c16 - l.shift : end;
+  // Offsets count from 4 bytes before the block: a window may start before its row.
+  const uint32_t at = (uint32_t)(l.blk - u0 / cg) * (uint32_t)M * (uint32_t)G + 4u;
+  l.col0 = at + (uint32_t)l.c;
+  l.past = at + (uint32_t)(l.c < G - VEC ? l.c : G - VEC);
+  return l;
+}
+
 // One task of shifted row phases on a 512-lane workgroup (see
 // pass_a_shifted_kernel): units u0 .. u0 + LPR - 1, of which the last is only read
 // for the columns it has of the one before. prepare() runs with the first rows in
@@ -608,25 +664,15 @@ __device__ __forceinline__ void pass_a_task_shifted(const PassATask& t, int u0, 
                                                     int tid, Prepare&& prepare) {
   constexpr int VEC = 16, RP = 512 / LPR, S = shifted_stride(LPR);
   static_assert(RP % 4 == 0, "a lane's rows lie a multiple of 4 bytes apart");
-  // A wavefront takes UW units and 64 / UW phases that are equal mod 4: one shift a unit.
   constexpr int UW = LPR <= 32 ? 16 : LPR / 2;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int lc = (LPR > UW ? (wave >> 2) * UW : 0) + lane % UW;
-  const int ph = (wave & 3) + 4 * (lane / UW + (LPR > UW ? 0 : (wave >> 2) * (64 / UW)));
+  const int lane = tid & 63;
   const int M = t.block_len, G = (int)t.row_bytes, cg = t.col_groups;
   const int units = t.n_blocks * cg;
   const int b_first = u0 / cg;
-  const bool live = u0 + lc < units;
-  const int u = live ? u0 + lc : units - 1;
-  const int blk = u / cg, c16 = (u - blk * cg) * VEC;
-  // Bytes from an aligned dword to the lane's first row; its rows' windows start
-  // that many columns before the unit, or as far on as the row's end allows.
-  const int s = (int)(((uint32_t)(uintptr_t)t.x + ((uint32_t)blk * (uint32_t)M + (uint32_t)ph) * (uint32_t)G) & 3u);
-  const int end = G - VEC + (-(s + G - VEC) & 3);
-  const int c = c16 - s < end ? c16 - s : end;
-  // Offsets count from 4 bytes before the block: a window may start before its row.
-  const uint32_t at = (uint32_t)(blk - b_first) * (uint32_t)M * (uint32_t)G + 4u;
-  const uint32_t col0 = at + (uint32_t)c, past = at + (uint32_t)(c < G - VEC ? c : G - VEC);
+  const ShiftedLane l = shifted_lane<LPR>(reinterpret_cast<uintptr_t>(t.x), u0, tid, M, G, cg, units);
+  const int lc = l.lc, ph = l.ph, c16 = l.c16, s = l.shift, c = l.c;
+  const bool live = l.live;
+  const uint32_t col0 = l.col0, past = l.past;
   uint32_t v[2 * VEC];
   phased_sums<RP>(t.x + (int64_t)b_first * M * G - 4, G, M, ph, col0, past, lut, v, prepare);
   // Column c + k goes to place d = c + k - c16 of the unit (below 0: of the unit
