@@ -131,8 +131,8 @@ int sk_compute(sk_plan_t plan, const uint8_t* d_packed, const uint8_t* d_mask,
  * held until the process ends, with 64 KiB of counters): a call whose window (L >= 2)
  * needs more, F (ceil(B / R) + 1) N 4 bytes with R the library's chunk
  * length, returns SK_ERR_SHAPE. False-alarm thresholds are not available
- * (k sigma flags). Calls that overlap on one GPU share the array and race:
- * order them on one stream. */
+ * (k sigma flags). Calls that overlap on one GPU share the array and race: they
+ * spoil each other's results (never a later call's). Order them on one stream. */
 int sk_compute_noalloc(const sk_plan_desc* desc, const uint8_t* d_packed, const uint8_t* d_mask,
                        const sk_outputs* outs, void* stream);
 

@@ -170,15 +170,7 @@ int sk_plan_create(const sk_plan_desc* desc, sk_plan_t* out) {
     const size_t part = pass_b_direct_part_bytes((int32_t)N, (int32_t)F, p->n_blocks);
     const size_t done = pass_b_direct_done_bytes((int32_t)N, (int32_t)F, p->n_blocks);
     SK_ALLOC(p->part, part + done);
-    if (done > 0) {
-      p->done = (uint32_t*)((char*)p->part + part);
-      if (hipMemset(p->done, 0, done) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
-        set_error("clearing the window kernel's counters failed");
-        free_plan_memory(p);
-        delete p;
-        return SK_ERR_DEVICE;
-      }
-    }
+    if (done > 0) p->done = (uint32_t*)((char*)p->part + part);
   }
   p->cur = 0;
   *out = p;
@@ -229,6 +221,8 @@ static PassAConfig pass_a_config(const sk_plan_desc& d, int64_t B, const PassATu
   t->timeline = nullptr;
   t->simd_balance = 1;
   t->by_xcd = 0;
+  t->done = nullptr;
+  t->n_done = 0;
   if (u.lpr == 0 && u.variant < 0 && u.grid == 0 && u.blocks == 0) {
     const int shifted = pass_a_shifted_lanes(d_packed, t->row_bytes, B, d.block_len);
     const int lanes = shifted ? shifted : pass_a_phased_lanes(d_packed, t->row_bytes, d.n_inputs, B, d.block_len);
@@ -469,6 +463,8 @@ static int plan_call(sk_plan_s* p, const uint8_t* d_packed, const uint8_t* d_mas
     a.cs = p->cs;
   }
   if (chunk_sums) *chunk_sums = t.cs != nullptr;
+  t.done = a.done;
+  t.n_done = pass_b_direct_counts(a);
 
   int rc = launch_pass_a(t, c, s, ea);
   if (rc) return rc;
@@ -776,8 +772,8 @@ int sk_plan_pass_a_timeline(sk_plan_t p, const uint8_t* d_x, int32_t simd_balanc
 // taken once per device with hipGetSymbolAddress and kept below.
 static constexpr size_t kNoallocScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) uint8_t scratch[kNoallocScratchBytes];
-// The window kernel's counters (zero between calls; its slices' sums take the
-// scratch in the prefix sums' place).
+// The window kernel's counters (its slices' sums take the scratch in the prefix
+// sums' place). Each call's pass A clears those it uses.
 static constexpr size_t kNoallocDone = 1 << 14;
 static __device__ uint32_t scratch_done[kNoallocDone];
 
@@ -864,6 +860,8 @@ int sk_compute_noalloc(const sk_plan_desc* desc, const uint8_t* d_packed, const 
   const int32_t Rw = pass_b_plan_chunk(d.n_inputs, d.n_channels, B, L);
   PassBArgs a = make_pass_b_args(d, B, L >= 2 ? L - 1 : 0, Rw, 0, d_mask, outs, cb, nullptr);
   if (!a.direct) a = make_pass_b_args(d, B, L >= 2 ? L - 1 : 0, R, 0, d_mask, outs, cb, nullptr);
+  t.done = a.done;
+  t.n_done = pass_b_direct_counts(a);
   rc = launch_pass_a(t, c, s);
   if (rc) return rc;
   return launch_pass_b(a, s);

@@ -54,6 +54,8 @@ struct PassATask {
   int32_t simd_balance; // variant 4: 1 = wavefronts of a SIMD kept level (the library's
                         // setting), 0 = left to the arbiter (timeline comparisons only)
   int32_t by_xcd;       // variants 5, 6: consecutive tasks on one XCD, not in turn over all
+  uint32_t* done;       // the window kernel's counters of this call, n_done of them (0: none): cleared
+  int32_t n_done;       // by pass A, so no earlier call can leave a count behind
 };
 
 struct PassAConfig {
@@ -128,7 +130,7 @@ struct PassBArgs {
   int32_t vec;            // inputs per combine lane: 4 (N >= 4) or 1
   int32_t direct;         // 1: the window kernel (R blocks per wavefront), 0: scan and combine
   double* part;           // window kernel, N > 256: [5][F][B][W] sums of the input slices (W = combine_waves)
-  uint32_t* done;         // and [F][segments] finished slices, zero between calls
+  uint32_t* done;         // and [F][segments] finished slices, cleared by the call's pass A
   int32_t estimator;
   double k_sigma, expect_offset, sigma_override;
 };
@@ -141,6 +143,8 @@ int pass_b_vec(int32_t n_inputs);
 bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec);
 size_t pass_b_direct_part_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
 size_t pass_b_direct_done_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
+// Counters of a call that pass A clears (0 where no slices meet).
+int32_t pass_b_direct_counts(const PassBArgs& a);
 // Library choice of R: blocks per wavefront of the window kernel where a call
 // takes it, 1 for the stepped combine's runs of 16 blocks, else as pass_b_chunk.
 int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window);

@@ -119,6 +119,7 @@ __global__ __launch_bounds__(wg_size<LPR>()) void pass_a_shared_kernel(PassATask
       __syncthreads();
     }
   }
+  clear_counts(t);
 }
 
 template <int VEC, int LPR>
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(LPR) void pass_a_packed_kernel(PassATask t) {
       store_group<VEC>(t, b, g0, s1, s2);
     }
   }
+  clear_counts(t);
 }
 
 template <int U>
@@ -204,6 +206,7 @@ __global__ __launch_bounds__(256) void pass_a_side_by_side_kernel(PassATask t, i
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
   for (int64_t task = blockIdx.x; task < t.n_tasks; task += gridDim.x)
     pass_a_task_side_by_side<U>(t, lpb, task, lut, tid);
+  clear_counts(t);
 }
 
 int pass_a_side_by_side_lanes(int64_t col_groups) {
@@ -286,6 +289,7 @@ __global__ __launch_bounds__(512) void pass_a_deferred_kernel(PassATask t) {
       for (int k = 0; k < VEC; k += 4) *reinterpret_cast<u32x4*>(d + k) = u32x4{c[k], c[k + 1], c[k + 2], c[k + 3]};
     }
   }
+  clear_counts(t);
   if (t.timeline) {
     __builtin_amdgcn_s_waitcnt(0);
     const uint64_t t_end = __builtin_amdgcn_s_memrealtime();
@@ -336,6 +340,7 @@ __global__ __launch_bounds__(512, 4) void pass_a_phased_kernel(PassATask t) {
       for (int o = tid; o < 32 * S; o += 512) red_own[o] = 0u;
     lds_barrier();
   });
+  clear_counts(t);
 }
 
 static int launch_phased(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {
@@ -383,6 +388,7 @@ __global__ __launch_bounds__(512, 4) void pass_a_shifted_kernel(PassATask t) {
     for (int o = tid; o < 32 * S; o += 512) red[o] = 0u;
     lds_barrier();
   });
+  clear_counts(t);
 }
 
 static int launch_shifted(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {

@@ -103,7 +103,8 @@ constexpr int WINDOW_WAVES = 8;
 // block's; above, slices meet in device memory and the last to finish a segment
 // adds them in slice order and finishes its blocks. Those words are written and
 // read with agent-scope atomics (past the XCDs' caches), and the count is added
-// to once they have arrived, so no cache is written back.
+// to once they have arrived, so no cache is written back. The counts start at zero:
+// the call's pass A clears them.
 //
 // Further workgroups carry the older history on when the call is shorter than
 // the window, as the scan does.
@@ -377,7 +378,6 @@ __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, 
   before = __builtin_amdgcn_readfirstlane(before);
   if (before != (uint32_t)W - 1) return;
   asm volatile("" ::: "memory");
-  if (lane == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (mine) {
     uint64_t v[COMBINE_MAX_WAVES][5];
 #pragma unroll
@@ -488,6 +488,11 @@ size_t pass_b_direct_part_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_
 size_t pass_b_direct_done_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks) {
   // Segments of at least 8 blocks.
   return combine_waves(n_inputs, 4) > 1 ? sizeof(uint32_t) * n_channels * (size_t)((n_blocks + 7) / 8) : 0;
+}
+
+int32_t pass_b_direct_counts(const PassBArgs& a) {
+  const int X = WINDOW_WAVES * a.chunk;
+  return a.direct && combine_waves(a.n_inputs, 4) > 1 ? a.n_channels * ((a.n_blocks + X - 1) / X) : 0;
 }
 
 // Blocks per wavefront of the window kernel: the fewest that leave at most a
