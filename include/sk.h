@@ -132,7 +132,9 @@ int sk_compute(sk_plan_t plan, const uint8_t* d_packed, const uint8_t* d_mask,
  * needs more, F (ceil(B / R) + 1) N 4 bytes with R the library's chunk
  * length, returns SK_ERR_SHAPE. False-alarm thresholds are not available
  * (k sigma flags). Calls that overlap on one GPU share the array and race: they
- * spoil each other's results (never a later call's). Order them on one stream. */
+ * spoil each other's results (never a later call's). Order them on one stream.
+ * (Calls without a window, L <= 1, of at most 256 inputs with windows of few rows,
+ * or with a window of at most R blocks and B >= L - 1, do not touch the array.) */
 int sk_compute_noalloc(const sk_plan_desc* desc, const uint8_t* d_packed, const uint8_t* d_mask,
                        const sk_outputs* outs, void* stream);
 

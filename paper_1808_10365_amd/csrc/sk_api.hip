@@ -301,7 +301,7 @@ int sk_plan_set_pass_b_tile(sk_plan_t p, int32_t chunk, int32_t vec) {
     return SK_ERR_INVALID_ARG;
   }
   const int32_t N = p->d.n_inputs, F = p->d.n_channels, L = p->d.norm_window_blocks;
-  const int32_t R = chunk ? chunk : vec == 1 ? pass_b_chunk(N, F, p->n_blocks, L) : pass_b_plan_chunk(N, F, p->n_blocks, L);
+  const int32_t R = chunk ? chunk : vec == 1 ? pass_b_chunk(N, F, p->n_blocks, pass_b_vec(N)) : pass_b_plan_chunk(N, F, p->n_blocks, L);
   if (p->d.norm_window_blocks >= 2) {
     const size_t need = pass_b_prefix_bytes(p->d.n_inputs, p->d.n_channels, p->n_blocks, R);
     if (need > p->pc_bytes) {
@@ -823,7 +823,9 @@ int sk_compute_noalloc(const sk_plan_desc* desc, const uint8_t* d_packed, const 
   if (B == 0) return SK_OK;
   if (!d_packed) { set_error("NULL input"); return SK_ERR_INVALID_ARG; }
   const int L = d.norm_window_blocks;
-  const int32_t R = pass_b_chunk(d.n_inputs, d.n_channels, B, L);
+  // (Calls that need no scratch take none, and so may overlap.)
+  const int32_t Rs = pass_b_scan_free_chunk(d.n_inputs, d.n_channels, B, L);
+  const int32_t R = Rs ? Rs : pass_b_chunk(d.n_inputs, d.n_channels, B, pass_b_vec(d.n_inputs));
   const size_t need = L >= 2 ? pass_b_prefix_bytes(d.n_inputs, d.n_channels, B, R) : 0;
   if (need > kNoallocScratchBytes) {
     set_error("call needs %zu bytes of scratch; sk_compute_noalloc holds %zu (F (ceil(B / %d) + 1) N int32)", need,

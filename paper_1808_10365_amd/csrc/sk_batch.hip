@@ -1014,7 +1014,7 @@ int sk_batch_create(const sk_plan_desc* descs, int32_t n, const sk_batch_opts* o
       P.hs[1] = (int32_t*)p;
     }
     set_pass_a(P, 16, 1);
-    set_pass_b(P, pass_b_chunk((int32_t)N, (int32_t)F, B, L));
+    set_pass_b(P, pass_b_chunk((int32_t)N, (int32_t)F, B, 4));
     P.r1 = o.r1;
     P.r2 = o.r2;
     P.v = o.v;

@@ -135,8 +135,11 @@ struct PassBArgs {
   double k_sigma, expect_offset, sigma_override;
 };
 
-// Library choice of R for a call of B blocks (F channels, N inputs).
-int pass_b_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window);
+// Library choice of R for a call of B blocks (F channels, N inputs, `vec` per lane).
+int pass_b_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int vec);
+// Chunk length at which a call's window is at most a chunk, so that its combine reads
+// no prefix sums and no scratch; 0 if there is none.
+int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window);
 int pass_b_vec(int32_t n_inputs);
 // Whether a call takes the window kernel at `chunk` blocks per wavefront, and the
 // scratch its input slices meet in (bytes of part and of done; 0 for N <= 256).

@@ -463,6 +463,12 @@ static int64_t window_workgroups(int32_t n_inputs, int32_t n_channels, int64_t n
   return (int64_t)n_channels * combine_waves(n_inputs, 4) * ((n_blocks + WINDOW_WAVES * chunk - 1) / (WINDOW_WAVES * chunk));
 }
 
+int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window) {
+  // (Input counts that are no multiple of 4 count their wavefronts by one input per lane.)
+  const int R = pass_b_chunk(n_inputs, n_channels, n_blocks, n_inputs % 4 ? 1 : pass_b_vec(n_inputs));
+  return window >= 2 && !pass_b_needs_scan(window, R, n_blocks) ? R : 0;
+}
+
 // The window kernel reads up to min(L - 1, B) rows again per workgroup (and per
 // 2048 inputs), the scan and the combine a bounded number per block: the line is
 // at 2^17 such rows, about half a megabyte a CU, and at twice that where no
@@ -472,8 +478,12 @@ static int64_t window_workgroups(int32_t n_inputs, int32_t n_channels, int64_t n
 // 20.2 (1024, 4, 512, 512: just below), 15.3 / 18.3 (256, 4, 1024, 1024); above it
 // 26.8 / 24.6 (2048, 2, 512, 1024), 25.8 / 25.6 (512, 8, 1024, 512), 41.6 / 31.4
 // (2048, 4, 1024, 256).
+//
+// Not where the combine needs no prefix sums: one launch too, and no row again: 29.4 /
+// 18.9 (2048, 4, 1024, 2), 115 / 63 (2048, 4, 4096, 4), 22 / 17 (64, 8, 4096, 2), equal at
+// 12.4 / 12.6 (256, 8, 2048, 4).
 bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec) {
-  if (window < 2 || vec != 4 || n_blocks < 1) return false;
+  if (window < 2 || vec != 4 || n_blocks < 1 || pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window)) return false;
   const int64_t rows = window - 1 < n_blocks ? window - 1 : n_blocks;
   const int64_t passes = (n_inputs + 2047) / 2048;
   const int64_t wgs = window_workgroups(n_inputs, n_channels, n_blocks, chunk);
@@ -505,17 +515,18 @@ static int window_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, 
   return 4;
 }
 
-int pass_b_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window) {
+int pass_b_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int vec) {
   // Four blocks per combine workgroup, fewer while there are too few
   // wavefronts to fill the device (at least ~4 per SIMD).
-  const int64_t waves_per_chunk = combine_waves(n_inputs, pass_b_vec(n_inputs));
+  const int64_t waves_per_chunk = combine_waves(n_inputs, vec);
   int R = 4;
   while (R > 1 && ((n_blocks + R - 1) / R) * n_channels * waves_per_chunk < 4096) R /= 2;
-  (void)window;
   return R;
 }
 
 int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window) {
+  const int free_chunk = pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window);
+  if (free_chunk) return free_chunk;
   const int R = window_chunk(n_inputs, n_channels, n_blocks, window);
   if (pass_b_direct(n_inputs, n_channels, n_blocks, window, R, pass_b_vec(n_inputs))) return R;
   // Runs of 16 blocks cost least at one block a step: fewer registers, and pass A then
@@ -525,7 +536,7 @@ int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, in
   if (steps_suit(n_inputs, window, pass_b_vec(n_inputs), 1, n_blocks) &&
       step_chunks(1, n_blocks * n_channels * combine_waves(n_inputs, 4)) > 1)
     return 1;
-  return pass_b_chunk(n_inputs, n_channels, n_blocks, window);
+  return pass_b_chunk(n_inputs, n_channels, n_blocks, pass_b_vec(n_inputs));
 }
 
 size_t pass_b_prefix_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t chunk) {

@@ -50,6 +50,27 @@ def test_overlapping_noalloc_calls_leave_later_ones_right():
         assert _same(out, refs[c]), CALLS[c]
 
 
+def test_overlapping_noalloc_calls_with_windows_of_one_chunk():
+    # These use no scratch: every call is right, overlapped or not.
+    calls = [(2048, 4, 64, 1024, 4), (501, 4, 64, 520, 3)]
+    gen = torch.Generator(device=DEV).manual_seed(6)
+    streams = [torch.cuda.Stream() for _ in calls]
+    work = []
+    for N, F, M, B, L in calls:
+        x = torch.randint(0, 256, (M * B, F, N), dtype=torch.uint8, device=DEV, generator=gen)
+        plan = sk.Plan(N, F, M * B, M, norm_window=L)
+        ref = plan.compute(x, want=sk.ALL_OUTPUTS)
+        work.append((x, ref, [plan.alloc_outputs(DEV, sk.ALL_OUTPUTS) for _ in range(8)], M, L))
+        torch.cuda.synchronize()
+        plan.close()
+    for r in range(200):
+        for (x, ref, outs, M, L), s in zip(work, streams):
+            sk.compute_noalloc(x, outs[r % 8], M, norm_window=L, stream=s)
+    torch.cuda.synchronize()
+    for x, ref, outs, M, L in work:
+        assert all(_same(out, ref) for out in outs), (x.shape, M, L)
+
+
 def test_overlapping_calls_of_a_plan_leave_it_right():
     xs = _frames()
     streams = [torch.cuda.Stream() for _ in range(2)]

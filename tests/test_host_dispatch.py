@@ -12,3 +12,40 @@ def test_plan_creation_clears_nothing_and_waits_for_nothing(dispatch):
             print([line for line in log() if not line.startswith("malloc")])
         """)
     assert out.split() == ["[]"] * 4
+
+
+def test_noalloc_windows_of_one_chunk_use_no_scratch(dispatch):
+    # The combine alone: no prefix sums, no sums of slices, so such calls may overlap.
+    out = dispatch("""
+        o = outs()
+        for N, F, M, B, L in [(2048, 4, 64, 1024, 2), (2048, 4, 64, 1024, 4), (512, 8, 64, 1024, 4), (1000, 4, 64, 512, 2),
+                              (501, 4, 64, 512, 4), (257, 4, 64, 1024, 3), (8192, 1, 64, 1100, 2)]:
+            d = desc(N, F, M, B, L)
+            assert sk.sk_compute_noalloc(ctypes.byref(d), X, None, ctypes.byref(o), None) == 0, sk.sk_last_error()
+            names = launches()
+            assert "pass_a" in names[0]
+            print(" ".join(names[1:]))
+        """)
+    assert len(out.splitlines()) == 7
+    for line in out.splitlines():
+        assert len(line.split()) == 1 and "combine_kernel" in line, line
+
+
+def test_routes_of_plans_with_a_window(dispatch):
+    # Each call takes the kernels that serve its sizes best (measured, in the rules'
+    # comments): N, F, M, B, L and what must, and must not, be among pass B's kernels.
+    calls = [(2048, 4, 16, 4096, 2, "combine", "scan"), (64, 8, 64, 4096, 2, "combine", "window"),
+             (256, 8, 64, 2048, 3, "combine", "window"), (2048, 1, 64, 2048, 20, "window", "scan"),
+             (1024, 4, 64, 512, 64, "window", "scan"), (256, 4, 256, 192, 256, "window", "scan")]
+    out = dispatch(f"""
+        o = outs()
+        for N, F, M, B, L, has, no in {calls!r}:
+            rc, h = plan(N, F, M, B, L)
+            assert rc == 0, sk.sk_last_error()
+            log()
+            assert sk.sk_compute(h, X, None, ctypes.byref(o), None) == 0, sk.sk_last_error()
+            names = " ".join(launches()[1:])
+            if has not in names or no in names:
+                print(N, F, M, B, L, names)
+        """)
+    assert out == ""
