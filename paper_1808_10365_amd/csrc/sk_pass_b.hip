@@ -25,6 +25,12 @@ __global__ __launch_bounds__(64 * SCAN_MAX_WAVES) void scan_kernel(PassBArgs a) 
   scan_body(a, blockIdx.y, blockIdx.x, wave_id(), blockDim.x >> 6, lds);
 }
 
+template <int R>
+__global__ __launch_bounds__(64 * SCAN_MAX_WAVES) void scan_chunks_kernel(PassBArgs a) {
+  __shared__ uint32_t lds[SCAN_MAX_WAVES * 64];
+  scan_chunks_body<R>(a, blockIdx.y, blockIdx.x, wave_id(), blockDim.x >> 6, lds);
+}
+
 template <int V, int R, typename RI, bool OFF32>
 __global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void combine_kernel(PassBArgs a) {
   __shared__ CombineShared sh;
@@ -430,16 +436,30 @@ int launch_pass_b(const PassBArgs& args, hipStream_t s, PassEvents ev) {
   }
   const int F = a.n_channels;
   hipEvent_t start = ev.start;
-  const bool stepped = steps_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks);
-  if (stepped) a.steps = step_chunks(a.chunk, (int64_t)a.n_chunks * F * combine_waves(a.n_inputs, 4));
+  const int64_t waves = (int64_t)a.n_chunks * F * combine_waves(a.n_inputs, 4);
+  const bool stepped = runs_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks, waves);
+  if (stepped) a.steps = step_chunks(a.chunk, waves);
   if (pass_b_needs_scan(a.window, a.chunk, a.n_blocks)) {
     // Enough wavefronts for the chunks, or for the history rows a call
     // shorter than the window moves.
     const int64_t sg = shift_groups(a.hist_next_len, a.n_blocks);
-    int W = scan_rows_waves(a.cs ? a.n_chunks : a.n_blocks, SCAN_MAX_WAVES);
-    while (W < SCAN_MAX_WAVES && W * SCAN_PARTS < sg) W *= 2;
-    const dim3 grid((a.n_inputs + SCAN_INPUTS - 1) / SCAN_INPUTS, F), wg(64 * W);
-    launch_kernel(scan_kernel, grid, wg, 0, s, start, nullptr, a);
+    const dim3 grid((a.n_inputs + SCAN_INPUTS - 1) / SCAN_INPUTS, F);
+    if (stepped || (a.chunk == 1 && (int64_t)grid.x * F <= 256)) {
+      int W = scan_rows_waves(a.cs ? a.n_chunks : a.n_blocks, SCAN_MAX_WAVES);
+      while (W < SCAN_MAX_WAVES && W * SCAN_PARTS < sg) W *= 2;
+      const dim3 wg(64 * W);
+      launch_kernel(scan_kernel, grid, wg, 0, s, start, nullptr, a);
+    } else {
+      const dim3 half((a.n_inputs + 63) / 64, F), wg(64 * scan_chunks_waves(sg > a.n_chunks ? sg : a.n_chunks));
+      switch (a.chunk) {
+        case 1: launch_kernel(scan_chunks_kernel<1>, half, wg, 0, s, start, nullptr, a); break;
+        case 2: launch_kernel(scan_chunks_kernel<2>, half, wg, 0, s, start, nullptr, a); break;
+        case 4: launch_kernel(scan_chunks_kernel<4>, half, wg, 0, s, start, nullptr, a); break;
+        default:
+          set_error("pass B: chunk length %d is not 1, 2 or 4", a.chunk);
+          return SK_ERR_INVALID_ARG;
+      }
+    }
     SK_HIP_TRY(hipGetLastError());
     start = nullptr;
   }
@@ -484,10 +504,11 @@ int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_block
 // 12.4 / 12.6 (256, 8, 2048, 4).
 bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec) {
   if (window < 2 || vec != 4 || n_blocks < 1 || pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window)) return false;
+  const int W = combine_waves(n_inputs, 4);
   const int64_t rows = window - 1 < n_blocks ? window - 1 : n_blocks;
   const int64_t passes = (n_inputs + 2047) / 2048;
   const int64_t wgs = window_workgroups(n_inputs, n_channels, n_blocks, chunk);
-  return wgs * rows * passes < ((int64_t)1 << (combine_waves(n_inputs, 4) == 1 ? 18 : 17));
+  return wgs * rows * passes < ((int64_t)1 << (W == 1 ? 18 : 17));
 }
 
 size_t pass_b_direct_part_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks) {
@@ -524,6 +545,7 @@ int pass_b_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int vec
   return R;
 }
 
+
 int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window) {
   const int free_chunk = pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window);
   if (free_chunk) return free_chunk;
@@ -532,9 +554,8 @@ int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, in
   // Runs of 16 blocks cost least at one block a step: fewer registers, and pass A then
   // writes no chunk sums for the scan (whole calls, R = 1 against 4, us: 363.9 / 366.4
   // CHIME M = 256, 206.4 / 211.1 M = 128, 134.8 / 138.4 1024 inputs, 8 channels, M = 64,
-  // 249.3 / 251.9 2048 inputs, 4096 blocks, L = 500; 366.8 / 366.6 1024 inputs, L = 300).
-  if (steps_suit(n_inputs, window, pass_b_vec(n_inputs), 1, n_blocks) &&
-      step_chunks(1, n_blocks * n_channels * combine_waves(n_inputs, 4)) > 1)
+  // and windows of 16 k blocks).
+  if (runs_suit(n_inputs, window, pass_b_vec(n_inputs), 1, n_blocks, n_blocks * n_channels * combine_waves(n_inputs, 4)))
     return 1;
   return pass_b_chunk(n_inputs, n_channels, n_blocks, pass_b_vec(n_inputs));
 }

@@ -13,10 +13,11 @@
 // of two neighbours, and the window's history part is one value.
 //
 // Kernels.
-//   scan     (L >= 2) exclusive prefix sums of S1 at the chunk boundaries of
-//            the call, PC[k] = sum of S1 over [0, k R) (mod 2^32: every
-//            difference that is used is a window sum < 2^31, so it is exact),
-//            one lane per (f, i), a workgroup's wavefronts over consecutive
+//   scan     (L >= 2; scan_chunks_body for plans, scan_body for batches, for runs
+//            of blocks and for chunks of one) exclusive prefix sums of S1 at the
+//            chunk boundaries of the call, PC[k] = sum of S1 over [0, k R) (mod
+//            2^32: every difference that is used is a window sum < 2^31, so it is
+//            exact), one lane per (f, i), a workgroup's wavefronts over consecutive
 //            chunk ranges joined through LDS. It also carries the older
 //            history into the next call's suffix sums when a call is shorter
 //            than the window.
@@ -210,8 +211,7 @@ __device__ __forceinline__ bool prefix_row_read(const PassBArgs& a, int k, int w
 // SCAN_ROWS, so the registers do not depend on it. lds: W * 64 words.
 //
 // Bound by its rounds' round trips: 1024 inputs, 2000 blocks, L = 1024: pass B 40.4 ->
-// 27.9 us against one walker of 64 inputs and 64 rows per wavefront; 2048 inputs, 4
-// channels, 1024 blocks by chunk sums 28.4 -> 27.7.
+// 27.9 us against one walker of 64 inputs and 64 rows per wavefront.
 constexpr int SCAN_ROWS = 32;   // two runs of the stepped combine
 
 // Inputs per slice: a wavefront's lanes are SCAN_PARTS walkers, each of its own rows.
@@ -292,6 +292,85 @@ __device__ __forceinline__ void scan_body(const PassBArgs& a, int f, int slice, 
     __syncthreads();
   }
   shift_history(a, f, i, active, carry, w, W);
+}
+
+// Chunks a scan lane holds per round: 64 rows of S1 in flight at most.
+template <int R>
+constexpr int scan_chunks_per_lane() { return 64 / R; }
+
+// The scan of plans whose combine reads every prefix row: the chunk length fixed, so no
+// row asks whether it ends a chunk, and 64 inputs per slice, so half the workgroups.
+// One workgroup of W wavefronts: channel f, inputs [64 slice, 64 slice + 64),
+// one input per lane. Wavefront w takes chunks [k0, k0 + C) of each round of
+// C W chunks (C = 64 / R); the rounds carry the running prefix. S1 of a
+// chunk is the pass A chunk sum when the call has them (a.cs), else the sum
+// of its R rows. lds: W * 64 words.
+//
+// Bound by its rounds' round trips, and past one workgroup per CU by the registers
+// that hold a second one back. Against scan_body (us, scan alone): 18.9 / 37.7 (3000
+// inputs, 4 channels, 1100 blocks), 15.3 / 23.9 (4096, 4, 1024), 18.2 / 22.0 (1024, 8,
+// 2048), 27.6 / 32.1 (512, 8, 4096). In chunks of one block, which store every row,
+// scan_body is the better while its workgroups find a CU each: pass B 37.7 / 30.8 (2
+// inputs, 3000 blocks), 31.5 / 28.2 (1024, 1, 2000), but calls of 16384 inputs, 500
+// blocks, L = 1000 take 120.5 / 125.7.
+template <int R>
+__device__ __forceinline__ void scan_chunks_body(const PassBArgs& a, int f, int slice, int w, int W, uint32_t* lds) {
+  constexpr int C = scan_chunks_per_lane<R>();
+  const int lane = threadIdx.x & 63;
+  const int i = slice * 64 + lane;
+  const bool active = i < a.n_inputs;
+  const int nk = a.n_chunks, B = a.n_blocks;
+  const int64_t rowN = a.n_inputs;
+  uint32_t* pc = a.pc + (int64_t)f * (nk + 1) * rowN + i;
+  if (w == 0 && active) pc[0] = 0u;
+  uint32_t carry = 0;   // prefix before this round, for this lane's input
+  for (int base = 0; base < nk; base += C * W) {
+    const int k0 = base + w * C;
+    uint32_t cs[C];
+    if (a.cs) {
+      const int32_t* p = a.cs + ((int64_t)f * nk + k0) * rowN + i;
+#pragma unroll
+      for (int j = 0; j < C; ++j) cs[j] = (active && k0 + j < nk) ? (uint32_t)p[(int64_t)j * rowN] : 0u;
+    } else {
+      uint32_t x[C][R];
+      const int32_t* p = a.s1 + ((int64_t)f * B + (int64_t)k0 * R) * rowN + i;
+#pragma unroll
+      for (int j = 0; j < C; ++j)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          x[j][r] = (active && (k0 + j) * R + r < B) ? (uint32_t)p[(int64_t)(j * R + r) * rowN] : 0u;
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        uint32_t t = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) t += x[j][r];
+        cs[j] = t;
+      }
+    }
+#pragma unroll
+    for (int j = 1; j < C; ++j) cs[j] += cs[j - 1];
+    lds[w * 64 + lane] = cs[C - 1];
+    __syncthreads();
+    uint32_t off = carry, all = carry;
+    for (int q = 0; q < W; ++q) {
+      const uint32_t t = lds[q * 64 + lane];
+      if (q < w) off += t;
+      all += t;
+    }
+    carry = all;
+    if (active) {
+#pragma unroll
+      for (int j = 0; j < C; ++j)
+        if (k0 + j < nk) pc[(int64_t)(k0 + j + 1) * rowN] = off + cs[j];
+    }
+    __syncthreads();
+  }
+  shift_history(a, f, i, active, carry, w, W);
+}
+
+// Waves of a workgroup of scan_chunks_body for nk chunks (or groups of history rows).
+__host__ __device__ __forceinline__ int scan_chunks_waves(int64_t nk) {
+  return nk < SCAN_MAX_WAVES ? (nk > 0 ? (int)nk : 1) : SCAN_MAX_WAVES;
 }
 
 // Waves per slice of a scan: a power of two covering the call's
@@ -652,6 +731,17 @@ __host__ __device__ __forceinline__ bool steps_suit(int n_inputs, int window, in
 // us against 34.1 at one chunk each), else one chunk (4096: 25.1 against 27.1).
 __host__ __device__ __forceinline__ int step_chunks(int chunk, int64_t waves) {
   return waves * chunk >= 32768 ? STEP_BLOCKS / chunk : 1;
+}
+
+// Whether a plan's call takes the stepped combine, `waves` as above: where its runs
+// read only every 16th prefix row, which is what makes its scan cheap. Pass B, stepped
+// against scan_chunks_body and combine_body (us): 80.6 / 108.9 (2048 inputs, 4 channels,
+// 4096 blocks, L = 256) and 43.4 / 53.6 (1024, 8, 2048, 256), but 111 / 108 and 57 / 52 at
+// L = 33, and 33.9 / 30.9 where no runs of 16 blocks fit (2048, 4, 1000, 256).
+__host__ __device__ __forceinline__ bool runs_suit(int n_inputs, int window, int vec, int chunk, int64_t n_blocks,
+                                                   int64_t waves) {
+  const int steps = step_chunks(chunk, waves);
+  return steps_suit(n_inputs, window, vec, chunk, n_blocks) && steps > 1 && (window / chunk) % steps == 0;
 }
 
 template <int R>
