@@ -501,13 +501,26 @@ int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_block
 //
 // Not where the combine needs no prefix sums: one launch too, and no row again: 29.4 /
 // 18.9 (2048, 4, 1024, 2), 115 / 63 (2048, 4, 4096, 4), 22 / 17 (64, 8, 4096, 2), equal at
-// 12.4 / 12.6 (256, 8, 2048, 4).
+// 12.4 / 12.6 (256, 8, 2048, 4). And not where many blocks make the slices' meeting cost
+// more than a scan: from 2^16 wavefront sums of 4 slices or more on (121 / 111: 2048, 4,
+// 4096, 8; 57.8 / 55.2: 1024, 8, 2048, 12; below it 30.3 / 39.2: 2048, 2, 2048, 8, with two
+// slices 57.5 / 65.7: 512, 8, 4096, 12), and where the stepped combine runs, from 2^15 of
+// 4 slices (32.5 / 27.4: 2048, 4, 1024, 16) or 2^16 (57.6 / 54.0: 512, 8, 4096, 16; below
+// it 30.1 / 31.3: 512, 8, 2048, 16). Where the scan is one round or little more, a window
+// past 16 blocks costs more than it from 7 2^12 sums on (33.3 / 29.0: 2048, 4, 1000, 33;
+// 60.5 / 50.0: 3000, 4, 1100, 32; below it 18.0 / 24.2: 2048, 2, 1024, 64).
 bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec) {
   if (window < 2 || vec != 4 || n_blocks < 1 || pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window)) return false;
   const int W = combine_waves(n_inputs, 4);
+  const int64_t waves = n_blocks * n_channels * W;
+  const bool runs = runs_suit(n_inputs, window, 4, 1, n_blocks, waves);
+  if (W > 1 && n_inputs <= 2048 && (W >= 4 || runs) && waves >= (W >= 4 && runs ? 1 << 15 : 1 << 16)) return false;
+  if (W > 1 && n_blocks <= 1152 && window > 16 && waves >= 7 << 12) return false;
   const int64_t rows = window - 1 < n_blocks ? window - 1 : n_blocks;
   const int64_t passes = (n_inputs + 2047) / 2048;
-  const int64_t wgs = window_workgroups(n_inputs, n_channels, n_blocks, chunk);
+  // (Past 2048 inputs the line is that of two blocks a wavefront, four being no faster:
+  // calls of 3000 inputs, 3 channels, 700 blocks, L = 100: 86.0 / 77.9 us.)
+  const int64_t wgs = window_workgroups(n_inputs, n_channels, n_blocks, passes > 1 && chunk > 2 ? 2 : chunk);
   return wgs * rows * passes < ((int64_t)1 << (W == 1 ? 18 : 17));
 }
 

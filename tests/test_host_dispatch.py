@@ -35,8 +35,9 @@ def test_routes_of_plans_with_a_window(dispatch):
     # Each call takes the kernels that serve its sizes best (measured, in the rules'
     # comments): N, F, M, B, L and what must, and must not, be among pass B's kernels.
     calls = [(2048, 4, 16, 4096, 256, "step_kernel", "window"), (2048, 4, 16, 4096, 100, "scan_chunks", "step"),
-             (2048, 4, 16, 4096, 2, "combine", "scan"),
-             (1024, 8, 32, 2048, 100, "scan_chunks", "step"), (3000, 4, 32, 1100, 256, "scan_chunks", "window"), (4096, 4, 32, 1024, 100, "scan_chunks", "window"),
+             (2048, 4, 16, 4096, 8, "scan_chunks", "window"), (2048, 4, 16, 4096, 2, "combine", "scan"),
+             (1024, 8, 32, 2048, 100, "scan_chunks", "step"), (2048, 4, 64, 1000, 100, "scan_chunks", "window"),
+             (3000, 4, 32, 1100, 100, "scan_chunks", "window"), (4096, 4, 32, 1024, 100, "scan_chunks", "window"),
              (64, 8, 64, 4096, 2, "combine", "window"), (256, 8, 64, 2048, 3, "combine", "window"),
              (2048, 1, 64, 2048, 20, "window", "scan"), (1024, 4, 64, 512, 64, "window", "scan"),
              (256, 4, 256, 192, 256, "window", "scan"), (2048, 4, 256, 1024, 256, "step_kernel", "chunks")]
