@@ -72,9 +72,10 @@ int sk_plan_set_pass_a_blocks(sk_plan_t plan, int32_t blocks);
 
 /* Pass B's chunk length R (1, 2 or 4; 0 = library choice): blocks per combine
  * workgroup and per prefix step, or, where a call's windows are summed directly
- * (window of at least 2 blocks, 4 inputs per lane, few rows to sum again),
- * blocks per wavefront. And inputs per lane (1 or 4; 0 = library choice, 4 from
- * 4 inputs on). Results do not depend on R. */
+ * (window of at least 2 blocks, inputs per lane as the library chooses, few rows
+ * to sum again), blocks per wavefront. And inputs per lane (1 or 4; 0 = library
+ * choice: 4, but 1 up to 64 inputs where 4 does not divide N). Results do not
+ * depend on R. */
 int sk_plan_set_pass_b_tile(sk_plan_t plan, int32_t chunk, int32_t inputs_per_lane);
 
 /* Pass A's lanes per row and workgroup count for the next call (after

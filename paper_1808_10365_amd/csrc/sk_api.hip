@@ -416,7 +416,7 @@ static PassBArgs make_pass_b_args(const sk_plan_desc& d, int64_t B, int32_t hist
   a.n_chunks = (int32_t)((B + chunk - 1) / chunk);
   a.steps = 1;
   a.vec = vec_pref == 1 ? 1 : pass_b_vec((int32_t)N);
-  a.direct = pass_b_direct((int32_t)N, d.n_channels, B, a.window, chunk, a.vec) &&
+  a.direct = vec_pref != 1 && pass_b_direct((int32_t)N, d.n_channels, B, a.window, chunk, a.vec) &&
              (cb.part || pass_b_direct_part_bytes((int32_t)N, d.n_channels, B) == 0);
   a.part = cb.part;
   a.done = cb.done;

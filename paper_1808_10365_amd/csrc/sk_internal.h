@@ -127,7 +127,7 @@ struct PassBArgs {
   int32_t chunk;          // R: blocks per combine workgroup and per prefix step (1, 2 or 4)
   int32_t n_chunks;       // ceil(B / R)
   int32_t steps;          // chunks per run of the stepped combine (a power of two; 1: every prefix row is read)
-  int32_t vec;            // inputs per combine lane: 4 (N >= 4) or 1
+  int32_t vec;            // inputs per combine lane: 4, or 1 (N <= 64 and no multiple of 4, or set so)
   int32_t direct;         // 1: the window kernel (R blocks per wavefront), 0: scan and combine
   double* part;           // window kernel, N > 256: [5][F][B][W] sums of the input slices (W = combine_waves)
   uint32_t* done;         // and [F][segments] finished slices, cleared by the call's pass A

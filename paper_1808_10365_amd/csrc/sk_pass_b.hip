@@ -38,31 +38,32 @@ __global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void combine_kernel(PassBAr
 }
 
 // One run of a.steps chunks per workgroup.
-template <int R, typename RI, bool OFF32>
+template <int R, typename RI, bool OFF32, int V>
 __global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void step_kernel(PassBArgs a) {
   __shared__ StepShared sh;
   const int steps = a.steps, f = blockIdx.y, k0 = (int)blockIdx.x * steps, W = blockDim.x >> 6;
-  step_body<R, RI, OFF32>(a, k0, steps, f, wave_id(), wave_id(), sh);
+  step_body<R, RI, OFF32, V>(a, k0, steps, f, wave_id(), wave_id(), sh);
   __syncthreads();
   const int j = threadIdx.x, b = k0 * R + j;
   if (j < steps * R && b < a.n_blocks) step_finish(a, f, b, j, 0, W, sh);
 }
 
-template <int R, bool OFF32>
+template <int R, bool OFF32, int V>
 static void launch_step_r(const PassBArgs& a, bool fit32, dim3 grid, dim3 wg, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1) {
-  if (fit32) launch_kernel(step_kernel<R, uint32_t, OFF32>, grid, wg, 0, s, e0, e1, a);
-  else launch_kernel(step_kernel<R, uint64_t, OFF32>, grid, wg, 0, s, e0, e1, a);
+  if (fit32) launch_kernel(step_kernel<R, uint32_t, OFF32, V>, grid, wg, 0, s, e0, e1, a);
+  else launch_kernel(step_kernel<R, uint64_t, OFF32, V>, grid, wg, 0, s, e0, e1, a);
 }
 
 template <int R>
 static int launch_step(const PassBArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const bool fit32 = combine_sums_fit_32(a.n_inputs, 4, a.block_len);
+  const bool fit32 = combine_sums_fit_32(a.n_inputs, a.vec, a.block_len);
   const bool off32 = combine_offsets_fit_32(a.n_inputs, a.n_blocks, a.n_chunks, a.hist_cap);
-  const int W = combine_waves(a.n_inputs, 4);
+  const int W = combine_waves(a.n_inputs, a.vec);
   const dim3 grid((a.n_chunks + a.steps - 1) / a.steps, a.n_channels), wg(64 * W);
-  if (off32) launch_step_r<R, true>(a, fit32, grid, wg, s, e0, e1);
-  else launch_step_r<R, false>(a, fit32, grid, wg, s, e0, e1);
+  if (a.vec == 1) launch_step_r<R, false, 1>(a, fit32, grid, wg, s, e0, e1);
+  else if (off32) launch_step_r<R, true, 4>(a, fit32, grid, wg, s, e0, e1);
+  else launch_step_r<R, false, 4>(a, fit32, grid, wg, s, e0, e1);
   SK_HIP_TRY(hipGetLastError());
   return SK_OK;
 }
@@ -97,7 +98,7 @@ static int launch_combine_v(const PassBArgs& a, bool fit32, dim3 grid, dim3 wg, 
 constexpr int WINDOW_WAVES = 8;
 
 // Window kernel: pass B in one launch, without prefix sums. A workgroup takes
-// one slice of 256 inputs of a channel and X = NW R consecutive blocks, R per
+// one slice of 64 V inputs of a channel (V = 1: one slice, up to 64 inputs) and X = NW R consecutive blocks, R per
 // wavefront. The window sum before its first block comes from the rows
 // themselves: the wavefronts share them, and each then starts from that sum, the
 // blocks of the wavefronts before it and the rows those let go, all met in LDS.
@@ -114,9 +115,9 @@ constexpr int WINDOW_WAVES = 8;
 //
 // Further workgroups carry the older history on when the call is shorter than
 // the window, as the scan does.
-template <int R, typename RI>
+template <int R, typename RI, int V>
 __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, int W, int segs, int shift_wgs) {
-  constexpr int NW = WINDOW_WAVES, V = 4, C = 64 * V, X = NW * R, BATCH = 8;
+  constexpr int NW = WINDOW_WAVES, C = 64 * V, X = NW * R, BATCH = 8;
   static_assert(X <= 64, "one wavefront finishes a segment");
   __shared__ int32_t sh_base[NW][C], sh_delta[NW][C], sh_own[NW][C], sh_after[NW][C];
   __shared__ double fin_A[X], fin_Q[X];
@@ -406,18 +407,18 @@ __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, 
   }
 }
 
-template <int R>
+template <int R, int V>
 static int launch_window(const PassBArgs& a, hipStream_t s, PassEvents ev) {
   constexpr int X = WINDOW_WAVES * R;
-  const int W = combine_waves(a.n_inputs, 4), segs = (a.n_blocks + X - 1) / X;
+  const int W = combine_waves(a.n_inputs, V), segs = (a.n_blocks + X - 1) / X;
   const int rows = a.hist_next_len - a.n_blocks;      // older history rows that stay
   const int shift_wgs = a.hs_next && rows > 0 ? (rows + WINDOW_WAVES * 8 - 1) / (WINDOW_WAVES * 8) : 0;
-  const int groups = (a.n_inputs + 255) / 256;
+  const int groups = (a.n_inputs + 64 * V - 1) / (64 * V);
   const dim3 grid(a.n_channels * (W * segs + groups * shift_wgs)), wg(64 * WINDOW_WAVES);
-  if (combine_sums_fit_32(a.n_inputs, 4, a.block_len))
-    launch_kernel(window_kernel<R, uint32_t>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
+  if (combine_sums_fit_32(a.n_inputs, V, a.block_len))
+    launch_kernel(window_kernel<R, uint32_t, V>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
   else
-    launch_kernel(window_kernel<R, uint64_t>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
+    launch_kernel(window_kernel<R, uint64_t, V>, grid, wg, 0, s, ev.start, ev.stop, a, W, segs, shift_wgs);
   SK_HIP_TRY(hipGetLastError());
   return SK_OK;
 }
@@ -427,9 +428,9 @@ int launch_pass_b(const PassBArgs& args, hipStream_t s, PassEvents ev) {
   if (a.n_blocks <= 0) return SK_OK;
   if (a.direct) {
     switch (a.chunk) {
-      case 1: return launch_window<1>(a, s, ev);
-      case 2: return launch_window<2>(a, s, ev);
-      case 4: return launch_window<4>(a, s, ev);
+      case 1: return a.vec == 4 ? launch_window<1, 4>(a, s, ev) : launch_window<1, 1>(a, s, ev);
+      case 2: return a.vec == 4 ? launch_window<2, 4>(a, s, ev) : launch_window<2, 1>(a, s, ev);
+      case 4: return a.vec == 4 ? launch_window<4, 4>(a, s, ev) : launch_window<4, 1>(a, s, ev);
     }
     set_error("pass B: chunk length %d is not 1, 2 or 4", a.chunk);
     return SK_ERR_INVALID_ARG;
@@ -476,7 +477,10 @@ int launch_pass_b(const PassBArgs& args, hipStream_t s, PassEvents ev) {
   return launch_combine_v<1>(a, fit32, grid, wg, s, start, ev.stop);
 }
 
-int pass_b_vec(int32_t n_inputs) { return n_inputs >= 4 ? 4 : 1; }
+// Four inputs per lane, or one where a wavefront holds them all and rows keep to no
+// 16-byte boundary: its lanes then share the work (8 channels, 20000 blocks, us, four /
+// one: 53 / 40 with 5 to 63 inputs, but 53 / 69 with 65, which take two wavefronts).
+int pass_b_vec(int32_t n_inputs) { return n_inputs % 4 == 0 || n_inputs > 64 ? 4 : 1; }
 
 // Window workgroups of a call at R blocks per wavefront.
 static int64_t window_workgroups(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int chunk) {
@@ -484,7 +488,7 @@ static int64_t window_workgroups(int32_t n_inputs, int32_t n_channels, int64_t n
 }
 
 int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window) {
-  // (Input counts that are no multiple of 4 count their wavefronts by one input per lane.)
+  // (Input counts that are no multiple of 4 count their wavefronts by one input a lane.)
   const int R = pass_b_chunk(n_inputs, n_channels, n_blocks, n_inputs % 4 ? 1 : pass_b_vec(n_inputs));
   return window >= 2 && !pass_b_needs_scan(window, R, n_blocks) ? R : 0;
 }
@@ -510,10 +514,10 @@ int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_block
 // past 16 blocks costs more than it from 7 2^12 sums on (33.3 / 29.0: 2048, 4, 1000, 33;
 // 60.5 / 50.0: 3000, 4, 1100, 32; below it 18.0 / 24.2: 2048, 2, 1024, 64).
 bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec) {
-  if (window < 2 || vec != 4 || n_blocks < 1 || pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window)) return false;
+  if (window < 2 || (vec != 4 && n_inputs > 64) || n_blocks < 1 || pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window)) return false;
   const int W = combine_waves(n_inputs, 4);
   const int64_t waves = n_blocks * n_channels * W;
-  const bool runs = runs_suit(n_inputs, window, 4, 1, n_blocks, waves);
+  const bool runs = runs_suit(n_inputs, window, vec, 1, n_blocks, waves);
   if (W > 1 && n_inputs <= 2048 && (W >= 4 || runs) && waves >= (W >= 4 && runs ? 1 << 15 : 1 << 16)) return false;
   if (W > 1 && n_blocks <= 1152 && window > 16 && waves >= 7 << 12) return false;
   const int64_t rows = window - 1 < n_blocks ? window - 1 : n_blocks;

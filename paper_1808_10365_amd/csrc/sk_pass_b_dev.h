@@ -29,8 +29,8 @@
 //            fixed tree, wavefronts joined in LDS in a fixed order, then the
 //            estimator and flags of the chunk's blocks. It also writes the
 //            next call's history suffix sums for its blocks.
-//   step     the combine for calls with prefix sums, 4 inputs per lane and at most
-//            2048 inputs: a wavefront walks a run of up to 16 blocks (below).
+//   step     the combine for calls with prefix sums and one group of inputs per
+//            wavefront: a wavefront walks a run of up to 16 blocks (below).
 // Every load of a wavefront is issued before any of them is used, so a
 // combine wavefront costs one memory round trip.
 #pragma once
@@ -699,8 +699,8 @@ __device__ __forceinline__ void combine_body(const PassBArgs& a, int k, int f, i
 
 // ------------------------------------------------------------------ stepped combine
 //
-// The combine of long calls with a window (L >= 2, up to 2048 inputs, 4 per
-// lane): a wavefront walks up to STEP_BLOCKS / R chunks of R blocks one after the
+// The combine of long calls with a window (L >= 2; up to 2048 inputs, 4 per
+// lane, or up to 64, one per lane): a wavefront walks up to STEP_BLOCKS / R chunks of R blocks one after the
 // other, the next chunk's rows in flight while it works on one, and carries the
 // window from block to block. Only its first chunk reads prefix sums. Against one
 // chunk per wavefront: one start-up (and, batched, one problem lookup), one
@@ -721,9 +721,9 @@ struct StepShared {
 };
 
 // Whether a call takes the stepped combine (else combine_body): it has prefix sums,
-// and one group of 256 inputs per wavefront.
+// and one group of 64 `vec` inputs per wavefront.
 __host__ __device__ __forceinline__ bool steps_suit(int n_inputs, int window, int vec, int chunk, int64_t n_blocks) {
-  return vec == 4 && n_inputs <= 2048 && pass_b_needs_scan(window, chunk, n_blocks);
+  return n_inputs <= (vec == 4 ? 2048 : 64) && pass_b_needs_scan(window, chunk, n_blocks);
 }
 
 // Chunks of R blocks a wavefront walks, `waves` being the wavefronts at one chunk
@@ -744,15 +744,15 @@ __host__ __device__ __forceinline__ bool runs_suit(int n_inputs, int window, int
   return steps_suit(n_inputs, window, vec, chunk, n_blocks) && steps > 1 && (window / chunk) % steps == 0;
 }
 
-template <int R>
+template <int R, int V>
 struct StepRows {
-  IVec<4> x1[R], x2[R], old[R];   // old: S1[b - L], or (b < L - 1) the history value of b's window
+  IVec<V> x1[R], x2[R], old[R];   // old: S1[b - L], or (b < L - 1) the history value of b's window
 };
 
-// Blocks [b0, b0 + R) of channel f for the 4 inputs from il on.
-template <int R, bool OFF32>
+// Blocks [b0, b0 + R) of channel f for the V inputs from il on.
+template <int R, bool OFF32, int V>
 __device__ __forceinline__ void step_load(const PassBArgs& a, const int32_t* s1c, const int32_t* s2c,
-                                          const int32_t* hsc, int b0, int il, StepRows<R>& x) {
+                                          const int32_t* hsc, int b0, int il, StepRows<R, V>& x) {
   const int N = a.n_inputs, L = a.window, B = a.n_blocks, H = a.hist_len;
   if (b0 >= L && b0 + R <= B) {
 #pragma unroll
@@ -780,9 +780,8 @@ __device__ __forceinline__ void step_load(const PassBArgs& a, const int32_t* s1c
 
 // Wavefront `w` of the W of one run: chunks [k0, k0 + steps) of channel f; its
 // sums go to column `col` of sh. Contains no barrier.
-template <int R, typename RI, bool OFF32>
+template <int R, typename RI, bool OFF32, int V = 4>
 __device__ __forceinline__ void step_body(const PassBArgs& a, int k0, int steps, int f, int w, int col, StepShared& sh) {
-  constexpr int V = 4;
   const int lane = threadIdx.x & 63;
   const int N = a.n_inputs, L = a.window, B = a.n_blocks;
   const int i0 = (w * 64 + lane) * V;
@@ -797,8 +796,8 @@ __device__ __forceinline__ void step_body(const PassBArgs& a, int k0, int steps,
   const int run_end = run0 + steps * R < B ? run0 + steps * R : B;
   const int tail_from = B - a.hist_next_len;
   const bool run_tail = a.hs_next && run_end > tail_from;
-  StepRows<R> cur, next;
-  step_load<R, OFF32>(a, s1c, s2c, hsc, run0, il, cur);
+  StepRows<R, V> cur, next;
+  step_load<R, OFF32, V>(a, s1c, s2c, hsc, run0, il, cur);
   uint32_t use = active ? (1u << V) - 1 & ~0u << (i0 - il) : 0u;
   if (a.mask) {
 #pragma unroll
@@ -834,7 +833,7 @@ __device__ __forceinline__ void step_body(const PassBArgs& a, int k0, int steps,
   for (int st = 0; st < steps; ++st) {
     const int b0 = run0 + st * R;
     if (b0 >= B) break;
-    if (st + 1 < steps && b0 + R < B) step_load<R, OFF32>(a, s1c, s2c, hsc, b0 + R, il, next);
+    if (st + 1 < steps && b0 + R < B) step_load<R, OFF32, V>(a, s1c, s2c, hsc, b0 + R, il, next);
     const int nb = B - b0 < R ? B - b0 : R;
     const bool tail = a.hs_next && b0 + nb > tail_from;
     double accA[R], accQ[R];

@@ -76,3 +76,22 @@ def test_routes_of_pass_a(dispatch):
             sk.sk_plan_destroy(h)
         """)
     assert out == ""
+
+
+def test_lanes_of_small_input_counts(dispatch):
+    # One input per lane up to 64 inputs that 4 does not divide, four for the others.
+    calls = [(5, 8, 4, 20000, 1, "combine_kernelILi1E"), (63, 8, 4, 20000, 0, "combine_kernelILi1E"),
+             (65, 8, 4, 20000, 1, "combine_kernelILi4E"), (64, 8, 4, 20000, 1, "combine_kernelILi4E"),
+             (13, 1, 64, 300, 33, "window_kernel"), (2, 1, 64, 300, 33, "window_kernel"),
+             (51, 8, 4, 20000, 1024, "step_kernel")]
+    out = dispatch(f"""
+        o = outs()
+        for N, F, M, B, L, has in {calls!r}:
+            rc, h = plan(N, F, M, B, L)
+            log()
+            assert sk.sk_compute(h, X, None, ctypes.byref(o), None) == 0, sk.sk_last_error()
+            names = " ".join(launches()[1:])
+            if has not in names:
+                print(N, F, M, B, L, names)
+        """)
+    assert out == ""
