@@ -438,7 +438,7 @@ int launch_pass_b(const PassBArgs& args, hipStream_t s, PassEvents ev) {
   const int F = a.n_channels;
   hipEvent_t start = ev.start;
   const int64_t waves = (int64_t)a.n_chunks * F * combine_waves(a.n_inputs, 4);
-  const bool stepped = runs_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks, waves);
+  const bool stepped = runs_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks, waves, true);
   if (stepped) a.steps = step_chunks(a.chunk, waves);
   if (pass_b_needs_scan(a.window, a.chunk, a.n_blocks)) {
     // Enough wavefronts for the chunks, or for the history rows a call
@@ -488,8 +488,9 @@ static int64_t window_workgroups(int32_t n_inputs, int32_t n_channels, int64_t n
 }
 
 int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window) {
-  // (Input counts that are no multiple of 4 count their wavefronts by one input a lane.)
-  const int R = pass_b_chunk(n_inputs, n_channels, n_blocks, n_inputs % 4 ? 1 : pass_b_vec(n_inputs));
+  // (Input counts past 256 that are no multiple of 4 count their wavefronts by one input
+  // a lane.)
+  const int R = pass_b_chunk(n_inputs, n_channels, n_blocks, n_inputs % 4 && n_inputs > 256 ? 1 : pass_b_vec(n_inputs));
   return window >= 2 && !pass_b_needs_scan(window, R, n_blocks) ? R : 0;
 }
 
@@ -512,14 +513,18 @@ int pass_b_scan_free_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_block
 // 4 slices (32.5 / 27.4: 2048, 4, 1024, 16) or 2^16 (57.6 / 54.0: 512, 8, 4096, 16; below
 // it 30.1 / 31.3: 512, 8, 2048, 16). Where the scan is one round or little more, a window
 // past 16 blocks costs more than it from 7 2^12 sums on (33.3 / 29.0: 2048, 4, 1000, 33;
-// 60.5 / 50.0: 3000, 4, 1100, 32; below it 18.0 / 24.2: 2048, 2, 1024, 64).
+// 60.5 / 50.0: 3000, 4, 1100, 32; below it 18.0 / 24.2: 2048, 2, 1024, 64). Where 4 does
+// not divide the inputs, rows off 16-byte boundaries cost the others more: calls of 2047
+// inputs, 4 channels, 2100 blocks 135 / 154 at L = 7, 138 / 145 at L = 16.
 bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec) {
   if (window < 2 || (vec != 4 && n_inputs > 64) || n_blocks < 1 || pass_b_scan_free_chunk(n_inputs, n_channels, n_blocks, window)) return false;
   const int W = combine_waves(n_inputs, 4);
-  const int64_t waves = n_blocks * n_channels * W;
-  const bool runs = runs_suit(n_inputs, window, vec, 1, n_blocks, waves);
-  if (W > 1 && n_inputs <= 2048 && (W >= 4 || runs) && waves >= (W >= 4 && runs ? 1 << 15 : 1 << 16)) return false;
-  if (W > 1 && n_blocks <= 1152 && window > 16 && waves >= 7 << 12) return false;
+  if (W > 1 && n_inputs % 4 == 0) {
+    const int64_t waves = n_blocks * n_channels * W;
+    const bool runs = runs_suit(n_inputs, window, vec, 1, n_blocks, waves);
+    if (n_inputs <= 2048 && (W >= 4 || runs) && waves >= (W >= 4 && runs ? 1 << 15 : 1 << 16)) return false;
+    if (n_blocks <= 1152 && window > 16 && waves >= 7 << 12) return false;
+  }
   const int64_t rows = window - 1 < n_blocks ? window - 1 : n_blocks;
   const int64_t passes = (n_inputs + 2047) / 2048;
   // (Past 2048 inputs the line is that of two blocks a wavefront, four being no faster:
@@ -572,7 +577,7 @@ int pass_b_plan_chunk(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, in
   // writes no chunk sums for the scan (whole calls, R = 1 against 4, us: 363.9 / 366.4
   // CHIME M = 256, 206.4 / 211.1 M = 128, 134.8 / 138.4 1024 inputs, 8 channels, M = 64,
   // and windows of 16 k blocks).
-  if (runs_suit(n_inputs, window, pass_b_vec(n_inputs), 1, n_blocks, n_blocks * n_channels * combine_waves(n_inputs, 4)))
+  if (runs_suit(n_inputs, window, pass_b_vec(n_inputs), 1, n_blocks, n_blocks * n_channels * combine_waves(n_inputs, 4), true))
     return 1;
   return pass_b_chunk(n_inputs, n_channels, n_blocks, pass_b_vec(n_inputs));
 }

@@ -737,11 +737,14 @@ __host__ __device__ __forceinline__ int step_chunks(int chunk, int64_t waves) {
 // read only every 16th prefix row, which is what makes its scan cheap. Pass B, stepped
 // against scan_chunks_body and combine_body (us): 80.6 / 108.9 (2048 inputs, 4 channels,
 // 4096 blocks, L = 256) and 43.4 / 53.6 (1024, 8, 2048, 256), but 111 / 108 and 57 / 52 at
-// L = 33, and 33.9 / 30.9 where no runs of 16 blocks fit (2048, 4, 1000, 256).
+// L = 33, and 33.9 / 30.9 where no runs of 16 blocks fit (2048, 4, 1000, 256). (And where
+// rows keep to no 16-byte boundary, which its fewer loads bear better: 301 / 333 (301, 8,
+// 20000, 100); any_window.)
 __host__ __device__ __forceinline__ bool runs_suit(int n_inputs, int window, int vec, int chunk, int64_t n_blocks,
-                                                   int64_t waves) {
+                                                   int64_t waves, bool any_window = false) {
   const int steps = step_chunks(chunk, waves);
-  return steps_suit(n_inputs, window, vec, chunk, n_blocks) && steps > 1 && (window / chunk) % steps == 0;
+  return steps_suit(n_inputs, window, vec, chunk, n_blocks) && steps > 1 &&
+         ((window / chunk) % steps == 0 || (any_window && vec == 4 && n_inputs % 4 != 0));
 }
 
 template <int R, int V>

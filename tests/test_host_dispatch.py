@@ -40,7 +40,10 @@ def test_routes_of_plans_with_a_window(dispatch):
              (3000, 4, 32, 1100, 100, "scan_chunks", "window"), (4096, 4, 32, 1024, 100, "scan_chunks", "window"),
              (64, 8, 64, 4096, 2, "combine", "window"), (256, 8, 64, 2048, 3, "combine", "window"),
              (2048, 1, 64, 2048, 20, "window", "scan"), (1024, 4, 64, 512, 64, "window", "scan"),
-             (256, 4, 256, 192, 256, "window", "scan"), (2048, 4, 256, 1024, 256, "step_kernel", "chunks")]
+             (256, 4, 256, 192, 256, "window", "scan"), (2048, 4, 256, 1024, 256, "step_kernel", "chunks"),
+             # Rows off 16-byte boundaries.
+             (301, 8, 4, 20000, 100, "step_kernel", "chunks"), (2047, 4, 16, 2100, 7, "window", "scan"),
+             (190, 1, 4, 8000, 3, "window", "combine"), (301, 1, 4, 8000, 3, "combine", "window")]
     out = dispatch(f"""
         o = outs()
         for N, F, M, B, L, has, no in {calls!r}:
