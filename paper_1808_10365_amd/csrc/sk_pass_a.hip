@@ -478,20 +478,22 @@ static bool uneven_workgroups(int64_t n) { return n > 256 && n < 440; }
 //   16-byte groups: 61 / 68 (2048 inputs, 403 MB), 43 / 51 (1024 inputs, 268 MB),
 //     11.5 / 13.8 (256 inputs, 50 MB), 21 / 65 (16 inputs, 67 MB), but 175 / 174 at
 //     1 GiB, 360 / 334 at 2 GiB, 98 / 95 at 0.5 GiB of M = 128 and 105 / 102 for wide
-//     rows of M = 64, 55 / 47 where short blocks fill the chip side by side (64
-//     bytes, M = 40, 130 MB): the variants whose lanes hold whole rows there;
+//     rows of M = 64: the variants whose lanes hold whole rows there;
 //   little work: 5.5 / 5.3 below 1024 units, 6.7 / 4.2 in short blocks of 2 MB, and in
 //     narrow rows 6.4 / 5.6 (16 bytes, M = 256, 8 MB);
-//   long blocks in few narrow rows, whose units fill too few workgroups: 20.8 / 12.7 and
-//     45.5 / 36.7 (16 bytes, M = 1700, 30 and 130 MB), 13.0 / 11.9 (32 bytes), 18.4 / 16.9
-//     (104 bytes);
+//   long blocks in narrow rows, 16 units a workgroup, where that gives few workgroups or a few
+//     past one per CU: 20.8 / 12.7 (16 bytes, M = 1700, 1102 units), 26.0 / 19.5 (M = 900,
+//     4166), 18.2 / 15.6 (32 bytes, 4166); 15.2 / 17.0 between (16 bytes, M = 1024, 3662);
 //   narrow rows off 16-byte boundaries: 106 / 68 (16 bytes, M = 640, 300 MB), 43 / 39 (M =
-//     160, 70 MB), 298 / 238 (M = 80, 300 MB); 56.8 / 52.4 (48 bytes, M = 160, 200 MB); 34.9 / 32.5 (64 bytes, M = 128,
-//     130 MB), 61.5 / 58.4 (M = 256, 300 MB); 71.5 / 63.7 (104 bytes, M = 200, 300 MB);
-//     129 / 118 (144 bytes, M = 160, 500 MB);
-//   short blocks whose last batch is mostly masked: 25.0 / 21.2 (600 bytes, M = 33, 70 MB),
-//     23.1 / 20.8 (4000 bytes, M = 20), 23.4 / 21.0 (104 bytes, M = 90), and 17.0 / 14.0 at
-//     M = 24 (200 bytes, 30 MB); 30.8 / 24.8 (160 inputs, M = 80, 100 MB).
+//     160, 70 MB), 298 / 238 (M = 80, 300 MB); 56.8 / 52.4 (48 bytes, M = 160, 200 MB);
+//     34.9 / 32.5 (64 bytes, M = 128, 130 MB), 61.5 / 58.4 (M = 256, 300 MB); 71.5 / 63.7
+//     (104 bytes, M = 200, 300 MB); 129 / 118 (144 bytes, M = 160, 500 MB);
+//   short blocks: 17.0 / 14.0 (200 bytes, M = 24, 30 MB), 135 / 116 (600 bytes, M = 20, 500
+//     MB), 20.5 / 17.0 (4000 bytes, M = 20, 45 MB; 11.0 / 13.6 with 20 MB), 135 / 124 (352
+//     bytes, M = 50, 500 MB), 12.3 / 10.6 (4000 bytes, M = 34, 20 MB); where the last
+//     batch is mostly masked 23.4 / 21.0 (104 bytes, M = 90), 30.8 / 24.8 (160 inputs, M = 80,
+//     100 MB); and where 55 / 47 side by side (64 inputs, M = 40, 130 MB), but 26.5 / 41.4
+//     (400 inputs, 4 channels, M = 60).
 int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len) {
   const int64_t cg = (row_bytes + 15) / 16, units = cg * n_blocks;
   const int M = block_len;
@@ -500,22 +502,27 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
       (512 / cg + 2) * M * row_bytes >= ((int64_t)1 << 31))
     return 0;
   const bool whole = pick_vec(x, n_inputs) == 16;
+  const bool past_cu = units > 4096 && units < 5200;   // at 16 units a workgroup
   if (whole) {
     if (M < 32 || units * M * 16 > ((int64_t)1 << (M < 192 ? 28 : 29)) || (cg >= 512 && M < 128) ||
-        (cg >= 2 && M < 64 && units >= 1 << 16))
+        (cg >= 2 && cg < 10 && M < 50 && units >= 1 << 16) ||
+        (cg == 1 && ((M >= 900 && units < 1900) || (M >= 1600 && units > 4096 && units < 7040) || (M >= 2500 && units < 3000))) ||
+        (cg == 3 && ((M >= 1024 && units < 1600) || (M >= 2500 && past_cu))))
       return 0;
   } else if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0) {
-    if (M < 16 || (cg <= 4 && units < 2048) || (cg == 1 && M > 128 && reinterpret_cast<uintptr_t>(x) % 16) ||
-        (cg == 3 && M > 128 && M < 192) || ((cg == 4 || cg == 5) && M >= 128 && M < 512 && units >= 1 << 14) ||
+    if (M < 16 || (cg <= 4 && (units < 2048 || (M >= 640 && past_cu))) || (cg == 1 && M >= 640 && (units < 2240 || (units > 4096 && units < 5800))) ||
+        (cg == 1 && M > 128 && reinterpret_cast<uintptr_t>(x) % 16) ||
+        (cg == 3 && M > 128 && M < 192) || (cg == 4 && M >= 128 && M < 512 && units >= 1 << 14) ||
         ((cg == 6 || cg == 7) && M >= 128 && M < 256 && units >= 1 << 15) ||
         (cg >= 8 && cg < 12 && M >= 128 && M < 192 && units >= 1 << 17) ||
-        (cg >= 12 && cg < 64 && M < 32 && units >= 1 << 15 && units < 1 << 17))
+        (cg >= 12 && cg < 64 && M < 32 && units >= 1 << 16) ||
+        (cg >= 16 && M < 40 && ((units >= 96000 && units < 160000) || (M >= 32 && units >= 30000 && units < 60000))) ||
+        (cg >= 16 && cg < 48 && M >= 44 && M < 64 && units >= 1 << 17))
       return 0;
   } else if (M < 192 || cg < 16) {
     return 0;
   }
   if (M > 16 && M < 64 && units * M * 16 < 3 << 20 && !(whole && cg <= 3)) return 0;
-  if (M >= 1024 && units < (cg == 1 ? 8192 : cg <= (whole ? 3 : 4) ? 5120 : cg <= 8 && !whole ? 2048 : 0)) return 0;
   // About one workgroup per CU with the fewest phases to join (in1000: 20.2 us
   // with 188 workgroups of 128 units, 21.4 with 752 of 32, 29 with 94 of 256); rows of
   // under 16 groups keep a wavefront's lanes on neighbouring rows, and short calls
@@ -539,11 +546,10 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
   const int batch = 2048 / lanes, rows = (M + batch - 1) / batch * batch;
   const bool much = M >= 64 && M < 100 && 10 * rows > 13 * M;
   if (whole) {
-    if (much && cg >= 6 && units >= 1 << 16) return 0;
+    if (much && cg >= 6 && cg < 16 && units >= 1 << 16) return 0;
   } else if (cg == 1) {
     if (much && reinterpret_cast<uintptr_t>(x) % 16) return 0;
-  } else if (cg >= 6 && units >= 1 << 15 &&
-             ((much && cg < 16) || (M < 64 && 10 * rows > 11 * M && (M < 32 || units < 1 << 18)))) {
+  } else if (cg >= 6 && cg < 16 && units >= 1 << 15 && (much || (M < 64 && 10 * rows > 11 * M))) {
     return 0;
   }
   return lanes;
@@ -561,12 +567,13 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
 //     the first, 40.6 / 40 (131 bytes, M = 64) and 10 / 8.4 (189 bytes, M = 64);
 //   long blocks in many units stay with variant 5 (split loads, but whole rows a
 //     workgroup): 56 / 52 (2047 bytes, M = 256, 268 MB), and the narrowest rows with
-//     variant 0: 43.3 / 37.1 (117 bytes, M = 128, 130 MB), 41.4 / 31.9 (123 bytes, M = 392).
+//     variant 0: 43.3 / 37.1 (117 bytes, M = 128, 130 MB), 41.4 / 31.9 (123 bytes, M = 392),
+//     37.5 / 26.3 (128 bytes, M = 256, 131 MB).
 int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len) {
   const int64_t cg = (row_bytes + 18) / 16, units = cg * n_blocks;
   if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0) return 0;
   if (cg < (block_len < 128 ? 64 : 8) || block_len < 64 || units < (block_len < 128 ? 1 << 17 : 1024) ||
-      units * block_len < 1 << 18 || (block_len >= 192 && units > 60000) || (cg == 8 && units > 15000) ||
+      units * block_len < 1 << 18 || (block_len >= 192 && units > 60000) || (cg <= 9 && units > 15000) ||
       row_bytes >= (1 << 24) || units >= ((int64_t)1 << 30) || (512 / cg + 2) * block_len * row_bytes >= ((int64_t)1 << 31))
     return 0;
   int lanes = 16;

@@ -61,9 +61,9 @@ def test_routes_of_plans_with_a_window(dispatch):
 def test_routes_of_pass_a(dispatch):
     # Row phases only where they are the faster (measured, in the rule's comment): N, F,
     # M, B, the input's place in 16 bytes, and units per workgroup (0: another variant).
-    calls = [(2, 8, 1695, 3062, 0, 0), (16, 1, 1700, 1102, 0, 0), (16, 1, 640, 29296, 8, 0), (16, 1, 80, 23437, 8, 0),
+    calls = [(2, 8, 1695, 1800, 0, 0), (16, 1, 1700, 1102, 0, 0), (16, 1, 640, 29296, 8, 0), (16, 1, 80, 23437, 8, 0),
              (50, 4, 24, 6250, 0, 0), (104, 1, 200, 14423, 0, 0), (8, 8, 256, 7934, 4, 0), (300, 2, 33, 3535, 0, 0),
-             (39, 3, 128, 20905, 0, 0), (123, 1, 392, 3209, 0, 0), (104, 1, 24, 801, 0, 0), (48, 1, 50, 41666, 0, 0),
+             (39, 3, 128, 20905, 0, 0), (123, 1, 392, 3209, 0, 0), (104, 1, 24, 801, 0, 0), (48, 1, 40, 52083, 0, 0), (400, 4, 34, 4183, 0, 256), (16, 1, 1024, 6739, 0, 16),
              (4, 8, 40, 101562, 0, 32), (50, 4, 40, 37500, 0, 512), (88, 4, 128, 6658, 4, 64), (104, 1, 128, 2253, 0, 32),
              (256, 4, 256, 192, 0, 16), (1000, 3, 256, 128, 0, 128), (16, 1, 128, 60000, 0, 16)]
     out = dispatch(f"""
