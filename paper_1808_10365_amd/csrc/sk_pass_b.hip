@@ -438,14 +438,19 @@ int launch_pass_b(const PassBArgs& args, hipStream_t s, PassEvents ev) {
   const int F = a.n_channels;
   hipEvent_t start = ev.start;
   const int64_t waves = (int64_t)a.n_chunks * F * combine_waves(a.n_inputs, 4);
-  const bool stepped = runs_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks, waves, true);
+  // Runs of blocks with every prefix row written, too, where a wavefront has few inputs
+  // (us, against the plain combine): 75.0 / 82.2 (64 inputs, 8 channels, 8192 blocks, L =
+  // 33), 56.4 / 57.7 (64, 1, 8192), but 86.9 / 84.3 (256, 8, 8192).
+  const bool runs = runs_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks, waves, true);
+  const bool stepped = runs || (a.n_inputs <= 64 && steps_suit(a.n_inputs, a.window, a.vec, a.chunk, a.n_blocks) &&
+                                step_chunks(a.chunk, waves) > 1);
   if (stepped) a.steps = step_chunks(a.chunk, waves);
   if (pass_b_needs_scan(a.window, a.chunk, a.n_blocks)) {
     // Enough wavefronts for the chunks, or for the history rows a call
     // shorter than the window moves.
     const int64_t sg = shift_groups(a.hist_next_len, a.n_blocks);
     const dim3 grid((a.n_inputs + SCAN_INPUTS - 1) / SCAN_INPUTS, F);
-    if (stepped || (a.chunk == 1 && (int64_t)grid.x * F <= 256)) {
+    if (runs || (int64_t)grid.x * F <= (a.chunk == 1 ? 256 : a.chunk == 2 ? 128 : 0)) {
       int W = scan_rows_waves(a.cs ? a.n_chunks : a.n_blocks, SCAN_MAX_WAVES);
       while (W < SCAN_MAX_WAVES && W * SCAN_PARTS < sg) W *= 2;
       const dim3 wg(64 * W);

@@ -312,7 +312,8 @@ constexpr int scan_chunks_per_lane() { return 64 / R; }
 // 2048), 27.6 / 32.1 (512, 8, 4096). In chunks of one block, which store every row,
 // scan_body is the better while its workgroups find a CU each: pass B 37.7 / 30.8 (2
 // inputs, 3000 blocks), 31.5 / 28.2 (1024, 1, 2000), but calls of 16384 inputs, 500
-// blocks, L = 1000 take 120.5 / 125.7.
+// blocks, L = 1000 take 120.5 / 125.7. In chunks of two, while they leave half the CUs:
+// 61.8 / 57.5 (64, 4, 6000), 27.5 / 26.2 (1024, 1, 2000), but 35.7 / 36.4 (2048, 2, 1500).
 template <int R>
 __device__ __forceinline__ void scan_chunks_body(const PassBArgs& a, int f, int slice, int w, int W, uint32_t* lds) {
   constexpr int C = scan_chunks_per_lane<R>();
