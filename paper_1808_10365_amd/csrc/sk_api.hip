@@ -417,7 +417,7 @@ static PassBArgs make_pass_b_args(const sk_plan_desc& d, int64_t B, int32_t hist
   a.steps = 1;
   a.vec = vec_pref == 1 ? 1 : pass_b_vec((int32_t)N);
   a.direct = vec_pref != 1 && pass_b_direct((int32_t)N, d.n_channels, B, a.window, chunk, a.vec) &&
-             (cb.part || pass_b_direct_part_bytes((int32_t)N, d.n_channels, B) == 0);
+             (cb.part || pass_b_direct_part_bytes((int32_t)N, d.n_channels, B) == 0) && pass_b_window_fits(a);
   a.part = cb.part;
   a.done = cb.done;
   a.estimator = d.estimator;

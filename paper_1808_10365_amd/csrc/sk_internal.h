@@ -146,6 +146,8 @@ int pass_b_vec(int32_t n_inputs);
 bool pass_b_direct(int32_t n_inputs, int32_t n_channels, int64_t n_blocks, int32_t window, int32_t chunk, int vec);
 size_t pass_b_direct_part_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
 size_t pass_b_direct_done_bytes(int32_t n_inputs, int32_t n_channels, int64_t n_blocks);
+// Whether the older history rows that the window kernel moves fit its launch.
+bool pass_b_window_fits(const PassBArgs& a);
 // Counters of a call that pass A clears (0 where no slices meet).
 int32_t pass_b_direct_counts(const PassBArgs& a);
 // Library choice of R: blocks per wavefront of the window kernel where a call

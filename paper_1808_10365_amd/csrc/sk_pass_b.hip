@@ -407,12 +407,24 @@ __global__ __launch_bounds__(64 * WINDOW_WAVES) void window_kernel(PassBArgs a, 
   }
 }
 
+// Workgroups per channel and group of inputs that move the older history rows that stay.
+static int window_shift_wgs(const PassBArgs& a) {
+  const int rows = a.hist_next_len - a.n_blocks;
+  return a.hs_next && rows > 0 ? (rows + WINDOW_WAVES * 8 - 1) / (WINDOW_WAVES * 8) : 0;
+}
+
+// (A launch holds fewer than 2^32 lanes, 2^23 workgroups; those of the blocks are below
+// 2^18. The scan walks such a history in loops.)
+bool pass_b_window_fits(const PassBArgs& a) {
+  const int64_t groups = (a.n_inputs + 64 * a.vec - 1) / (64 * a.vec);
+  return a.n_channels * groups * window_shift_wgs(a) < 1 << 22;
+}
+
 template <int R, int V>
 static int launch_window(const PassBArgs& a, hipStream_t s, PassEvents ev) {
   constexpr int X = WINDOW_WAVES * R;
   const int W = combine_waves(a.n_inputs, V), segs = (a.n_blocks + X - 1) / X;
-  const int rows = a.hist_next_len - a.n_blocks;      // older history rows that stay
-  const int shift_wgs = a.hs_next && rows > 0 ? (rows + WINDOW_WAVES * 8 - 1) / (WINDOW_WAVES * 8) : 0;
+  const int shift_wgs = window_shift_wgs(a);
   const int groups = (a.n_inputs + 64 * V - 1) / (64 * V);
   const dim3 grid(a.n_channels * (W * segs + groups * shift_wgs)), wg(64 * WINDOW_WAVES);
   if (combine_sums_fit_32(a.n_inputs, V, a.block_len))

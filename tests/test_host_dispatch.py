@@ -98,3 +98,20 @@ def test_lanes_of_small_input_counts(dispatch):
                 print(N, F, M, B, L, names)
         """)
     assert out == ""
+
+
+def test_long_histories_fit_a_launch(dispatch):
+    # 128 channels of 4 inputs with a window of 8 million blocks, in calls of 64: the
+    # history rows that each call moves grow past what one launch can hold.
+    out = dispatch("""
+        o = outs()
+        rc, h = plan(4, 128, 2, 64, 8388607)
+        assert rc == 0, sk.sk_last_error()
+        r = ctypes.byref(o)
+        for c in range(140000):
+            assert sk.sk_compute(h, X, None, r, None) == 0, (c, sk.sk_last_error())
+            if c % 1000 == 0:
+                names = launches()[-2:]
+        print(names)
+        """)
+    assert "scan" in out and "combine" in out
