@@ -112,20 +112,64 @@ static void free_plan_memory(sk_plan_s* p) {
   if (p->hs[1]) (void)hipFree(p->hs[1]);
 }
 
-#define SK_ALLOC(ptr, nbytes)                                                     \
-  do {                                                                            \
-    size_t nb_ = (nbytes);                                                        \
-    if (nb_ > 0) {                                                                \
-      hipError_t e_ = hipMalloc((void**)&(ptr), nb_);                             \
-      if (e_ != hipSuccess) {                                                     \
-        set_error("hipMalloc(%zu) failed: %s", nb_, hipGetErrorString(e_));       \
-        free_plan_memory(p);                                                      \
-        delete p;                                                                 \
-        return SK_ERR_NOMEM;                                                      \
-      }                                                                           \
-      p->bytes += nb_;                                                            \
-    }                                                                             \
-  } while (0)
+// One allocation of a plan: false (the message set, HIP's own error taken) if there is no
+// room. Nothing is allocated for no bytes.
+template <typename T>
+static bool plan_alloc(sk_plan_s* p, T** ptr, size_t nbytes) {
+  *ptr = nullptr;
+  if (nbytes == 0) return true;
+  const hipError_t e = hipMalloc((void**)ptr, nbytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *ptr = nullptr;
+    set_error("hipMalloc(%zu) failed: %s", nbytes, hipGetErrorString(e));
+    return false;
+  }
+  p->bytes += nbytes;
+  return true;
+}
+
+// Chunk sums from pass A, for plans whose chunks can be pass A's tasks (sized for the
+// shortest such chunk, R = 2, which a tuner may pick). Without room for them the scan
+// reads the rows.
+static void alloc_chunk_sums(sk_plan_s* p) {
+  if (p->cs || p->chunk < 2 || p->d.norm_window_blocks < 2 || p->n_blocks < 2) return;
+  const size_t bytes = (size_t)p->d.n_channels * (size_t)((p->n_blocks + 1) / 2) * (size_t)p->d.n_inputs * sizeof(int32_t);
+  if (plan_alloc(p, &p->cs, bytes)) p->cs_bytes = bytes;
+}
+
+// A plan's device memory at R = chunk. False without room (nothing is held then).
+static bool alloc_plan_memory(sk_plan_s* p, int32_t chunk) {
+  const int32_t N = p->d.n_inputs, F = p->d.n_channels, L = p->d.norm_window_blocks;
+  const int64_t B = p->n_blocks;
+  const size_t fbn = (size_t)F * B * N;
+  p->chunk = chunk;
+  bool ok = plan_alloc(p, &p->s1, fbn * sizeof(int32_t)) && plan_alloc(p, &p->s2, fbn * sizeof(int32_t));
+  if (ok && L >= 2) {
+    const size_t hist = (size_t)F * p->hist_cap * N * sizeof(int32_t);
+    p->pc_bytes = pass_b_prefix_bytes(N, F, B, chunk);
+    ok = plan_alloc(p, &p->pc, p->pc_bytes) && plan_alloc(p, &p->hs[0], hist) && plan_alloc(p, &p->hs[1], hist);
+  }
+  if (!ok) {
+    free_plan_memory(p);
+    p->s1 = p->s2 = nullptr;
+    p->pc = nullptr;
+    p->hs[0] = p->hs[1] = nullptr;
+    p->bytes = p->pc_bytes = 0;
+    return false;
+  }
+  if (L >= 2) {
+    alloc_chunk_sums(p);
+    // What the window kernel's slices meet in, where some R takes a call to it (without
+    // room: scan and combine).
+    bool direct = false;
+    for (int r : {1, 2, 4}) direct = direct || pass_b_direct(N, F, B, L, r, pass_b_vec(N));
+    const size_t part = pass_b_direct_part_bytes(N, F, B), done = pass_b_direct_done_bytes(N, F, B);
+    if (direct && part > 0 && plan_alloc(p, &p->part, part + done)) p->done = (uint32_t*)((char*)p->part + part);
+  }
+  clear_error();
+  return true;
+}
 
 extern "C" {
 
@@ -151,26 +195,14 @@ int sk_plan_create(const sk_plan_desc* desc, sk_plan_t* out) {
   const int L = desc->norm_window_blocks;
   p->hist_cap = L >= 2 ? L - 1 : 0;
   p->hist_len = 0;
-  p->chunk = pass_b_plan_chunk((int32_t)N, (int32_t)F, p->n_blocks, L);
   p->s1_s2_owned = 1;
-  const size_t fbn = (size_t)F * p->n_blocks * N;
-  SK_ALLOC(p->s1, fbn * sizeof(int32_t));
-  SK_ALLOC(p->s2, fbn * sizeof(int32_t));
-  if (L >= 2) {
-    p->pc_bytes = pass_b_prefix_bytes((int32_t)N, (int32_t)F, p->n_blocks, p->chunk);
-    SK_ALLOC(p->pc, p->pc_bytes);
-    // Chunk sums from pass A when its tasks are the plan's pass B chunks
-    // (sized for the shortest such chunk, R = 2, which a tuner may pick).
-    if (p->n_blocks >= 2) {
-      p->cs_bytes = (size_t)F * (size_t)((p->n_blocks + 1) / 2) * (size_t)N * sizeof(int32_t);
-      SK_ALLOC(p->cs, p->cs_bytes);
-    }
-    SK_ALLOC(p->hs[0], (size_t)F * p->hist_cap * N * sizeof(int32_t));
-    SK_ALLOC(p->hs[1], (size_t)F * p->hist_cap * N * sizeof(int32_t));
-    const size_t part = pass_b_direct_part_bytes((int32_t)N, (int32_t)F, p->n_blocks);
-    const size_t done = pass_b_direct_done_bytes((int32_t)N, (int32_t)F, p->n_blocks);
-    SK_ALLOC(p->part, part + done);
-    if (done > 0) p->done = (uint32_t*)((char*)p->part + part);
+  // R = 1 costs a prefix row per block: without room for those, the R of fewer rows
+  // (results do not depend on it).
+  const int32_t R = pass_b_plan_chunk((int32_t)N, (int32_t)F, p->n_blocks, L);
+  const int32_t lean = pass_b_chunk((int32_t)N, (int32_t)F, p->n_blocks, pass_b_vec((int32_t)N));
+  if (!alloc_plan_memory(p, R) && (lean <= R || !alloc_plan_memory(p, lean))) {
+    delete p;
+    return SK_ERR_NOMEM;
   }
   p->cur = 0;
   *out = p;
@@ -316,6 +348,8 @@ int sk_plan_set_pass_b_tile(sk_plan_t p, int32_t chunk, int32_t vec) {
   }
   p->chunk = R;
   p->pass_b_vec = vec;
+  alloc_chunk_sums(p);
+  clear_error();
   return SK_OK;
 }
 
@@ -537,7 +571,7 @@ int sk_plan_autotune(sk_plan_t p, const uint8_t* d_x, int32_t reps, void* stream
     if (cg >= 512) {
       for (int q : {1, 2, 4}) a_opts.push_back({4, 0, q, 0, 0, 1});
       // The same tasks without the chunk sums where they would be written.
-      if (p->cs)
+      if (p->d.norm_window_blocks >= 2 && p->n_blocks >= 2)
         for (int q : {2, 4}) a_opts.push_back({4, 0, q, 0, 0, 0});
     }
     if (cg >= 512) a_opts.push_back({2, 1024, 1, 0, 0, 1});

@@ -115,3 +115,36 @@ def test_long_histories_fit_a_launch(dispatch):
         print(names)
         """)
     assert "scan" in out and "combine" in out
+
+
+def test_plan_memory(dispatch):
+    # N, F, M, B, L and the bytes that plans of these sizes have always fitted in: they
+    # still do, with a chunk length that needs fewer prefix rows if it must be, and plans
+    # whose calls never take the window kernel hold nothing for it.
+    out = dispatch("""
+        b = ctypes.c_size_t()
+        o = outs()
+        for N, F, M, B, L, fits in [(2048, 4, 256, 1024, 256, 109019136), (2048, 4, 16, 4096, 256, 385843200),
+                                    (1000, 3, 256, 128, 16, 5748000), (300, 8, 40, 5000, 16, 132297600),
+                                    (16, 1, 256, 16, 4, 4032)]:
+            fake.fake_limit(ctypes.c_size_t(fits))
+            rc, h = plan(N, F, M, B, L)
+            assert rc == 0, (N, F, M, B, L, sk.sk_last_error())
+            assert sk.sk_compute(h, X, None, ctypes.byref(o), None) == 0, sk.sk_last_error()
+            sk.sk_plan_destroy(h)
+            assert fake.fake_used() == 0
+            fake.fake_limit(ctypes.c_size_t(fits // 2))
+            rc, h = plan(N, F, M, B, L)
+            assert rc == -3 and not h.value and fake.fake_used() == 0, rc
+            fake.fake_limit(ctypes.c_size_t(1 << 40))
+        log()
+        rc, h = plan(2048, 4, 256, 1024, 256)
+        sk.sk_plan_device_bytes(h, ctypes.byref(b))
+        print(b.value, len([line for line in log() if line.startswith("malloc")]))
+        # Chunk sums come with the chunk length that uses them.
+        assert sk.sk_plan_set_pass_b_tile(h, 4, 0) == 0
+        print([line for line in log() if line.startswith("malloc")])
+        """)
+    lines = out.splitlines()
+    assert lines[0] == f"{4 * (2 * 1024 + 1025 + 2 * 255) * 2048 * 4} 5"
+    assert lines[1] == f"['malloc {4 * 512 * 2048 * 4}']"
