@@ -24,7 +24,7 @@
  * candidate's time and the pick are cached in a JSON file keyed by the
  * device arch and the class, and a class found there is not timed again. Then
  * the whole batch is timed with the classes' picks and in row phases, and the
- * faster is kept (cached for batches of as many problems and bytes).
+ * faster is kept (cached for batches of the same shapes).
  *
  * Requirements: every problem has N % 16 == 0 and a 16-byte aligned input.
  * Errors as in sk.h.

@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <map>
 #include <numeric>
 #include <string>
@@ -878,9 +879,23 @@ static void apply_form(sk_batch_s* b, int form) {
   order_queue(b);
 }
 
+// A batch's shapes in 64 bits (FNV-1a over the sorted problems), for its cache key.
+static uint64_t shapes_hash(const sk_batch_s* b) {
+  std::vector<std::array<int64_t, 5>> all;
+  for (const BatchProb& P : b->host)
+    all.push_back({P.a.n_inputs, P.a.row_bytes, P.a.block_len, P.a.n_blocks, P.window});
+  std::sort(all.begin(), all.end());
+  uint64_t h = 0xcbf29ce484222325ULL;
+  for (const auto& p : all)
+    for (int64_t v : p)
+      for (int k = 0; k < 8; ++k) h = (h ^ (uint64_t)(v >> 8 * k & 255)) * 0x100000001b3ULL;
+  return h;
+}
+
 // The form of a batch's calls. With a tuning path: each form's whole call is
 // timed (best of kTuneReps after one untimed) unless the cache holds the pick of
-// a batch of as many problems and bytes. Without: the picks' form for batches
+// a batch of these shapes (or one for any batch of as many problems and bytes, as
+// caches were first written). Without: the picks' form for batches
 // mostly of wide rows and 1 GiB or more, whose blocks' sums are best held back
 // (2048 inputs, 4 channels, M = 256, 2 GiB: pass A 341 us against 352 in row
 // phases), row phases for the others (five problems, 79 MB: 25 us against 194;
@@ -895,10 +910,12 @@ static int choose_form(sk_batch_s* b, const std::string* path, hipStream_t s) {
   }
   int best = !fits || (wide >= ((int64_t)1 << 30) && 2 * wide >= total) ? FORM_PICKS : FORM_PHASED;
   if (path && fits) {
-    char key[256];
-    snprintf(key, sizeof key, "%s|batch|set|n=%d|bytes=%lld|form", b->arch.c_str(), b->n, (long long)total);
+    char any[256], key[320];
+    snprintf(any, sizeof any, "%s|batch|set|n=%d|bytes=%lld", b->arch.c_str(), b->n, (long long)total);
+    snprintf(key, sizeof key, "%s|shapes=%016llx|form", any, (unsigned long long)shapes_hash(b));
     std::map<std::string, int> cache = load_cache(*path);
     auto it = cache.find(key);
+    if (it == cache.end()) it = cache.find(std::string(any) + "|form");
     if (it != cache.end() && it->second >= 0 && it->second < N_FORMS) {
       best = it->second;
     } else {
