@@ -316,7 +316,7 @@ __global__ __launch_bounds__(512) void pass_a_deferred_kernel(PassATask t) {
 // is summed.
 //
 // The phases meet in LDS: the row groups of a wavefront first (two swaps leave
-// each lane 8 of the 32 sums at LPR <= 16, as in the combine), then one LDS add
+// each lane 8 of the 32 sums at LPR = 16, as in the combine), then one LDS add
 // per value left.
 //
 // Bound by HBM for calls of about 50 MB to 0.5 GB, at 80 to 93 % of the read
@@ -346,10 +346,6 @@ __global__ __launch_bounds__(512, 4) void pass_a_phased_kernel(PassATask t) {
 static int launch_phased(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {
   const dim3 g(grid), w(512);
   switch (lpr) {
-    case 1: launch_kernel(pass_a_phased_kernel<1>, g, w, 0, s, ev.start, ev.stop, t); break;
-    case 2: launch_kernel(pass_a_phased_kernel<2>, g, w, 0, s, ev.start, ev.stop, t); break;
-    case 4: launch_kernel(pass_a_phased_kernel<4>, g, w, 0, s, ev.start, ev.stop, t); break;
-    case 8: launch_kernel(pass_a_phased_kernel<8>, g, w, 0, s, ev.start, ev.stop, t); break;
     case 16: launch_kernel(pass_a_phased_kernel<16>, g, w, 0, s, ev.start, ev.stop, t); break;
     case 32: launch_kernel(pass_a_phased_kernel<32>, g, w, 0, s, ev.start, ev.stop, t); break;
     case 64: launch_kernel(pass_a_phased_kernel<64>, g, w, 0, s, ev.start, ev.stop, t); break;
@@ -357,7 +353,7 @@ static int launch_phased(const PassATask& t, int lpr, int grid, hipStream_t s, P
     case 256: launch_kernel(pass_a_phased_kernel<256>, g, w, 0, s, ev.start, ev.stop, t); break;
     case 512: launch_kernel(pass_a_phased_kernel<512>, g, w, 0, s, ev.start, ev.stop, t); break;
     default:
-      set_error("pass A: phased variant needs 1..512 lanes per row, got %d", lpr);
+      set_error("pass A: phased variant needs 16..512 lanes per row, got %d", lpr);
       return SK_ERR_INVALID_ARG;
   }
   SK_HIP_TRY(hipGetLastError());

@@ -555,6 +555,7 @@ __host__ __device__ __forceinline__ uint32_t phased_column(int u, int u0, int M,
 template <int LPR, bool OVER, bool AGAIN, typename Prepare>
 __device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, const LanePackedLut& lut, uint32_t* red,
                                                    int tid, Prepare&& prepare) {
+  static_assert(LPR >= 16, "a row of 16 lanes holds the units of one or more row groups");
   constexpr int VEC = 16, RP = 512 / LPR;
   constexpr int S = phased_stride(LPR);
   constexpr int NV = LPR >= 64 ? 32 : LPR == 32 ? 16 : 8;   // sums a lane adds
@@ -601,12 +602,8 @@ __device__ __forceinline__ void pass_a_task_phased(const PassATask& t, int u0, c
 #pragma unroll
       for (int q = 0; q < NV; ++q) {
         swap_rows(c[2 * q], c[2 * q + 1]);
-        uint32_t x = c[2 * q] + c[2 * q + 1];
-        if constexpr (LPR <= 8) x += row_rot<8>(x);
-        if constexpr (LPR <= 4) x += row_rot<4>(x);
-        if constexpr (LPR <= 2) x += row_rot<2>(x);
-        if constexpr (LPR <= 1) x += row_rot<1>(x);
-        if ((lane & 15) < LPR) atomicAdd(&red[wave_value_of_row(q, lane >> 4) * S + lc], x);
+        const uint32_t x = c[2 * q] + c[2 * q + 1];
+        atomicAdd(&red[wave_value_of_row(q, lane >> 4) * S + lc], x);
       }
     }
   }
