@@ -256,8 +256,8 @@ static PassAConfig pass_a_config(const sk_plan_desc& d, int64_t B, const PassATu
   t->done = nullptr;
   t->n_done = 0;
   if (u.lpr == 0 && u.variant < 0 && u.grid == 0 && u.blocks == 0) {
-    const int shifted = pass_a_shifted_lanes(d_packed, t->row_bytes, B, d.block_len);
-    const int lanes = shifted ? shifted : pass_a_phased_lanes(d_packed, t->row_bytes, d.n_inputs, B, d.block_len);
+    const int shifted = pass_a_shifted_lanes(d_packed, t->row_bytes, B, d.block_len, u.n_cu);
+    const int lanes = shifted ? shifted : pass_a_phased_lanes(d_packed, t->row_bytes, d.n_inputs, B, d.block_len, u.n_cu);
     if (lanes) {
       const int stored = shifted ? lanes - 1 : lanes;
       t->col_groups = (int32_t)((t->row_bytes + (shifted ? 18 : 15)) / 16);

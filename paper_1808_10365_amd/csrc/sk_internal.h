@@ -85,9 +85,9 @@ inline void launch_kernel(void (*k)(P...), dim3 grid, dim3 wg, uint32_t lds, hip
 int launch_pass_a(const PassATask& t, const PassAConfig& c, hipStream_t s, PassEvents ev = PassEvents());
 int pick_vec(const uint8_t* x, int32_t n_inputs);
 // Variant 5: units of 16 columns per workgroup, or 0 where it does not suit.
-int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len);
+int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len, int n_cu);
 // Variant 6: the same for rows off 4-byte boundaries (one unit is read twice).
-int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len);
+int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len, int n_cu);
 // Lanes per row the variant supports; the planner clamps into [lo, hi].
 void pass_a_lane_range(int vec, int variant, int* lo, int* hi);
 // Whether the variant uses the packed lane table (tasks may span several blocks).

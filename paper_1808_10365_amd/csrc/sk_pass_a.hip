@@ -461,7 +461,7 @@ static int launch_vec(const PassATask& t, int lpr, int variant, int grid, hipStr
 
 // Two workgroups fit a CU: with somewhat more than one each, some CUs have twice the
 // others' work (2044 inputs, 2 channels, 314 MB: 68 us with 300, 58 with 600).
-static bool uneven_workgroups(int64_t n) { return n > 256 && n < 440; }
+static bool uneven_workgroups(int64_t n, int n_cu) { return n > n_cu && 32 * n < 55 * (int64_t)n_cu; }
 
 // Units a workgroup of variant 5 takes for a call it suits, else 0. Measured,
 // pass A alone (us, variant 5 against the best other):
@@ -490,7 +490,7 @@ static bool uneven_workgroups(int64_t n) { return n > 256 && n < 440; }
 //     batch is mostly masked 23.4 / 21.0 (104 bytes, M = 90), 30.8 / 24.8 (160 inputs, M = 80,
 //     100 MB); and where 55 / 47 side by side (64 inputs, M = 40, 130 MB), but 26.5 / 41.4
 //     (400 inputs, 4 channels, M = 60).
-int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len) {
+int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, int64_t n_blocks, int block_len, int n_cu) {
   const int64_t cg = (row_bytes + 15) / 16, units = cg * n_blocks;
   const int M = block_len;
   // 24-bit row bytes and 32-bit offsets over the blocks a workgroup spans.
@@ -498,7 +498,8 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
       (512 / cg + 2) * M * row_bytes >= ((int64_t)1 << 31))
     return 0;
   const bool whole = pick_vec(x, n_inputs) == 16;
-  const bool past_cu = units > 4096 && units < 5200;   // at 16 units a workgroup
+  // A few workgroups of 16 units past one per CU.
+  const bool past_cu = units > 16 * (int64_t)n_cu && 16 * units < 325 * (int64_t)n_cu;
   if (whole) {
     if (M < 32 || units * M * 16 > ((int64_t)1 << (M < 192 ? 28 : 29)) || (cg >= 512 && M < 128) ||
         (cg >= 2 && cg < 10 && M < 50 && units >= 1 << 16) ||
@@ -519,7 +520,7 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
     return 0;
   }
   if (M > 16 && M < 64 && units * M * 16 < 3 << 20 && !(whole && cg <= 3)) return 0;
-  // About one workgroup per CU with the fewest phases to join (in1000: 20.2 us
+  // About one workgroup per CU (256 in these figures) with the fewest phases to join (in1000: 20.2 us
   // with 188 workgroups of 128 units, 21.4 with 752 of 32, 29 with 94 of 256); rows of
   // under 16 groups keep a wavefront's lanes on neighbouring rows, and short calls
   // take 16 units (within a microsecond of the best there). Where a block is but one or two
@@ -529,8 +530,8 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
   // bytes, 300 MB: 88 with 512, 119 with 32).
   int lanes = 16;
   if (cg >= 16 && units >= (1 << 14)) {
-    while (lanes < (M < 128 ? (M >= 64 && cg < 32 ? 128 : 256) : M < 192 && cg < 32 ? 64 : 512) && 160 * 2 * lanes <= units) lanes *= 2;
-    if (lanes > 32 && uneven_workgroups(units / lanes)) lanes /= 2;
+    while (lanes < (M < 128 ? (M >= 64 && cg < 32 ? 128 : 256) : M < 192 && cg < 32 ? 64 : 512) && 5 * (int64_t)n_cu / 8 * 2 * lanes <= units) lanes *= 2;
+    if (lanes > 32 && uneven_workgroups(units / lanes, n_cu)) lanes /= 2;
   } else if (cg >= 6 && M > 32 && M < 64 && units >= 1 << 15) {
     lanes = units >= 3 << 16 ? 512 : 256;
   } else if (cg >= 6 && M >= 128 && M < 192 && units >= 1 << 13) {
@@ -565,7 +566,7 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
 //     workgroup): 56 / 52 (2047 bytes, M = 256, 268 MB), and the narrowest rows with
 //     variant 0: 43.3 / 37.1 (117 bytes, M = 128, 130 MB), 41.4 / 31.9 (123 bytes, M = 392),
 //     37.5 / 26.3 (128 bytes, M = 256, 131 MB).
-int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len) {
+int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len, int n_cu) {
   const int64_t cg = (row_bytes + 18) / 16, units = cg * n_blocks;
   if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0) return 0;
   if (cg < (block_len < 128 ? 64 : 8) || block_len < 64 || units < (block_len < 128 ? 1 << 17 : 1024) ||
@@ -573,8 +574,8 @@ int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, 
       row_bytes >= (1 << 24) || units >= ((int64_t)1 << 30) || (512 / cg + 2) * block_len * row_bytes >= ((int64_t)1 << 31))
     return 0;
   int lanes = 16;
-  while (lanes < 128 && units / (2 * lanes - 1) >= 150) lanes *= 2;
-  return lanes > 16 && uneven_workgroups(units / (lanes - 1)) ? lanes / 2 : lanes;
+  while (lanes < 128 && 128 * (units / (2 * lanes - 1)) >= 75 * (int64_t)n_cu) lanes *= 2;
+  return lanes > 16 && uneven_workgroups(units / (lanes - 1), n_cu) ? lanes / 2 : lanes;
 }
 
 int pick_vec(const uint8_t* x, int32_t n_inputs) {

@@ -18,7 +18,7 @@ std::map<uintptr_t, size_t> blocks;
 std::string text;
 size_t used = 0, limit = (size_t)1 << 48;
 uintptr_t next_block = 0x7f0000000000ull;
-std::atomic<int> events_done{1};
+std::atomic<int> events_done{1}, cus{256};
 uint8_t symbols[64];
 size_t n_symbols = 0;
 struct Dim {
@@ -44,8 +44,8 @@ thread_local int last_error = 0;
 }  // namespace
 
 extern "C" {
-// What the test sees: the log so far (then empty), the bytes held, the bytes there
-// are, and whether events have completed.
+// What the test sees and sets: the log so far (then empty), the bytes held, the bytes
+// there are, whether events have completed, and the device's compute units.
 const char* fake_log() {
   static std::string out;
   std::lock_guard<std::mutex> lk(mu);
@@ -56,6 +56,7 @@ const char* fake_log() {
 size_t fake_used() { return used; }
 void fake_limit(size_t n) { limit = n; }
 void fake_events(int done) { events_done = done; }
+void fake_cus(int n) { cus = n; }
 
 void** __hipRegisterFatBinary(const void*) {
   static void* handle;
@@ -96,7 +97,7 @@ int hipGetDevice(int* d) {
 }
 int hipSetDevice(int) { return 0; }
 int hipDeviceGetAttribute(int* v, int, int) {
-  *v = 256;
+  *v = cus;
   return 0;
 }
 int hipDeviceSynchronize() { return 0; }

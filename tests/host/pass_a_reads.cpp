@@ -69,7 +69,7 @@ int main() {
     const int64_t G = (int64_t)N * F;
     const uint8_t* x = (const uint8_t*)(uintptr_t)(0x700000000000ull + at);
     const bool shifted = kind == '6';
-    if (!lanes) lanes = shifted ? pass_a_shifted_lanes(x, G, B, M) : pass_a_phased_lanes(x, G, N, B, M);
+    if (!lanes) lanes = shifted ? pass_a_shifted_lanes(x, G, B, M, 256) : pass_a_phased_lanes(x, G, N, B, M, 256);
     const int cg = (int)((G + (shifted ? 18 : 15)) / 16), stored = shifted ? lanes - 1 : lanes;
     const int64_t units = (int64_t)cg * B;
     Range r;

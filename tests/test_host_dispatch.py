@@ -148,3 +148,19 @@ def test_plan_memory(dispatch):
     lines = out.splitlines()
     assert lines[0] == f"{4 * (2 * 1024 + 1025 + 2 * 255) * 2048 * 4} 5"
     assert lines[1] == f"['malloc {4 * 512 * 2048 * 4}']"
+
+
+def test_pass_a_workgroups_follow_the_devices_cus(dispatch):
+    # About one workgroup per CU: a quarter of the CUs, four times the units each.
+    out = dispatch("""
+        o = outs()
+        for cus in (256, 64):
+            fake.fake_cus(cus)
+            for N, F, M, B, off in [(1000, 3, 256, 128, 0), (1001, 3, 256, 40, 0)]:
+                rc, h = plan(N, F, M, B, 1)
+                log()
+                assert sk.sk_compute(h, X, None, ctypes.byref(o), None) == 0, sk.sk_last_error()
+                name = launches()[0]
+                print(int(name.split("ILi")[1].split("E")[0]), "shifted" in name)
+        """)
+    assert out.split("\n")[:4] == ["128 False", "32 True", "512 False", "128 True"], out
