@@ -87,8 +87,9 @@ static size_t output_bytes(const sk_plan_desc& d, const sk_outputs& o) {
   return b;
 }
 
-// Called with the lock held: move completed frames to `done`.
-static void reap(sk_server_s* s) {
+// Called with the lock held: move completed frames to `done`. Whether there were any.
+static bool reap(sk_server_s* s) {
+  bool any = false;
   for (size_t k = 0; k < s->inflight.size();) {
     Frame* f = s->inflight[k].get();
     hipError_t q = hipEventQuery(f->done_ev);
@@ -101,6 +102,7 @@ static void reap(sk_server_s* s) {
     s->event_free.push_back(f->done_ev);
     if (f->ready_ev) s->event_free.push_back(f->ready_ev);
     s->stats.completed += 1;
+    any = true;
     s->inflight[k] = std::move(s->inflight.back());
     s->inflight.pop_back();
   }
@@ -108,6 +110,7 @@ static void reap(sk_server_s* s) {
     s->stats.busy_seconds += now_s() - s->busy_since;
     s->busy_since = -1.0;
   }
+  return any;
 }
 
 // Called with the lock held: admit queued frames in arrival order. A frame
@@ -174,9 +177,9 @@ static void worker_main(sk_server_s* s) {
   (void)prctl(PR_SET_TIMERSLACK, 1000UL, 0UL, 0UL, 0UL);
   std::unique_lock<std::mutex> lk(s->mu);
   for (;;) {
-    reap(s);
+    const bool done = reap(s);
     admit(s);
-    s->cv_done.notify_all();
+    if (done) s->cv_done.notify_all();   // (a look that found nothing wakes nobody)
     if (s->stop && s->queue.empty() && s->inflight.empty()) break;
     if (s->fatal) break;
     if (s->inflight.empty())

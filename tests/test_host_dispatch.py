@@ -164,3 +164,38 @@ def test_pass_a_workgroups_follow_the_devices_cus(dispatch):
                 print(int(name.split("ILi")[1].split("E")[0]), "shifted" in name)
         """)
     assert out.split("\n")[:4] == ["128 False", "32 True", "512 False", "128 True"], out
+
+
+def test_a_waiting_drain_is_not_woken_by_every_look(dispatch):
+    # A frame that takes its time: the dispatcher looks at it every 10 us, but a thread
+    # in sk_server_drain sleeps until it is done.
+    out = dispatch("""
+        import resource, threading, time
+
+        class Server(ctypes.Structure):
+            _fields_ = [("budget", ctypes.c_size_t), ("inflight", ctypes.c_int32), ("streams", ctypes.c_int32),
+                        ("queue", ctypes.c_int32)]
+
+        srv, ident, ticket, o = ctypes.c_void_p(), ctypes.c_int32(), ctypes.c_uint64(), outs()
+        assert sk.sk_server_create(ctypes.byref(Server(1 << 30, 4, 2, 16)), ctypes.byref(srv)) == 0
+        assert sk.sk_server_add_array(srv, ctypes.byref(desc(16, 1, 256, 16, 4)), ctypes.byref(ident)) == 0
+        fake.fake_events(0)
+        woken = []
+
+        def drain():
+            before = resource.getrusage(resource.RUSAGE_THREAD).ru_nvcsw
+            assert sk.sk_server_drain(srv) == 0
+            woken.append(resource.getrusage(resource.RUSAGE_THREAD).ru_nvcsw - before)
+
+        assert sk.sk_stream_submit(srv, 0, X, 0, ctypes.byref(o), ctypes.c_uint64(0), None, ctypes.byref(ticket)) == 0
+        t = threading.Thread(target=drain)
+        t.start()
+        time.sleep(0.3)
+        assert t.is_alive()
+        fake.fake_events(1)
+        t.join(10)
+        assert not t.is_alive()
+        print(woken[0])
+        sk.sk_server_destroy(srv)
+        """)
+    assert int(out) < 100, out
