@@ -62,7 +62,8 @@ int sk_plan_set_pass_a_tile(sk_plan_t plan, int32_t lanes_per_row);
  * workgroups loop over tasks). Variants 1..4 apply to the 16-byte path
  * (N % 16 == 0, aligned input); other inputs use variant 0. Lanes per row
  * are clamped to 256..1024 for variants 1 and 2. SK_ERR_INVALID_ARG outside
- * -1..4. */
+ * -1..4: the row phases that sk_plan_tuning reports as 5 and 6 are part of the
+ * library's choice, -1. */
 int sk_plan_set_pass_a_variant(sk_plan_t plan, int32_t variant, int32_t grid);
 
 /* Consecutive blocks one pass A task walks with the packed-table variants
@@ -94,7 +95,7 @@ int sk_read_probe(const uint8_t* d_x, int64_t bytes, int32_t workgroups, uint32_
 
 /* Result of sk_plan_autotune: the settings kept and their times. */
 typedef struct {
-  int32_t pass_a_variant;      /* 0..4, as SK_PASS_A_*; 5, 6: row phases over 16-byte units (library choice) */
+  int32_t pass_a_variant;      /* 0..4, as SK_PASS_A_*; 5, 6: row phases over 16-byte units (kept by SK_PASS_A_AUTO) */
   int32_t pass_a_lanes;        /* lanes per row */
   int32_t pass_a_blocks;       /* consecutive blocks per task */
   int32_t pass_a_chunk_sums;   /* 1: pass A writes the chunk sums the scan reads */

@@ -394,7 +394,7 @@ class Plan:
         _check(self._lib.sk_plan_set_pass_a_blocks(self.handle, int(blocks)))
 
     def set_pass_a_variant(self, variant: int, grid: int = 0):
-        """Pass A variant (-1: library choice; 0 shared table, 1/2 packed lane
+        """Pass A variant (-1: library choice, which may be row phases; 0 shared table, 1/2 packed lane
         table with 8/16 rows per load, 3 blocks side by side, 4 deferred stores)
         and workgroup count (0: one per task)."""
         _check(self._lib.sk_plan_set_pass_a_variant(self.handle, int(variant), int(grid)))
