@@ -78,6 +78,7 @@ __global__ __launch_bounds__(wg_size<LPR>()) void pass_a_shared_kernel(PassATask
   const int tid = threadIdx.x;
   for (int k = tid; k < 256; k += WG) lut16[k] = (uint16_t)code_power((uint32_t)k);
   __syncthreads();
+  const CountsToClear<WG> counts(t);
   const int lc = tid % LPR;
   const int ph = tid / LPR;
   const int M = t.block_len;
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(wg_size<LPR>()) void pass_a_shared_kernel(PassATask
       __syncthreads();
     }
   }
-  clear_counts(t);
+  counts.clear(tid);
 }
 
 template <int VEC, int LPR>
@@ -161,6 +162,7 @@ __global__ __launch_bounds__(LPR) void pass_a_packed_kernel(PassATask t) {
   const int tid = threadIdx.x;
   fill_lane_packed_lut<LPR>(lut32, tid);
   __syncthreads();
+  const CountsToClear<LPR> counts(t);
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
   const int M = t.block_len;
   const int64_t G = t.row_bytes;
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(LPR) void pass_a_packed_kernel(PassATask t) {
       store_group<VEC>(t, b, g0, s1, s2);
     }
   }
-  clear_counts(t);
+  counts.clear(tid);
 }
 
 template <int U>
@@ -203,10 +205,11 @@ __global__ __launch_bounds__(256) void pass_a_side_by_side_kernel(PassATask t, i
   const int tid = threadIdx.x;
   fill_lane_packed_lut<256>(lut32, tid);
   __syncthreads();
+  const CountsToClear<256> counts(t);
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
   for (int64_t task = blockIdx.x; task < t.n_tasks; task += gridDim.x)
     pass_a_task_side_by_side<U>(t, lpb, task, lut, tid);
-  clear_counts(t);
+  counts.clear(tid);
 }
 
 int pass_a_side_by_side_lanes(int64_t col_groups) {
@@ -239,6 +242,7 @@ __global__ __launch_bounds__(512) void pass_a_deferred_kernel(PassATask t) {
   fill_lane_packed_lut<512>(lut32, tid);
   simd_balance_post(simd_of, progress, tid);
   __syncthreads();
+  const CountsToClear<512> counts(t);
   SimdBalance bal = simd_balance_pair(simd_of, progress, 8);
   NoBalance arbiter;
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
@@ -289,7 +293,7 @@ __global__ __launch_bounds__(512) void pass_a_deferred_kernel(PassATask t) {
       for (int k = 0; k < VEC; k += 4) *reinterpret_cast<u32x4*>(d + k) = u32x4{c[k], c[k + 1], c[k + 2], c[k + 3]};
     }
   }
-  clear_counts(t);
+  counts.clear(tid);
   if (t.timeline) {
     __builtin_amdgcn_s_waitcnt(0);
     const uint64_t t_end = __builtin_amdgcn_s_memrealtime();
@@ -333,6 +337,7 @@ __global__ __launch_bounds__(512, 4) void pass_a_phased_kernel(PassATask t) {
   __shared__ __attribute__((aligned(16))) uint32_t lut32[LANE_LUT_DWORDS];
   __shared__ uint32_t red_own[RED ? 32 * S : 1];
   const int tid = threadIdx.x;
+  const CountsToClear<512> counts(t);
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
   pass_a_task_phased<LPR, OVER, false>(t, pass_a_task_of(t) * LPR, lut, OVER ? lut32 : red_own, tid, [&] {
     fill_lane_packed_lut<512>(lut32, tid);
@@ -340,7 +345,7 @@ __global__ __launch_bounds__(512, 4) void pass_a_phased_kernel(PassATask t) {
       for (int o = tid; o < 32 * S; o += 512) red_own[o] = 0u;
     lds_barrier();
   });
-  clear_counts(t);
+  counts.clear(tid);
 }
 
 static int launch_phased(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {
@@ -378,13 +383,14 @@ __global__ __launch_bounds__(512, 4) void pass_a_shifted_kernel(PassATask t) {
   __shared__ __attribute__((aligned(16))) uint32_t lut32[LANE_LUT_DWORDS];
   __shared__ uint32_t red[32 * S];
   const int tid = threadIdx.x;
+  const CountsToClear<512> counts(t);
   const LanePackedLut lut{reinterpret_cast<const uint8_t*>(lut32), (uint32_t)(tid & 63) * 4};
   pass_a_task_shifted<LPR>(t, pass_a_task_of(t) * (LPR - 1), lut, red, tid, [&] {
     fill_lane_packed_lut<512>(lut32, tid);
     for (int o = tid; o < 32 * S; o += 512) red[o] = 0u;
     lds_barrier();
   });
-  clear_counts(t);
+  counts.clear(tid);
 }
 
 static int launch_shifted(const PassATask& t, int lpr, int grid, hipStream_t s, PassEvents ev) {

@@ -180,14 +180,24 @@ __device__ __forceinline__ void phased_add(const u32x4 (&q)[PHASE_ROWS], const L
     }
 }
 
-// Clears the counters in which the call's window kernel counts its finished slices.
-// Called behind a kernel's last stores: ahead of its loads, the first rows' wait covers
-// the store too (0.5 us of pass A, 2048 inputs, 403 MB).
-__device__ __forceinline__ void clear_counts(const PassATask& t) {
-  if (t.n_done > 0)
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < t.n_done; k += (int64_t)gridDim.x * blockDim.x)
-      t.done[k] = 0u;
-}
+// Clears the counters in which the call's window kernel counts its finished slices:
+// `clear` behind a kernel's last stores (ahead of its loads, the first rows' wait covers
+// the store too: 0.5 us of pass A, 2048 inputs, 403 MB). The arguments are taken while
+// they are still in the scalar cache and kept in registers: at the end of a long kernel
+// they would come from host memory again (1 us of pass A, 2048 inputs, 2 GiB).
+template <int WG>
+struct CountsToClear {
+  uint32_t* done;
+  int32_t n, grid;
+  __device__ __forceinline__ explicit CountsToClear(const PassATask& t)
+      : done(t.done), n(t.n_done), grid((int32_t)gridDim.x) {
+    asm volatile("" : "+s"(done), "+s"(n), "+s"(grid));
+  }
+  __device__ __forceinline__ void clear(int tid) const {
+    if (n > 0)
+      for (int64_t k = (int64_t)blockIdx.x * WG + tid; k < n; k += (int64_t)grid * WG) done[k] = 0u;
+  }
+};
 
 // Nothing between packed runs.
 struct NoBalance {
