@@ -469,6 +469,38 @@ static int launch_vec(const PassATask& t, int lpr, int variant, int grid, hipStr
 // others' work (2044 inputs, 2 channels, 314 MB: 68 us with 300, 58 with 600).
 static bool uneven_workgroups(int64_t n, int n_cu) { return n > n_cu && 32 * n < 55 * (int64_t)n_cu; }
 
+// Rows of dwords off 16-byte boundaries in which variant 0, whose lanes take a dword each,
+// is faster than variant 5 though that keeps more loads in flight: calls of many units,
+// where its 16-byte loads are split or `rows`, a block's rows in whole batches, are many
+// more than M; and narrow rows, whose blocks are apart. Measured, variant 0 / 5 (us):
+//   32 bytes 69 / 74 (M = 160, 200 MB), 68 / 87 (M = 1024, 390 MB), but 73 / 59 (M = 128);
+//   48 bytes 83 / 100 (M = 2000, 400 MB), but 59 / 55 with 36 (M = 1757, 241 MB); 64 bytes 10.1 / 13.4 (M = 140, 30 MB);
+//   80 bytes 53 / 61 (M = 140, 114 MB); 112 bytes 11.1 / 12.2 (M = 64, 30 MB);
+//   240 bytes 20.4 / 25.4 (M = 64, 80 MB; 12.4 / 11.8 with 30 MB), 44 / 49 (M = 100, 200 MB);
+//   256 bytes 37 / 48 (M = 256, 200 MB), 75 / 93 (M = 512, 400 MB; 61 / 44 with 200 MB);
+//   512 bytes 20.8 / 25.3 (M = 50, 80 MB; 56 is the better in variant 5).
+// (4268 calls of 27 row lengths, 3 to 350 MB: of the 490 that this moves, 23 lose 5 % or
+// more, all are 9 % faster on average.)
+static bool dword_rows_shared(int64_t row_bytes, int64_t units, int M, int rows) {
+  const int64_t cg = (row_bytes + 15) / 16;
+  auto in = [&](int above, int to) { return M > above && M <= to; };
+  if (cg == 2) return in(64, 100) || (M > 130 && !(in(180, 400) && units >= 22000));
+  if (cg == 3)
+    return (in(64, 100) && units < 12000) || (in(200, 400) && units < 5000) || (row_bytes > 40 && M >= 1400 && units >= 8000);
+  if (cg == 4)
+    return (in(64, 100) && units < 12000) || in(130, 200) || (in(200, 400) && units >= 5000) || (M >= 1400 && units >= 8000);
+  if (cg >= 5 && cg < 10 && M > 64 && units >= 12000 && 2 * rows > 3 * M) return true;
+  if (cg == 5) return in(70, 85) && units >= 12000;
+  if (cg >= 6 && cg < 9)
+    return (in(60, 85) && units >= 12000) || (in(85, 130) && units >= 24000) || (in(30, 60) && units >= 16000 && units < (M > 45 ? 100000 : 1 << 15)) ||
+           (in(130, 180) && units >= 12000) || (in(180, 260) && units >= 24000);
+  if (cg >= 9 && cg < 12) return (in(30, 60) && units >= 24000 && units < 140000) || (in(60, 105) && units >= 33000);
+  if (cg >= 12 && cg < 18)
+    return (in(30, 260) && units >= (M <= 45 && cg < 16 ? 24000 : 33000)) ||
+           (cg >= 16 && in(260, 800) && units >= 33000 && units < (M < 400 ? 130000 : 60000));
+  return cg >= 18 && cg < 64 && in(30, 60) && units >= 65000 && units < 105000 && 4 * rows > 5 * M;
+}
+
 // Units a workgroup of variant 5 takes for a call it suits, else 0. Measured,
 // pass A alone (us, variant 5 against the best other):
 //   rows not of 16-byte groups, on 4-byte boundaries: 20.2 / 31.7 (3000 bytes,
@@ -555,6 +587,7 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
   } else if (cg >= 6 && cg < 16 && units >= 1 << 15 && (much || (M < 64 && 10 * rows > 11 * M))) {
     return 0;
   }
+  if (!whole && row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0 && dword_rows_shared(row_bytes, units, M, rows)) return 0;
   return lanes;
 }
 
@@ -568,15 +601,20 @@ int pass_a_phased_lanes(const uint8_t* x, int64_t row_bytes, int32_t n_inputs, i
 //   short blocks only in wide rows and where there are many: 217 / 255 (2545 bytes, M =
 //     100, 1 GB), 57 / 64 (4095 bytes, M = 64, 262 MB), but 19.1 / 19.1 with 65 MB of
 //     the first, 40.6 / 40 (131 bytes, M = 64) and 10 / 8.4 (189 bytes, M = 64);
-//   long blocks in many units stay with variant 5 (split loads, but whole rows a
-//     workgroup): 56 / 52 (2047 bytes, M = 256, 268 MB), and the narrowest rows with
-//     variant 0: 43.3 / 37.1 (117 bytes, M = 128, 130 MB), 41.4 / 31.9 (123 bytes, M = 392),
-//     37.5 / 26.3 (128 bytes, M = 256, 131 MB).
+//   long blocks of wide rows stay with variant 5 where its workgroups of 256 units are just short of one
+//     per CU: 51 / 53 (2047 bytes, M = 256, 262 MB), 68 / 64 (M = 320);
+//   many units of blocks of 256 or 320 rows in narrow rows stay with variant 5: 109 / 97
+//     (450 bytes, M = 256, 500 MB), 80 / 72 (350 bytes, M = 320, 330 MB), but 83 / 124 with
+//     M = 192 (1000 bytes, 420 MB), 85 / 95 (2047 bytes, M = 256, 420 MB), 102 / 108 (350
+//     bytes, M = 512, 500 MB); and the narrowest rows with variant 0: 43.3 / 37.1 (117
+//     bytes, M = 128, 130 MB), 41.4 / 31.9 (123 bytes, M = 392), 37.5 / 26.3 (128 bytes, M =
+//     256, 131 MB).
 int pass_a_shifted_lanes(const uint8_t* x, int64_t row_bytes, int64_t n_blocks, int block_len, int n_cu) {
   const int64_t cg = (row_bytes + 18) / 16, units = cg * n_blocks;
   if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0) return 0;
   if (cg < (block_len < 128 ? 64 : 8) || block_len < 64 || units < (block_len < 128 ? 1 << 17 : 1024) ||
-      units * block_len < 1 << 18 || (block_len >= 192 && units > 60000) || (cg <= 9 && units > 15000) ||
+      units * block_len < 1 << 18 || (cg <= 9 && units > 15000) ||
+      (block_len >= 192 && units > 60000 && ((cg >= 64 && units <= 256 * (int64_t)n_cu) || (block_len > 240 && block_len < 400 && cg >= 16 && cg < 32))) ||
       row_bytes >= (1 << 24) || units >= ((int64_t)1 << 30) || (512 / cg + 2) * block_len * row_bytes >= ((int64_t)1 << 31))
     return 0;
   int lanes = 16;

@@ -64,8 +64,14 @@ def test_routes_of_pass_a(dispatch):
     calls = [(2, 8, 1695, 1800, 0, 0), (16, 1, 1700, 1102, 0, 0), (16, 1, 640, 29296, 8, 0), (16, 1, 80, 23437, 8, 0),
              (50, 4, 24, 6250, 0, 0), (104, 1, 200, 14423, 0, 0), (8, 8, 256, 7934, 4, 0), (300, 2, 33, 3535, 0, 0),
              (39, 3, 128, 20905, 0, 0), (123, 1, 392, 3209, 0, 0), (104, 1, 24, 801, 0, 0), (48, 1, 40, 52083, 0, 0), (400, 4, 34, 4183, 0, 256), (16, 1, 1024, 6739, 0, 16),
-             (4, 8, 40, 101562, 0, 32), (50, 4, 40, 37500, 0, 512), (88, 4, 128, 6658, 4, 64), (104, 1, 128, 2253, 0, 32),
-             (256, 4, 256, 192, 0, 16), (1000, 3, 256, 128, 0, 128), (16, 1, 128, 60000, 0, 16)]
+             (4, 8, 40, 101562, 0, 32), (104, 1, 40, 37500, 0, 512), (88, 4, 128, 6658, 4, 64), (104, 1, 128, 2253, 0, 32),
+             (256, 4, 256, 192, 0, 16), (1000, 3, 256, 128, 0, 128), (16, 1, 128, 60000, 0, 16),
+             # Rows of dwords off 16-byte boundaries.
+             (50, 4, 40, 37500, 0, 0), (8, 4, 1024, 12206, 8, 0), (8, 4, 128, 48828, 8, 16), (16, 4, 140, 3348, 8, 0), (20, 4, 140, 17857, 4, 0),
+             (28, 4, 64, 4185, 4, 0), (60, 4, 64, 5208, 4, 0), (60, 4, 64, 1953, 4, 32), (64, 4, 256, 3051, 8, 0), (64, 4, 512, 1525, 8, 128),
+             (512, 1, 50, 3125, 8, 0), (512, 1, 56, 2790, 8, 128), (12, 3, 1757, 3815, 8, 16), (16, 3, 1800, 4000, 4, 0),
+             # Many units of rows off 4-byte boundaries.
+             (500, 2, 192, 2187, 1, -128), (640, 2, 256, 1067, 1, -128), (350, 1, 256, 5357, 0, 512), (350, 1, 512, 2678, 0, -128)]
     out = dispatch(f"""
         o = outs()
         for N, F, M, B, off, units in {calls!r}:
@@ -74,7 +80,8 @@ def test_routes_of_pass_a(dispatch):
             log()
             assert sk.sk_compute(h, ctypes.c_void_p(X.value + off), None, ctypes.byref(o), None) == 0, sk.sk_last_error()
             name = launches()[0]
-            if (f"phased_kernelILi{{units}}E" not in name) if units else ("phased" in name or "shifted" in name):
+            kind = "shifted" if units < 0 else "phased"   # (below 0: shifted row phases)
+            if (f"{{kind}}_kernelILi{{abs(units)}}E" not in name) if units else ("phased" in name or "shifted" in name):
                 print(N, F, M, B, off, name)
             sk.sk_plan_destroy(h)
         """)
